@@ -5,7 +5,7 @@
 // App. D row normaliser:
 //   K' = E K, V' = F V;  PhiK = phi(K') (shifted);  S = PhiK^T V';  z = PhiK^T 1
 //   P = phi(Q) (shifted per row);  out = (P S) / (P z)
-#include "flurka_internal.h"
+#include "flurka_gemm_f32.h"
 
 namespace flurka {
 
@@ -15,156 +15,67 @@ namespace flurka {
     } while (0)
 
 // ---------------------------------------------------------------------------
-// Strided batched GEMM, C[b,h] (M x N) (+)= A[b,h] (M x K) * B[b,h] (K x N).
-// Every operand is addressed through element strides, so transposes, shared
-// operands (batch stride 0) and a reduction index that runs over (batch, d)
-// pairs (K = Kout * Kin with separate strides) need no copies.
+// GEMM launches (flurka_gemm_f32.h)
 // ---------------------------------------------------------------------------
-struct GemmArgs {
-    const void* A;
-    const void* B;
-    void* C;
-    int M, N, K, Kin;
-    long sAm, sAki, sAko, sAb, sAh;
-    long sBn, sBki, sBko, sBb, sBh;
-    long sCm, sCn, sCb, sCh;
-    int H;
-    int a_bf16, b_bf16, c_bf16;
-    int accumulate;
-    int a_kfast, b_kfast;
-};
-
-constexpr int GT = 64;   // output tile edge
-constexpr int GK = 16;   // reduction step
-
-__global__ __launch_bounds__(256) void gemm_generic_kernel(GemmArgs g) {
-    __shared__ float As[GK][GT + 4];
-    __shared__ float Bs[GK][GT + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int tiles_n = (g.N + GT - 1) / GT;
-    const int m0 = (int)(blockIdx.x / tiles_n) * GT, n0 = (int)(blockIdx.x % tiles_n) * GT;
-    const int b = blockIdx.z / g.H, h = blockIdx.z % g.H;
-    const long aoff = (long)b * g.sAb + (long)h * g.sAh;
-    const long boff = (long)b * g.sBb + (long)h * g.sBh;
-    const long coff = (long)b * g.sCb + (long)h * g.sCh;
-
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-    // this thread's four elements of the A tile and of the B tile: LDS positions (fixed) and the loads of
-    // one reduction step; the loads of step k0 + GK are in flight while step k0 is being multiplied
-    int a_mm[4], a_kk[4], b_nn[4], b_kk[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (g.a_kfast) { a_kk[i] = tid & 15; a_mm[i] = (tid >> 4) + 16 * i; }
-        else           { a_mm[i] = tid & 63; a_kk[i] = (tid >> 6) + 4 * i; }
-        if (g.b_kfast) { b_kk[i] = tid & 15; b_nn[i] = (tid >> 4) + 16 * i; }
-        else           { b_nn[i] = tid & 63; b_kk[i] = (tid >> 6) + 4 * i; }
-    }
-    const bool one_level = g.Kin >= g.K;        // the reduction index is not a (outer, inner) pair
-    // element offsets of reduction step 0 (one-level index: a step adds GK * stride)
-    long pa[4], pb[4];
-    bool va[4], vb[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        va[i] = m0 + a_mm[i] < g.M;
-        vb[i] = n0 + b_nn[i] < g.N;
-        pa[i] = aoff + (long)(m0 + a_mm[i]) * g.sAm + (long)a_kk[i] * g.sAki;
-        pb[i] = boff + (long)(n0 + b_nn[i]) * g.sBn + (long)b_kk[i] * g.sBki;
-    }
-    float ra[4], rb[4];
-    auto fetch = [&](int k0) {
-        if (one_level) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                ra[i] = (va[i] && k0 + a_kk[i] < g.K) ? load_elem(g.A, pa[i] + (long)k0 * g.sAki, g.a_bf16) : 0.f;
-                rb[i] = (vb[i] && k0 + b_kk[i] < g.K) ? load_elem(g.B, pb[i] + (long)k0 * g.sBki, g.b_bf16) : 0.f;
-            }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int gm = m0 + a_mm[i], gk = k0 + a_kk[i];
-            float v = 0.f;
-            if (gm < g.M && gk < g.K) {
-                const int ko = gk / g.Kin, ki = gk - ko * g.Kin;
-                v = load_elem(g.A, aoff + (long)gm * g.sAm + (long)ki * g.sAki + (long)ko * g.sAko, g.a_bf16);
-            }
-            ra[i] = v;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int gn = n0 + b_nn[i], gk = k0 + b_kk[i];
-            float v = 0.f;
-            if (gn < g.N && gk < g.K) {
-                const int ko = gk / g.Kin, ki = gk - ko * g.Kin;
-                v = load_elem(g.B, boff + (long)gn * g.sBn + (long)ki * g.sBki + (long)ko * g.sBko, g.b_bf16);
-            }
-            rb[i] = v;
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < g.K; k0 += GK) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            As[a_kk[i]][a_mm[i]] = ra[i];
-            Bs[b_kk[i]][b_nn[i]] = rb[i];
-        }
-        __syncthreads();
-        if (k0 + GK < g.K) fetch(k0 + GK);
-        // two-level summation: a 16-term partial, then one add into the running sum
-        float part[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) part[i][j] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < GK; ++kk) {
-            float a[4], bb[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bb[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) part[i][j] = fmaf(a[i], bb[j], part[i][j]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] += part[i][j];
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int gm = m0 + ty * 4 + i;
-        if (gm >= g.M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int gn = n0 + tx * 4 + j;
-            if (gn >= g.N) continue;
-            const long ci = coff + (long)gm * g.sCm + (long)gn * g.sCn;
-            float v = acc[i][j];
-            if (g.accumulate) v += ((const float*)g.C)[ci];
-            store_elem(g.C, ci, v, g.c_bf16);
-        }
-    }
-}
-
-static flurka_status launch_gemm(GemmArgs g, int batches, hipStream_t s) {
-    g.a_kfast = (g.sAki == 1);
-    g.b_kfast = (g.sBki == 1);
-    const long tiles = (long)((g.N + GT - 1) / GT) * ((g.M + GT - 1) / GT);
-    dim3 grid((unsigned)tiles, 1, batches);
-    hipLaunchKernelGGL(gemm_generic_kernel, grid, dim3(256), 0, s, g);
+template <bool AKF, bool BKF, int TM, int TN>
+static flurka_status launch_gemm_tile(const GemmArgs& g, int splits, hipStream_t s) {
+    const long tiles = (long)((g.N + TN - 1) / TN) * ((g.M + TM - 1) / TM);
+    hipLaunchKernelGGL((gemm_f32_kernel<AKF, BKF, TM, TN>), dim3((unsigned)tiles, (unsigned)splits, (unsigned)(g.batches * (g.C2 ? 2 : 1))),
+                       dim3(256), 0, s, g);
     FLURKA_CHECK_LAUNCH();
     return FLURKA_OK;
 }
+
+template <bool AKF, bool BKF>
+static flurka_status launch_gemm_layout(GemmArgs g, float* part, size_t part_floats, hipStream_t s) {
+    // Larger tiles halve the operand traffic per product; smaller ones give more workgroups.  A tile edge
+    // of 128 is taken where the result still has two workgroups per compute unit.
+    const long many = 2L * chip_cus();
+    const long batches = (long)g.batches * (g.C2 ? 2 : 1);
+    auto tiles = [&](int tm, int tn) { return (long)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * batches; };
+    const int tm = g.M > 64 && tiles(128, 64) >= many ? 128 : 64;
+    const int tn = tm == 128 && g.N > 64 && tiles(128, 128) >= many ? 128 : 64;
+    // Split the reduction where the tiles alone leave compute units idle, into ranges of at least two steps.
+    const int steps = (g.K + F_GK - 1) / F_GK;
+    int splits = 1;
+    if (part && tiles(tm, tn) < many) {
+        const size_t count = (size_t)batches * g.M * g.N;
+        splits = (int)(many / tiles(tm, tn));
+        if (splits > steps / 2) splits = steps / 2;
+        if (splits > 32) splits = 32;
+        if ((size_t)splits > part_floats / count) splits = (int)(part_floats / count);
+        if (splits < 1) splits = 1;
+    }
+    g.steps_per_split = (steps + splits - 1) / splits;
+    splits = (steps + g.steps_per_split - 1) / g.steps_per_split;
+    g.part = splits > 1 ? part : nullptr;
+    flurka_status st = tm == 64 ? launch_gemm_tile<AKF, BKF, 64, 64>(g, splits, s)
+                       : tn == 64 ? launch_gemm_tile<AKF, BKF, 128, 64>(g, splits, s)
+                                  : launch_gemm_tile<AKF, BKF, 128, 128>(g, splits, s);
+    if (st != FLURKA_OK || splits == 1) return st;
+    const long count = (long)g.batches * g.M * g.N;
+    hipLaunchKernelGGL(gemm_f32_sum_kernel, dim3((unsigned)((count + 255) / 256), g.C2 ? 2u : 1u), dim3(256), 0, s, (float*)g.C,
+                       (float*)g.C2, (const float*)g.part, splits, count);
+    FLURKA_CHECK_LAUNCH();
+    return FLURKA_OK;
+}
+
+flurka_status launch_gemm_f32(GemmArgs g, int batches, float* part, size_t part_floats, hipStream_t s) {
+    g.batches = batches;
+    if (g.C2 && 2L * batches > 65535) {        // more batches than a grid dimension takes: one GEMM at a time
+        GemmArgs g2 = g;
+        g2.A = g.A2; g2.B = g.B2; g2.C = g.C2;
+        g.A2 = g.B2 = nullptr; g.C2 = nullptr;
+        g2.A2 = g2.B2 = nullptr; g2.C2 = nullptr;
+        const flurka_status st = launch_gemm_f32(g, batches, part, part_floats, s);
+        return st != FLURKA_OK ? st : launch_gemm_f32(g2, batches, part, part_floats, s);
+    }
+    const bool akf = g.sAki == 1, bkf = g.sBki == 1;
+    if (akf) return bkf ? launch_gemm_layout<true, true>(g, part, part_floats, s) : launch_gemm_layout<true, false>(g, part, part_floats, s);
+    return bkf ? launch_gemm_layout<false, true>(g, part, part_floats, s) : launch_gemm_layout<false, false>(g, part, part_floats, s);
+}
+
+static flurka_status launch_gemm(const GemmArgs& g, int batches, hipStream_t s) { return launch_gemm_f32(g, batches, nullptr, 0, s); }
 
 // ---------------------------------------------------------------------------
 // Row-wise kernels.  One 64-lane wavefront per row, four rows per block.
@@ -402,16 +313,18 @@ static flurka_status query_features_and_numerator(const Problem& p, const void* 
     return launch_gemm(g, p.BH, s);
 }
 
-// K' or V' (B,H,k,d) <- E (k,n) X (B,H,n,d)
-static flurka_status project(const Problem& p, const void* E, const void* X, float* Xp, hipStream_t s) {
+// K' = E K, V' = F V: (B,H,k,d) <- (k,n) (B,H,n,d).  `part`: scratch for a split reduction.
+static flurka_status project(const Problem& p, const FwdArgs& a, float* Kp, float* Vp, float* part, size_t part_floats,
+                             hipStream_t s) {
     GemmArgs g{};
-    g.A = E; g.B = X; g.C = Xp;
+    g.A = a.E; g.B = a.K; g.C = Kp;
+    g.A2 = a.F; g.B2 = a.V; g.C2 = Vp;
     g.M = p.k; g.N = p.d; g.K = p.n; g.Kin = p.n;
     g.sAm = p.n; g.sAki = 1; g.sAb = 0; g.sAh = p.ef_per_head ? (long)p.k * p.n : 0;
     g.sBn = 1; g.sBki = p.d; g.sBb = (long)p.H * p.n * p.d; g.sBh = (long)p.n * p.d;
     g.sCm = p.d; g.sCn = 1; g.sCb = (long)p.H * p.k * p.d; g.sCh = (long)p.k * p.d;
     g.H = p.H; g.a_bf16 = p.bf16; g.b_bf16 = p.bf16;
-    return launch_gemm(g, p.BH, s);
+    return launch_gemm_f32(g, p.BH, part, part_floats, s);
 }
 
 // PhiK (k x mf, shifted) from K' in ctx.  With `new_shift` the per-feature shifts c are computed
@@ -487,8 +400,8 @@ flurka_status generic_forward(const Problem& p, const FwdArgs& a, hipStream_t s)
     flurka_status st;
     {
         StageScope sc(s, STAGE_PROJECT);
-        if ((st = project(p, a.E, a.K, a.ctx + L.Kp, s)) != FLURKA_OK) return st;
-        if ((st = project(p, a.F, a.V, a.ctx + L.Vp, s)) != FLURKA_OK) return st;
+        // nothing of the workspace is in use yet: all of it may hold split partials
+        if ((st = project(p, a, a.ctx + L.Kp, a.ctx + L.Vp, a.ws, W.total, s)) != FLURKA_OK) return st;
     }
     {
         StageScope sc(s, STAGE_KEY_STATE);
@@ -694,9 +607,10 @@ flurka_status generic_backward_from(const Problem& p, const BwdArgs& a, hipStrea
 
     // dK = E^T dK', dV = F^T dV'   (n x d per head)
     stage_begin(s);
-    for (int which = 0; which < 2; ++which) {
+    {
         GemmArgs g{};
-        g.A = which ? a.F : a.E; g.B = which ? dVp : dKp; g.C = which ? a.dV : a.dK;
+        g.A = a.E; g.B = dKp; g.C = a.dK;
+        g.A2 = a.F; g.B2 = dVp; g.C2 = a.dV;
         g.M = p.n; g.N = p.d; g.K = p.k; g.Kin = p.k;
         g.sAm = 1; g.sAki = p.n; g.sAb = 0; g.sAh = p.ef_per_head ? (long)p.k * p.n : 0;
         g.sBn = 1; g.sBki = p.d; g.sBb = (long)p.H * p.k * p.d; g.sBh = (long)p.k * p.d;
@@ -707,9 +621,10 @@ flurka_status generic_backward_from(const Problem& p, const BwdArgs& a, hipStrea
     stage_end(s, STAGE_BWD_DKDV);
     // dE = sum_bh dK' K^T, dF = sum_bh dV' V^T   (k x n); reduction index = (bh, t)
     stage_begin(s);
-    for (int which = 0; which < 2; ++which) {
+    {
         GemmArgs g{};
-        g.A = which ? dVp : dKp; g.B = which ? a.V : a.K; g.C = which ? a.dF : a.dE;
+        g.A = dKp; g.B = a.K; g.C = a.dE;
+        g.A2 = dVp; g.B2 = a.V; g.C2 = a.dF;
         g.M = p.k; g.N = p.n; g.Kin = p.d;
         g.sAm = p.d; g.sAki = 1; g.sBn = p.d; g.sBki = 1; g.sCm = p.n; g.sCn = 1;
         g.b_bf16 = p.bf16; g.c_bf16 = p.bf16 && !p.grad_ef_f32;
