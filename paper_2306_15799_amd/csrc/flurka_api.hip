@@ -165,7 +165,7 @@ flurka_status forward_impl(const void* Q, const void* K, const void* V, const vo
     if (algo == FLURKA_ALGO_FAST && !fast_ok) return FLURKA_ERR_UNSUPPORTED;
     const bool use_fast = (algo != FLURKA_ALGO_GENERIC) && fast_ok;
     if (ctx_bytes < ctx_layout(p).total * sizeof(float)) return FLURKA_ERR_WORKSPACE;
-    const size_t need = use_fast ? fast_ws_bytes(p, 0) : generic_ws_layout(p, 0).total * sizeof(float);
+    const size_t need = use_fast ? fast_ws_bytes(p, 0) : generic_ws_floats(p, 0) * sizeof(float);
     if (workspace_bytes < need) return FLURKA_ERR_WORKSPACE;
     if (own_scratch && !(workspace = static_scratch())) return FLURKA_ERR_LAUNCH;
 
@@ -228,7 +228,7 @@ size_t flurka_workspace_bytes(int B, int H, int n, int d, int k, int m, flurka_d
     if (pass != FLURKA_PASS_FWD && pass != FLURKA_PASS_BWD) return 0;
     if (!valid_algo(algo)) return 0;
     const int bwd = (pass == FLURKA_PASS_BWD);
-    const size_t gen = generic_ws_layout(p, bwd).total * sizeof(float);
+    const size_t gen = generic_ws_floats(p, bwd) * sizeof(float);
     const size_t fast = fast_supported(p, bwd) ? fast_ws_bytes(p, bwd) : 0;
     if (algo == FLURKA_ALGO_GENERIC) return gen;
     if (algo == FLURKA_ALGO_FAST) return fast;
@@ -384,7 +384,7 @@ flurka_status backward_impl(const void* Q, const void* K, const void* V, const v
     if (algo == FLURKA_ALGO_FAST && !fast_ok) return FLURKA_ERR_UNSUPPORTED;
     const bool use_fast = (algo != FLURKA_ALGO_GENERIC) && fast_ok;
     if (ctx_bytes < ctx_layout(p).total * sizeof(float)) return FLURKA_ERR_WORKSPACE;
-    const size_t need = use_fast ? fast_ws_bytes(p, 1) : generic_ws_layout(p, 1).total * sizeof(float);
+    const size_t need = use_fast ? fast_ws_bytes(p, 1) : generic_ws_floats(p, 1) * sizeof(float);
     if (workspace_bytes < need) return FLURKA_ERR_WORKSPACE;
 
     BwdArgs a{Q, K, V, E, F, omega, out, dOut, (const float*)ctx, dQ, dK, dV, dE, dF, (float*)workspace, (float*)d_omega};

@@ -274,17 +274,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
             }
 }
 
-// C (and C2), contiguous (batch, M, N) fp32, from the split partials
-__global__ __launch_bounds__(256) void gemm_f32_sum_kernel(float* C, float* C2, const float* part, int splits, long count) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= count) return;
-    const long plane = count * (C2 ? 2 : 1);
-    const float* p = part + (blockIdx.y ? count : 0) + i;
-    float s = 0.f;
-    for (int u = 0; u < splits; ++u) s += p[u * plane];
-    (blockIdx.y ? C2 : C)[i] = s;
-}
-
 // `part`, `part_floats`: scratch for a split reduction (only for contiguous fp32 results: C[b,h][m][n] at
 // ((b H + h) M + m) N + n); nullptr if the reduction must not be split.
 flurka_status launch_gemm_f32(GemmArgs g, int batches, float* part, size_t part_floats, hipStream_t s);

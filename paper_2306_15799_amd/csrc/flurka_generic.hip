@@ -17,6 +17,17 @@ namespace flurka {
 // ---------------------------------------------------------------------------
 // GEMM launches (flurka_gemm_f32.h)
 // ---------------------------------------------------------------------------
+// C (and C2), contiguous (batch, M, N) fp32, from the split partials
+__global__ __launch_bounds__(256) void gemm_f32_sum_kernel(float* C, float* C2, const float* part, int splits, long count) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= count) return;
+    const long plane = count * (C2 ? 2 : 1);
+    const float* p = part + (blockIdx.y ? count : 0) + i;
+    float s = 0.f;
+    for (int u = 0; u < splits; ++u) s += p[u * plane];
+    (blockIdx.y ? C2 : C)[i] = s;
+}
+
 template <bool AKF, bool BKF, int TM, int TN>
 static flurka_status launch_gemm_tile(const GemmArgs& g, int splits, hipStream_t s) {
     const long tiles = (long)((g.N + TN - 1) / TN) * ((g.M + TM - 1) / TM);
@@ -368,7 +379,7 @@ static flurka_status key_features(const Problem& p, const void* omega, const flo
 }
 
 // PhiK, S, z, c from K', V' (in ctx)
-flurka_status generic_key_state(const Problem& p, const void* omega, float* ctx, float* Phi, hipStream_t s) {
+static flurka_status generic_key_state(const Problem& p, const void* omega, float* ctx, float* Phi, hipStream_t s) {
     const CtxLayout L = ctx_layout(p);
     float* Vp = ctx + L.Vp;
     float* S = ctx + L.S;
@@ -405,7 +416,13 @@ flurka_status generic_forward(const Problem& p, const FwdArgs& a, hipStream_t s)
     }
     {
         StageScope sc(s, STAGE_KEY_STATE);
-        if ((st = generic_key_state(p, a.omega, a.ctx, a.ws + W.PhiK, s)) != FLURKA_OK) return st;
+        st = f32_fused_supported(p) ? f32_key_state(p, a.omega, a.ctx, s)
+                                    : generic_key_state(p, a.omega, a.ctx, a.ws + W.PhiK, s);
+        if (st != FLURKA_OK) return st;
+    }
+    if (f32_fused_supported(p)) {
+        StageScope sc(s, STAGE_QUERY);
+        return f32_query_forward(p, a, s);
     }
     const int nc = generic_chunk_rows(p);
     float* P = a.ws + W.P;
@@ -432,15 +449,31 @@ flurka_status generic_forward(const Problem& p, const FwdArgs& a, hipStream_t s)
 //              rescaling of a row of P);  elu1: dx = dphi * phi'(x)
 //   dK = E^T dK', dV = F^T dV', dE = sum_bh dK' K^T, dF = sum_bh dV' V^T
 // ---------------------------------------------------------------------------
-flurka_status generic_backward(const Problem& p, const BwdArgs& a, hipStream_t s) {
-    return generic_backward_from(p, a, s, 0);
+// The four sequence-length GEMMs from dK', dV' (fp32)
+static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const float* dKp, const float* dVp, hipStream_t s);
+
+// head sizes up to 128: the query and key side on the fused kernels (flurka_f32.hip)
+static flurka_status fused_backward(const Problem& p, const BwdArgs& a, hipStream_t s) {
+    const F32BwdWs W = f32_bwd_ws_layout(p);
+    flurka_status st;
+    {
+        StageScope sc(s, STAGE_BWD_QUERY);
+        if ((st = f32_query_backward(p, a, s)) != FLURKA_OK) return st;
+    }
+    {
+        StageScope sc(s, STAGE_BWD_KEY);
+        if ((st = f32_key_backward(p, a, s)) != FLURKA_OK) return st;
+    }
+    return grad_gemms_f32(p, a, a.ws + W.dKp, a.ws + W.dVp, s);
 }
 
-// `done` bit 0: the caller has already written dQ and left dS, dz in the workspace slots of the
-// generic layout.  Bit 1: stop after the key side (dK', dV' in the workspace); the caller runs the
-// four sequence-length GEMMs itself.
-flurka_status generic_backward_from(const Problem& p, const BwdArgs& a, hipStream_t s, int done) {
-    const int query_done = done & 1;
+size_t generic_ws_floats(const Problem& p, int bwd) {
+    if (bwd && f32_fused_supported(p)) return f32_bwd_ws_layout(p).total;
+    return generic_ws_layout(p, bwd).total;
+}
+
+flurka_status generic_backward(const Problem& p, const BwdArgs& a, hipStream_t s) {
+    if (f32_fused_supported(p)) return fused_backward(p, a, s);
     const CtxLayout L = ctx_layout(p);
     const GenericWs W = generic_ws_layout(p, 1);
     const float* Kp = a.ctx + L.Kp;
@@ -463,8 +496,8 @@ flurka_status generic_backward_from(const Problem& p, const BwdArgs& a, hipStrea
     flurka_status st;
     const int nc = generic_chunk_rows(p);
 
-    if (!query_done) stage_begin(s);
-    for (int row0 = 0; row0 < p.n && !query_done; row0 += nc) {
+    stage_begin(s);
+    for (int row0 = 0; row0 < p.n; row0 += nc) {
         const int nr = (p.n - row0 < nc) ? (p.n - row0) : nc;
         const long rows = (long)p.BH * nr;
         st = query_features_and_numerator(p, a.Q, a.omega, S, cshift, P, N, row0, nr, nullptr, s);
@@ -538,7 +571,7 @@ flurka_status generic_backward_from(const Problem& p, const BwdArgs& a, hipStrea
         }
     }
 
-    if (!query_done) stage_end(s, STAGE_BWD_QUERY);
+    stage_end(s, STAGE_BWD_QUERY);
 
     stage_begin(s);
     const long krows = (long)p.BH * p.k;
@@ -603,8 +636,11 @@ flurka_status generic_backward_from(const Problem& p, const BwdArgs& a, hipStrea
     }
 
     stage_end(s, STAGE_BWD_KEY);
-    if (done & 2) return FLURKA_OK;
+    return grad_gemms_f32(p, a, dKp, dVp, s);
+}
 
+static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const float* dKp, const float* dVp, hipStream_t s) {
+    flurka_status st;
     // dK = E^T dK', dV = F^T dV'   (n x d per head)
     stage_begin(s);
     {

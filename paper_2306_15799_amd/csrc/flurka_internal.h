@@ -84,6 +84,10 @@ static inline GenericWs generic_ws_layout(const Problem& p, int bwd) {
     return W;
 }
 
+// Scratch of the generic path in floats.  The fused kernels (d <= 128) need no room in the forward beyond
+// split partials of the projection, for which they use what the unfused ones would take.
+size_t generic_ws_floats(const Problem& p, int bwd);
+
 struct FwdArgs {
     const void *Q, *K, *V, *E, *F, *omega;
     void* out;
@@ -102,7 +106,18 @@ struct BwdArgs {
 // Each returns FLURKA_OK or FLURKA_ERR_LAUNCH.
 flurka_status generic_forward(const Problem& p, const FwdArgs& a, hipStream_t s);
 flurka_status generic_backward(const Problem& p, const BwdArgs& a, hipStream_t s);
-flurka_status generic_backward_from(const Problem& p, const BwdArgs& a, hipStream_t s, int query_done);
+
+// Fused kernels of the same path (flurka_f32.hip) for head sizes up to 128.
+bool f32_fused_supported(const Problem& p);
+struct F32BwdWs {
+    size_t delta, dinv, dSpart, dzpart, dS, dz, dKp, dVp, dWpart, dU, dWkey;   // float offsets
+    size_t plain, total;       // floats without / with what the gradient for omega needs
+};
+F32BwdWs f32_bwd_ws_layout(const Problem& p);
+flurka_status f32_key_state(const Problem& p, const void* omega, float* ctx, hipStream_t s);    // S, z, c from K', V'
+flurka_status f32_query_forward(const Problem& p, const FwdArgs& a, hipStream_t s);             // out, lse
+flurka_status f32_query_backward(const Problem& p, const BwdArgs& a, hipStream_t s);            // dQ, dS, dz
+flurka_status f32_key_backward(const Problem& p, const BwdArgs& a, hipStream_t s);              // dK', dV' (d omega)
 
 // ---- stage timer -------------------------------------------------------------
 enum Stage {
@@ -187,8 +202,6 @@ size_t fast_baseline_ws_bytes(int which, const Problem& p);
 size_t fast_baseline_ctx_floats(int which, const Problem& p);
 flurka_status fast_kernel_attn_forward(const Problem& p, const FwdArgs& a, hipStream_t s);   // p.k == p.n
 flurka_status fast_linformer_forward(const Problem& p, const FwdArgs& a, hipStream_t s);
-// Key-side state from K', V' already in ctx: PhiK (scratch, BH*k*mf floats), S, z and the shifts c.
-flurka_status generic_key_state(const Problem& p, const void* omega, float* ctx, float* PhiK, hipStream_t s);
 
 // ---- device helpers --------------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
