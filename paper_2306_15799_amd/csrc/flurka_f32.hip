@@ -29,12 +29,6 @@ namespace flurka {
 
 constexpr float F32_LOG2E = FLURKA_LOG2E;
 
-typedef short f32_short4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint2 f32_read_tr16(const unsigned char* p) {
-    const f32_short4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((f32_short4 __attribute__((address_space(3)))*)p);
-    return __builtin_bit_cast(uint2, v);
-}
-
 __device__ __forceinline__ float f32_elu1(float x) { return x > 0.f ? x + 1.f : expf(x); }
 
 // ---- rows in memory -> operands ------------------------------------------------
@@ -93,8 +87,6 @@ __device__ __forceinline__ float4 any_load4(const void* p, long off, int c0, int
     return make_float4(pair_lo(w[0]), pair_hi(w[0]), pair_lo(w[1]), pair_hi(w[1]));
 }
 
-// T terms of 8 values, each an operand of mfma32.  T = 1: a bf16 operand as stored; T = 3: an fp32 operand.
-template <int T> struct Terms { uint4 t[T]; };
 // 8 values as loaded, before the split
 template <int T> struct Raw8 { float v[8]; };
 template <> struct Raw8<1> { uint4 v; };
@@ -122,17 +114,6 @@ __device__ __forceinline__ Terms<T> to_terms(const Raw8<T>& r) {
     return x;
 }
 
-// acc += A B over the terms, smallest products first
-template <int TA, int TB>
-__device__ __forceinline__ floatx16 mfma_terms(const uint4 (&a)[TA], const uint4 (&b)[TB], floatx16 acc) {
-#pragma unroll
-    for (int s = 2; s >= 0; --s)
-#pragma unroll
-        for (int i = 0; i < TA; ++i)
-            if (s - i >= 0 && s - i < TB) acc = mfma32(a[i], b[s - i], acc);
-    return acc;
-}
-
 // An accumulator tile's 16 values as T operand terms for the two 16-slot halves of the next reduction.
 template <int T>
 __device__ __forceinline__ void split_acc(const float (&v)[16], uint4 (&t)[2][T]) {
@@ -150,40 +131,6 @@ __device__ __forceinline__ void split_acc(const float (&v)[16], uint4 (&t)[2][T]
         for (int i = 0; i < T; ++i) t[sp][i] = make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]);
     }
 }
-
-// ---- 32 x D bf16 tile in LDS -----------------------------------------------------
-// Unpadded rows; 16-byte chunk c of row r sits at position c ^ swz(r), which makes both kinds of read
-// conflict-free (see BwdXLds in flurka_bwd.hip, where this layout comes from):
-//   row_frag   8 consecutive columns of row l32          (rows are the operand's free index)
-//   col_frag   column 32t + l32 of 8 rows of a 16-row group, in accumulator order   (rows are reduced over)
-template <int D>
-struct Tile32 {
-    static_assert(D == 64 || D == 128, "row swizzles are written for 128- and 256-byte rows");
-    static constexpr int pitch = D * 2, bytes = 32 * pitch, chunks = 32 * D / 8;
-    static __device__ __forceinline__ int swz(int r) {
-        return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-    }
-    static __device__ __forceinline__ unsigned char* chunk(unsigned char* t, int r, int c) { return t + r * pitch + 16 * (c ^ swz(r)); }
-    int row_off, row_xor, tr_row, tr_low, tr_hi;
-    __device__ __forceinline__ explicit Tile32(int lane) {
-        const int half = lane >> 5, l32 = lane & 31, s16 = lane & 15, r4 = s16 >> 2;
-        row_off = l32 * pitch;
-        row_xor = 16 * (swz(l32) ^ half);
-        tr_row = (4 * half + r4) * pitch + 8 * (s16 & 1);
-        tr_low = 16 * ((2 * ((lane >> 4) & 1) + ((s16 >> 1) & 1)) ^ half);
-        tr_hi = D == 128 ? r4 : (r4 >> 1);
-    }
-    __device__ __forceinline__ uint4 row_frag(const unsigned char* t, int s) const {
-        return *(const uint4*)(t + row_off + ((32 * s) ^ row_xor));
-    }
-    __device__ __forceinline__ uint4 col_frag(const unsigned char* t, int sp, int tt) const {
-        const unsigned char* fb = t + 16 * sp * pitch + tr_row;
-        const int col = ((tt ^ tr_hi) << 6) + tr_low;
-        const uint2 w0 = f32_read_tr16(fb + col);
-        const uint2 w1 = f32_read_tr16(fb + 8 * pitch + (col ^ 32));
-        return make_uint4(w0.x, w0.y, w1.x, w1.y);
-    }
-};
 
 // position of feature / row f of a 32-row tile in a per-row vector kept in accumulator order (16h + g)
 __device__ __forceinline__ int acc_slot(int f) { return 16 * ((f >> 2) & 1) + 4 * (f >> 3) + (f & 3); }

@@ -1,9 +1,13 @@
-// Strided batched GEMM with fp32 operands, products and sums on the matrix cores of gfx950
-// (v_mfma_f32_32x32x2_f32), for every contraction of the fp32-arithmetic path:
+// Strided batched GEMM of fp32 accuracy on the matrix cores of gfx950, for every contraction of the
+// fp32-arithmetic path that runs over the sequence:
 //     C[b,h] (M x N) (+)= A[b,h] (M x K) B[b,h] (K x N)
-// Operands are addressed through element strides, so transposes, shared operands (batch stride 0) and a
-// reduction index that runs over (outer, inner) pairs (K = Kout * Kin with separate strides) need no
-// copies.  bf16 operands are widened to fp32 on their way into LDS; nothing is rounded.
+// Operands are addressed through element strides, so transposes, shared operands (batch stride 0), a
+// reduction index that runs over (outer, inner) pairs (K = Kout * Kin) and result columns that run over
+// (head, coordinate) pairs (N = Nout * Nin) need no copies.
+//
+// Beside a bf16 operand, which enters as it is, an fp32 operand enters as three bf16 terms (8 + 8 + 8 = 24
+// mantissa bits: the split is exact, and so are the products).  Two fp32 operands are multiplied by the
+// fp32 matrix instruction.
 #pragma once
 
 #include "flurka_mfma.h"
@@ -17,16 +21,180 @@ struct GemmArgs {
     const void* A2;      // operands and result of a second GEMM of the same shape in the same launch
     const void* B2;      // (nullptr: none)
     void* C2;
-    int M, N, K, Kin;
+    int M, N, K, Kin, Nin;                       // Nin = 0: one level of columns
     long sAm, sAki, sAko, sAb, sAh;
-    long sBn, sBki, sBko, sBb, sBh;
-    long sCm, sCn, sCb, sCh;
+    long sBn, sBki, sBko, sBb, sBh, sBno;        // sBno, sCno: between outer column indices
+    long sCm, sCn, sCb, sCh, sCno;
     int H;
     int a_bf16, b_bf16, c_bf16;
     int accumulate;
     // filled in by launch_gemm_f32
-    float* part;         // split partials [split][which][batch][M][N] (nullptr: the reduction is not split)
+    float* part;         // split partials [split][which], each laid out like C (nullptr: the reduction is not split)
     int batches, steps_per_split;
+    long c_count;        // elements of C (split reductions: C is contiguous)
+};
+
+// ---- operand terms ----------------------------------------------------------
+// T terms of 8 values, each an operand of mfma32.  T = 1: a bf16 operand as stored; T = 3: an fp32 operand.
+template <int T> struct Terms { uint4 t[T]; };
+
+// acc += A B over the terms, smallest products first.  Term i is at most 2^-9i of the value; of the products of
+// two split operands the six with i + j <= 2 are formed, the rest is below 2^-26 of the product: less than
+// the rounding of one fp32 addition.
+template <int TA, int TB>
+__device__ __forceinline__ floatx16 mfma_terms(const uint4 (&a)[TA], const uint4 (&b)[TB], floatx16 acc) {
+#pragma unroll
+    for (int s = 2; s >= 0; --s)
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+            if (s - i >= 0 && s - i < TB) acc = mfma32(a[i], b[s - i], acc);
+    return acc;
+}
+
+typedef short f32_short4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 f32_read_tr16(const unsigned char* p) {
+    const f32_short4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((f32_short4 __attribute__((address_space(3)))*)p);
+    return __builtin_bit_cast(uint2, v);
+}
+
+// ---- 32 x D bf16 tile in LDS ---------------------------------------------------
+// Unpadded rows; 16-byte chunk c of row r sits at position c ^ swz(r), which makes both kinds of read
+// conflict-free (see BwdXLds in flurka_bwd.hip, where this layout comes from):
+//   row_frag   8 consecutive columns of row l32          (rows are the operand's free index)
+//   col_frag   column 32t + l32 of 8 rows of a 16-row group, in accumulator order   (rows are reduced over):
+//              slot 8h + e of lane half h is row 8(e/4) + 4h + e%4 of the group
+template <int D>
+struct Tile32 {
+    static_assert(D == 64 || D == 128, "row swizzles are written for 128- and 256-byte rows");
+    static constexpr int pitch = D * 2, bytes = 32 * pitch, chunks = 32 * D / 8;
+    static __device__ __forceinline__ int swz(int r) {
+        return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+    }
+    static __device__ __forceinline__ unsigned char* chunk(unsigned char* t, int r, int c) { return t + r * pitch + 16 * (c ^ swz(r)); }
+    int row_off, row_xor, tr_row, tr_low, tr_hi;
+    __device__ __forceinline__ explicit Tile32(int lane) {
+        const int half = lane >> 5, l32 = lane & 31, s16 = lane & 15, r4 = s16 >> 2;
+        row_off = l32 * pitch;
+        row_xor = 16 * (swz(l32) ^ half);
+        tr_row = (4 * half + r4) * pitch + 8 * (s16 & 1);
+        tr_low = 16 * ((2 * ((lane >> 4) & 1) + ((s16 >> 1) & 1)) ^ half);
+        tr_hi = D == 128 ? r4 : (r4 >> 1);
+    }
+    __device__ __forceinline__ uint4 row_frag(const unsigned char* t, int s) const {
+        return *(const uint4*)(t + row_off + ((32 * s) ^ row_xor));
+    }
+    __device__ __forceinline__ uint4 col_frag(const unsigned char* t, int sp, int tt) const {
+        const unsigned char* fb = t + 16 * sp * pitch + tr_row;
+        const int col = ((tt ^ tr_hi) << 6) + tr_low;
+        const uint2 w0 = f32_read_tr16(fb + col);
+        const uint2 w1 = f32_read_tr16(fb + 8 * pitch + (col ^ 32));
+        return make_uint4(w0.x, w0.y, w1.x, w1.y);
+    }
+};
+
+// ---- operand tiles of the GEMM -----------------------------------------------------
+constexpr int F_GK = 32;                  // reduction step
+
+// 4 consecutive elements starting at element i, as 16 bytes (fp32, T = 3) or 8 bytes (bf16, T = 1) that need
+// no more than the element's own alignment
+template <int T> struct Raw4 { uint4 v; };
+template <> struct Raw4<1> { uint2 v; };
+template <int T>
+__device__ __forceinline__ Raw4<T> ld4_raw(const void* p, long i) {
+    Raw4<T> r;
+    if constexpr (T == 1) __builtin_memcpy(&r.v, (const uint16_t*)p + i, 8);
+    else                  __builtin_memcpy(&r.v, (const float*)p + i, 16);
+    return r;
+}
+// one element of a group at a time (edges of the operand); `keep` false: zero
+template <int T>
+__device__ __forceinline__ void set_elem(Raw4<T>& r, int e, const void* p, long i, bool keep) {
+    uint32_t* w = (uint32_t*)&r.v;
+    if constexpr (T == 1) {
+        uint32_t x = 0u;
+        if (keep) x = ((const uint16_t*)p)[i];
+        w[e >> 1] = (e & 1) ? (w[e >> 1] | (x << 16)) : x;
+    } else {
+        w[e] = keep ? ((const uint32_t*)p)[i] : 0u;
+    }
+}
+template <int T>
+__device__ __forceinline__ void split4(const Raw4<T>& r, uint2 (&t)[T]) {
+    if constexpr (T == 1) {
+        t[0] = r.v;
+    } else {
+        split3_pair(__uint_as_float(r.v.x), __uint_as_float(r.v.y), t[0].x, t[1].x, t[2].x);
+        split3_pair(__uint_as_float(r.v.z), __uint_as_float(r.v.w), t[0].y, t[1].y, t[2].y);
+    }
+}
+
+// One operand tile of TR free indices ("rows") x 32 reduction slots, T terms.
+// KF: the reduction index is the contiguous one in memory; the tile is kept [row][slot], 80-byte rows (16
+// consecutive rows start in 16 different groups of 4 banks), the four 4-slot groups of a 16-slot block in
+// the order 0, 2, 1, 3, so that a lane half's 8 slots in accumulator order are 16 consecutive bytes.
+// Otherwise the rows are contiguous; the tile is kept [slot][row] (Tile32) and fragments come out through
+// transposing reads, in the same slot order.
+template <bool KF, int TR, int T>
+struct GemmTile {
+    static constexpr int term = KF ? TR * 80 : Tile32<TR>::bytes;
+    static constexpr int bytes = T * term;
+    static constexpr int groups = TR * F_GK / 4 / 256;       // of 4 elements, per thread
+    static __device__ __forceinline__ void place(int tid, int i, int& r, int& kk) {
+        const int idx = tid + 256 * i;
+        if (KF) { r = idx >> 3; kk = 4 * (idx & 7); }
+        else    { kk = idx / (TR / 4); r = 4 * (idx % (TR / 4)); }
+    }
+    static __device__ __forceinline__ void store(unsigned char* t, int r, int kk, const Raw4<T>& x) {
+        uint2 w[T];
+        split4<T>(x, w);
+        unsigned char* p;
+        if (KF) {
+            const int g = (kk >> 2) & 3;
+            p = t + r * 80 + 32 * (kk >> 4) + 8 * (((g & 1) << 1) | (g >> 1));
+        } else {
+            p = Tile32<TR>::chunk(t, kk, r >> 3) + 2 * (r & 4);
+        }
+#pragma unroll
+        for (int k = 0; k < T; ++k) *(uint2*)(p + k * term) = w[k];
+    }
+    // fragment of rows 32 rt + l32, 16-slot block s
+    static __device__ __forceinline__ void frag(const unsigned char* t, int lane, int rt, int s, uint4 (&f)[T]) {
+        if (KF) {
+            const unsigned char* p = t + (32 * rt + (lane & 31)) * 80 + 32 * s + 16 * (lane >> 5);
+#pragma unroll
+            for (int k = 0; k < T; ++k) f[k] = *(const uint4*)(p + k * term);
+        } else {
+            const Tile32<TR> tl(lane);
+#pragma unroll
+            for (int k = 0; k < T; ++k) f[k] = tl.col_frag(t + k * term, s, rt);
+        }
+    }
+};
+
+// fp32 x fp32: operand tiles as they are, for v_mfma_f32_32x32x2_f32.  Six bf16 products would take less matrix
+// time, but not less time in all (the kernel is then bound by LDS and the split: 48 us against 55 us at
+// 16 x (256 x 64 x 4096)), and the bf16 instruction truncates where this one rounds: the projections of a long
+// sequence come out 1e-6 too small instead of 2e-7 off either way.
+// [row][slot] tile: 36 floats per row (16 consecutive rows start in 16 different groups of 4 banks), a
+// fragment is 4 slots.  [slot][row] tile: TR + 8 floats (the two halves' slots, 4 rows apart, use different
+// halves of the 64 banks), a fragment is one dword.  Lane half h takes slots 8q + 4h + e (q, e = 0..3).
+template <bool KF, int TR>
+struct GemmTileF32 {
+    static constexpr int pitch = KF ? F_GK + 4 : TR + 8;
+    static constexpr int bytes = (KF ? TR : F_GK) * pitch * 4;
+    static constexpr int groups = TR * F_GK / 4 / 256;
+    static __device__ __forceinline__ void place(int tid, int i, int& r, int& kk) { GemmTile<KF, TR, 3>::place(tid, i, r, kk); }
+    static __device__ __forceinline__ void store(unsigned char* t, int r, int kk, const Raw4<3>& x) {
+        *(uint4*)((float*)t + (KF ? r * pitch + kk : kk * pitch + r)) = x.v;
+    }
+    // slots 8q + 4 half .. + 3 of row 32 rt + l32
+    static __device__ __forceinline__ void frag(const unsigned char* t, int lane, int rt, int q, float (&f)[4]) {
+        const int r = 32 * rt + (lane & 31), k = 8 * q + 4 * (lane >> 5);
+        if (KF) *(float4*)f = *(const float4*)((const float*)t + r * pitch + k);
+        else
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f[e] = ((const float*)t)[(k + e) * pitch + r];
+    }
 };
 
 // v_mfma_f32_32x32x2_f32, one wavefront: D(32x32) += A(32x2) B(2x32), all fp32.
@@ -35,65 +203,23 @@ __device__ __forceinline__ floatx16 mfma_f32(float a, float b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-constexpr int F_GK = 32;                  // reduction step
-
-// 4 consecutive elements starting at element i, as 16 bytes (fp32) or 8 bytes (bf16) that need no more
-// than the element's own alignment
-__device__ __forceinline__ uint4 ld4_raw(const void* p, long i, int bf16) {
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (bf16) __builtin_memcpy(&v, (const uint16_t*)p + i, 8);
-    else      __builtin_memcpy(&v, (const float*)p + i, 16);
-    return v;
-}
-__device__ __forceinline__ float4 raw_to_f32(const uint4& v, int bf16) {
-    if (bf16) return make_float4(pair_lo(v.x), pair_hi(v.x), pair_lo(v.y), pair_hi(v.y));
-    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-}
-// element e of a group, one at a time (edges of the operand)
-__device__ __forceinline__ void raw_set(uint4& v, int e, uint32_t bits, int bf16) {
-    uint32_t* w = &v.x;
-    if (bf16) w[e >> 1] |= bits << (16 * (e & 1));
-    else      w[e] = bits;
-}
-__device__ __forceinline__ uint32_t elem_bits(const void* p, long i, int bf16) {
-    return bf16 ? (uint32_t)((const uint16_t*)p)[i] : ((const uint32_t*)p)[i];
-}
-
-// One operand tile of TR rows x 32 reduction slots.  KF: the reduction index is the contiguous one in
-// memory; the tile is kept [row][slot] and fragments are read 16 bytes (4 slots) at a time.  Otherwise the
-// rows are contiguous; the tile is kept [slot][row] and a fragment read is one dword per lane.  Either
-// way a thread moves groups of 4 consecutive elements, and lane half h of the wavefront takes
-// slots 8q + 4h + e (q, e = 0..3): the order of the slots is free as long as both operands agree.
-// Pitches: 36 floats put 16 consecutive rows into 16 different groups of 4 banks; TR + 8 floats put the
-// two halves' slots (4 rows of the tile apart) into different halves of the 64 banks.
-template <bool KF, int TR>
-struct F32Tile {
-    static constexpr int pitch = KF ? F_GK + 4 : TR + 8;
-    static constexpr int floats = KF ? TR * pitch : F_GK * pitch;
-    static constexpr int groups = TR * F_GK / 4 / 256;       // per thread
-    static __device__ __forceinline__ void place(int tid, int i, int& r, int& kk) {
-        const int idx = tid + 256 * i;
-        if (KF) { r = idx >> 3; kk = 4 * (idx & 7); }
-        else    { kk = idx / (TR / 4); r = 4 * (idx % (TR / 4)); }
-    }
-    static __device__ __forceinline__ float* at(float* t, int r, int kk) { return KF ? t + r * pitch + kk : t + kk * pitch + r; }
-};
+template <bool C, class X, class Y> struct PickType { typedef X type; };
+template <class X, class Y> struct PickType<false, X, Y> { typedef Y type; };
 
 // Tile TM x TN of C per workgroup of four wavefronts (2 x 2, each TM/2 x TN/2), 32-deep steps through one
-// LDS buffer; the loads of the next step are in flight during the current one, and two or three
-// workgroups share a compute unit.  A 32x32x2 fp32 MFMA takes 64 cycles and needs two dwords per lane, so
-// LDS and issue slots are far from their limits: the kernel is bound by the fp32 matrix rate (the chip's
-// 152 TFLOP/s measured on a large product) once there are enough tiles, by latency otherwise.  At
-// 16 x (4096 x 256 x 64), fp32: 33 us = 65 TFLOP/s where the vector-unit kernel before it (64 x 64 x 16 tiles,
-// one element per load) took 135 us.
-// Every 16 products form a partial sum of their own that is then added to the running sum: the rounding
-// error of a long reduction grows with K/16, not with K.
-template <bool AKF, bool BKF, int TM, int TN>
+// LDS buffer; the loads of the next step are in flight during the current one, and two or more workgroups
+// share a compute unit.  Bound by LDS traffic and the vector instructions of the split for bf16 operands
+// (one to three products per fragment), by the fp32 matrix rate for fp32 x fp32.
+// Every 16 products (fp32 x fp32; else 32, every step) form a partial sum of their own that is then added to
+// the running sum, so that the rounding error of a long reduction grows with K/16, not with K.
+template <bool AKF, bool BKF, int TA, int TB, int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-    using TA = F32Tile<AKF, TM>;
-    using TB = F32Tile<BKF, TN>;
-    __shared__ __attribute__((aligned(16))) float As[TA::floats];
-    __shared__ __attribute__((aligned(16))) float Bs[TB::floats];
+    constexpr bool NATIVE = TA == 3 && TB == 3;         // fp32 x fp32
+    using LA = typename PickType<NATIVE, GemmTileF32<AKF, TM>, GemmTile<AKF, TM, TA>>::type;
+    using LB = typename PickType<NATIVE, GemmTileF32<BKF, TN>, GemmTile<BKF, TN, TB>>::type;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[LA::bytes + LB::bytes];
+    unsigned char* const As = lds;
+    unsigned char* const Bs = lds + LA::bytes;
     constexpr int MT = TM / 64, NT = TN / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, l32 = lane & 31;
@@ -110,79 +236,76 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     int k_end = k_begin + g.steps_per_split * F_GK;
     if (k_end > g.K) k_end = g.K;
     const bool one_level = g.Kin >= g.K;
-    // groups of 4 slots never straddle two outer indices, and the contiguous index has stride 1
+    const int Nin = g.Nin ? g.Nin : g.N;
+    // groups of 4 never straddle two outer indices, and the contiguous index has stride 1
     const bool a_vec = AKF ? (g.sAki == 1 && (one_level || g.Kin % 4 == 0)) : g.sAm == 1;
-    const bool b_vec = BKF ? (g.sBki == 1 && (one_level || g.Kin % 4 == 0)) : g.sBn == 1;
+    const bool b_vec = BKF ? (g.sBki == 1 && (one_level || g.Kin % 4 == 0)) : (g.sBn == 1 && (!g.Nin || g.Nin % 4 == 0));
 
     auto k_offset = [&](int k, long ski, long sko) -> long {
         if (one_level) return (long)k * ski;
         const int ko = k / g.Kin;
         return (long)ko * sko + (long)(k - ko * g.Kin) * ski;
     };
-    auto load_group = [&](bool kf, const void* p, long off, int r, int k, int rmax, long sr, long ski, long sko, bool vec,
-                          int bf16) -> uint4 {
-        if (vec && (kf ? (r < rmax && k + 3 < k_end) : (r + 3 < rmax && k < k_end)))
-            return ld4_raw(p, off + (long)r * sr + k_offset(k, ski, sko), bf16);
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int re = kf ? r : r + e, ke = kf ? k + e : k;
-            if (re < rmax && ke < k_end) raw_set(v, e, elem_bits(p, off + (long)re * sr + k_offset(ke, ski, sko), bf16), bf16);
-        }
-        return v;
+    auto a_row = [&](int r) -> long { return (long)r * g.sAm; };
+    auto b_row = [&](int r) -> long {
+        if (!g.Nin) return (long)r * g.sBn;
+        const int no = r / Nin;
+        return (long)no * g.sBno + (long)(r - no * Nin) * g.sBn;
     };
-    // Interior steps (every group of the tile exists and the step lies inside one outer index) take the
-    // short way: fixed offsets per thread plus one uniform offset per step, no tests per group.
+    // Steps inside the range and inside one outer index take the short way: fixed offsets per thread, one
+    // uniform offset per step, and clamped row indices (rows past the end only feed results nobody stores).
     const bool whole_steps = one_level || g.Kin % F_GK == 0;
-    const bool a_short = a_vec && whole_steps && m0 + TM <= g.M, b_short = b_vec && whole_steps && n0 + TN <= g.N;
-    long pa[TA::groups], pb[TB::groups];
+    const bool a_short = a_vec && whole_steps && (AKF || g.M % 4 == 0 || m0 + TM <= g.M);
+    const bool b_short = b_vec && whole_steps && (BKF || g.N % 4 == 0 || n0 + TN <= g.N);
+    long pa[LA::groups], pb[LB::groups];
 #pragma unroll
-    for (int i = 0; i < TA::groups; ++i) {
+    for (int i = 0; i < LA::groups; ++i) {
         int r, kk;
-        TA::place(tid, i, r, kk);
-        pa[i] = aoff + (long)(m0 + r) * g.sAm + (long)kk * g.sAki;
+        LA::place(tid, i, r, kk);
+        const int rc = m0 + r < g.M ? m0 + r : (AKF ? g.M - 1 : 0);
+        pa[i] = aoff + a_row(rc) + (long)kk * g.sAki;
     }
 #pragma unroll
-    for (int i = 0; i < TB::groups; ++i) {
+    for (int i = 0; i < LB::groups; ++i) {
         int r, kk;
-        TB::place(tid, i, r, kk);
-        pb[i] = boff + (long)(n0 + r) * g.sBn + (long)kk * g.sBki;
+        LB::place(tid, i, r, kk);
+        const int rc = n0 + r < g.N ? n0 + r : (BKF ? g.N - 1 : 0);
+        pb[i] = boff + b_row(rc) + (long)kk * g.sBki;
     }
-    uint4 ra[TA::groups], rb[TB::groups];
+    Raw4<TA> ra[LA::groups];
+    Raw4<TB> rb[LB::groups];
     auto fetch = [&](int k0) {
         const bool inside = k0 + F_GK <= k_end;
         if (inside && a_short) {
             const long ko = k_offset(k0, g.sAki, g.sAko);
-            if (g.a_bf16) {
 #pragma unroll
-                for (int i = 0; i < TA::groups; ++i) ra[i] = ld4_raw(A, pa[i] + ko, 1);
-            } else {
-#pragma unroll
-                for (int i = 0; i < TA::groups; ++i) ra[i] = ld4_raw(A, pa[i] + ko, 0);
-            }
+            for (int i = 0; i < LA::groups; ++i) ra[i] = ld4_raw<TA>(A, pa[i] + ko);
         } else {
 #pragma unroll
-            for (int i = 0; i < TA::groups; ++i) {
+            for (int i = 0; i < LA::groups; ++i) {
                 int r, kk;
-                TA::place(tid, i, r, kk);
-                ra[i] = load_group(AKF, A, aoff, m0 + r, k0 + kk, g.M, g.sAm, g.sAki, g.sAko, a_vec, g.a_bf16);
+                LA::place(tid, i, r, kk);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int re = m0 + (AKF ? r : r + e), ke = k0 + (AKF ? kk + e : kk);
+                    set_elem<TA>(ra[i], e, A, aoff + a_row(re) + k_offset(ke, g.sAki, g.sAko), re < g.M && ke < k_end);
+                }
             }
         }
         if (inside && b_short) {
             const long ko = k_offset(k0, g.sBki, g.sBko);
-            if (g.b_bf16) {
 #pragma unroll
-                for (int i = 0; i < TB::groups; ++i) rb[i] = ld4_raw(B, pb[i] + ko, 1);
-            } else {
-#pragma unroll
-                for (int i = 0; i < TB::groups; ++i) rb[i] = ld4_raw(B, pb[i] + ko, 0);
-            }
+            for (int i = 0; i < LB::groups; ++i) rb[i] = ld4_raw<TB>(B, pb[i] + ko);
         } else {
 #pragma unroll
-            for (int i = 0; i < TB::groups; ++i) {
+            for (int i = 0; i < LB::groups; ++i) {
                 int r, kk;
-                TB::place(tid, i, r, kk);
-                rb[i] = load_group(BKF, B, boff, n0 + r, k0 + kk, g.N, g.sBn, g.sBki, g.sBko, b_vec, g.b_bf16);
+                LB::place(tid, i, r, kk);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int re = n0 + (BKF ? r : r + e), ke = k0 + (BKF ? kk + e : kk);
+                    set_elem<TB>(rb[i], e, B, boff + b_row(re) + k_offset(ke, g.sBki, g.sBko), re < g.N && ke < k_end);
+                }
             }
         }
     };
@@ -195,87 +318,94 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     if (k_begin < k_end) fetch(k_begin);
     for (int k0 = k_begin; k0 < k_end; k0 += F_GK) {
 #pragma unroll
-        for (int i = 0; i < TA::groups; ++i) {
+        for (int i = 0; i < LA::groups; ++i) {
             int r, kk;
-            TA::place(tid, i, r, kk);
-            *(float4*)TA::at(As, r, kk) = raw_to_f32(ra[i], g.a_bf16);
+            LA::place(tid, i, r, kk);
+            LA::store(As, r, kk, ra[i]);
         }
 #pragma unroll
-        for (int i = 0; i < TB::groups; ++i) {
+        for (int i = 0; i < LB::groups; ++i) {
             int r, kk;
-            TB::place(tid, i, r, kk);
-            *(float4*)TB::at(Bs, r, kk) = raw_to_f32(rb[i], g.b_bf16);
+            LB::place(tid, i, r, kk);
+            LB::store(Bs, r, kk, rb[i]);
         }
         __syncthreads();
         if (k0 + F_GK < k_end) fetch(k0 + F_GK);
-#pragma unroll
-        for (int ph = 0; ph < F_GK / 16; ++ph) {
-            floatx16 part[MT][NT];
+        floatx16 part[MT][NT];
+        auto clear = [&]() {
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
                 for (int j = 0; j < NT; ++j) part[i][j] = zero16();
-#pragma unroll
-            for (int q = 2 * ph; q < 2 * ph + 2; ++q) {
-                float fa[MT][4], fb[NT][4];
-#pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    const int r = wm * (TM / 2) + 32 * i + l32;
-                    if (AKF) *(float4*)fa[i] = *(const float4*)TA::at(As, r, 8 * q + 4 * half);
-                    else
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) fa[i][e] = *TA::at(As, r, 8 * q + 4 * half + e);
-                }
-#pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    const int r = wn * (TN / 2) + 32 * j + l32;
-                    if (BKF) *(float4*)fb[j] = *(const float4*)TB::at(Bs, r, 8 * q + 4 * half);
-                    else
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) fb[j][e] = *TB::at(Bs, r, 8 * q + 4 * half + e);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int i = 0; i < MT; ++i)
-#pragma unroll
-                        for (int j = 0; j < NT; ++j) part[i][j] = mfma_f32(fa[i][e], fb[j][e], part[i][j]);
-            }
+        };
+        auto flush = [&]() {
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
-                for (int j = 0; j < NT; ++j)
+                for (int j = 0; j < NT; ++j) acc[i][j] += part[i][j];
+        };
+        clear();
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] += part[i][j][e];
+        for (int s = 0; s < F_GK / 16; ++s) {
+            if constexpr (NATIVE) {
+#pragma unroll
+                for (int q = 2 * s; q < 2 * s + 2; ++q) {
+                    float fa[MT][4], fb[NT][4];
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) LA::frag(As, lane, wm * MT + i, q, fa[i]);
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) LB::frag(Bs, lane, wn * NT + j, q, fb[j]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int i = 0; i < MT; ++i)
+#pragma unroll
+                            for (int j = 0; j < NT; ++j) part[i][j] = mfma_f32(fa[i][e], fb[j][e], part[i][j]);
+                }
+                flush();
+                if (s + 1 < F_GK / 16) clear();
+            } else {
+                uint4 fa[MT][TA], fb[NT][TB];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) LA::frag(As, lane, wm * MT + i, s, fa[i]);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) LB::frag(Bs, lane, wn * NT + j, s, fb[j]);
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) part[i][j] = mfma_terms<TA, TB>(fa[i], fb[j], part[i][j]);
+            }
         }
+        if constexpr (!NATIVE) flush();
         __syncthreads();
     }
     // this lane holds column 32j + l32 and rows 32i + 8(e/4) + 4 half + e%4 of each MFMA tile
-    float* const part_out = g.part ? g.part + ((long)((int)blockIdx.y * (g.C2 ? 2 : 1) + which) * g.batches + bz) * g.M * g.N : nullptr;
-    void* const C = which ? g.C2 : g.C;
+    float* const part_out = g.part ? g.part + ((long)blockIdx.y * (g.C2 ? 2 : 1) + which) * g.c_count : nullptr;
+    void* const C = part_out ? (void*)part_out : which ? g.C2 : g.C;
+    const bool c_bf16 = !part_out && g.c_bf16, accumulate = !part_out && g.accumulate;
     const long coff = (long)b * g.sCb + (long)h * g.sCh;
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int j = 0; j < NT; ++j) {
+        const int gn = n0 + wn * (TN / 2) + 32 * j + l32;
+        if (gn >= g.N) continue;
+        const int no = g.Nin ? gn / Nin : 0;
+        const long cn = coff + (long)no * g.sCno + (long)(gn - no * Nin) * g.sCn;
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int gm = m0 + wm * (TM / 2) + 32 * i + 8 * (e >> 2) + 4 * half + (e & 3);
-                const int gn = n0 + wn * (TN / 2) + 32 * j + l32;
-                if (gm >= g.M || gn >= g.N) continue;
+                if (gm >= g.M) continue;
+                const long ci = cn + (long)gm * g.sCm;
                 float v = acc[i][j][e];
-                if (part_out) {
-                    part_out[(long)gm * g.N + gn] = v;
-                } else {
-                    const long ci = coff + (long)gm * g.sCm + (long)gn * g.sCn;
-                    if (g.accumulate) v += ((const float*)C)[ci];
-                    store_elem(C, ci, v, g.c_bf16);
-                }
+                if (accumulate) v += ((const float*)C)[ci];
+                store_elem(C, ci, v, c_bf16);
             }
+    }
 }
 
-// `part`, `part_floats`: scratch for a split reduction (only for contiguous fp32 results: C[b,h][m][n] at
-// ((b H + h) M + m) N + n); nullptr if the reduction must not be split.
+// `part`, `part_floats`: scratch for a split reduction (only for contiguous fp32 results of `c_count` elements
+// in all batches together); nullptr if the reduction must not be split.
 flurka_status launch_gemm_f32(GemmArgs g, int batches, float* part, size_t part_floats, hipStream_t s);
 
 }  // namespace flurka

@@ -17,7 +17,7 @@ namespace flurka {
 // ---------------------------------------------------------------------------
 // GEMM launches (flurka_gemm_f32.h)
 // ---------------------------------------------------------------------------
-// C (and C2), contiguous (batch, M, N) fp32, from the split partials
+// C (and C2), contiguous fp32, from the split partials
 __global__ __launch_bounds__(256) void gemm_f32_sum_kernel(float* C, float* C2, const float* part, int splits, long count) {
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= count) return;
@@ -28,51 +28,54 @@ __global__ __launch_bounds__(256) void gemm_f32_sum_kernel(float* C, float* C2, 
     (blockIdx.y ? C2 : C)[i] = s;
 }
 
-template <bool AKF, bool BKF, int TM, int TN>
+template <bool AKF, bool BKF, int TA, int TB, int TM, int TN>
 static flurka_status launch_gemm_tile(const GemmArgs& g, int splits, hipStream_t s) {
     const long tiles = (long)((g.N + TN - 1) / TN) * ((g.M + TM - 1) / TM);
-    hipLaunchKernelGGL((gemm_f32_kernel<AKF, BKF, TM, TN>), dim3((unsigned)tiles, (unsigned)splits, (unsigned)(g.batches * (g.C2 ? 2 : 1))),
+    hipLaunchKernelGGL((gemm_f32_kernel<AKF, BKF, TA, TB, TM, TN>), dim3((unsigned)tiles, (unsigned)splits, (unsigned)(g.batches * (g.C2 ? 2 : 1))),
                        dim3(256), 0, s, g);
     FLURKA_CHECK_LAUNCH();
     return FLURKA_OK;
 }
 
-template <bool AKF, bool BKF>
+template <bool AKF, bool BKF, int TA, int TB>
 static flurka_status launch_gemm_layout(GemmArgs g, float* part, size_t part_floats, hipStream_t s) {
-    // Larger tiles halve the operand traffic per product; smaller ones give more workgroups.  A tile edge
-    // of 128 is taken where the result still has two workgroups per compute unit.
-    const long many = 2L * chip_cus();
+    // Larger tiles halve the operand traffic per product; smaller ones give more workgroups.  A tile edge of
+    // 128 is taken where the result, with its reduction split as far as that goes, still has a workgroup
+    // for every compute unit.
+    const long cus = chip_cus();
     const long batches = (long)g.batches * (g.C2 ? 2 : 1);
-    auto tiles = [&](int tm, int tn) { return (long)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * batches; };
-    const int tm = g.M > 64 && tiles(128, 64) >= many ? 128 : 64;
-    const int tn = tm == 128 && g.N > 64 && tiles(128, 128) >= many ? 128 : 64;
-    // Split the reduction where the tiles alone leave compute units idle, into ranges of at least two steps.
     const int steps = (g.K + F_GK - 1) / F_GK;
-    int splits = 1;
-    if (part && tiles(tm, tn) < many) {
-        const size_t count = (size_t)batches * g.M * g.N;
-        splits = (int)(many / tiles(tm, tn));
-        if (splits > steps / 2) splits = steps / 2;
-        if (splits > 32) splits = 32;
-        if ((size_t)splits > part_floats / count) splits = (int)(part_floats / count);
-        if (splits < 1) splits = 1;
-    }
-    g.steps_per_split = (steps + splits - 1) / splits;
+    auto tiles = [&](int tm, int tn) { return (long)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * batches; };
+    auto max_splits = [&]() -> long {           // ranges of at least two steps, as many as the scratch holds
+        if (!part) return 1;
+        long q = steps / 2 < 32 ? steps / 2 : 32;
+        const long room = (long)(part_floats / ((size_t)g.c_count * (g.C2 ? 2 : 1)));
+        if (q > room) q = room;
+        return q < 1 ? 1 : q;
+    };
+    const long most = max_splits();
+    const int tm = g.M > 64 && tiles(128, 64) * most >= cus ? 128 : 64;
+    const int tn = tm == 128 && g.N > 64 && tiles(128, 128) * most >= cus ? 128 : 64;
+    // two workgroups per compute unit where splitting allows it
+    long splits = (2 * cus + tiles(tm, tn) - 1) / tiles(tm, tn);
+    if (tiles(tm, tn) >= 2 * cus || splits < 1) splits = 1;
+    if (splits > most) splits = most;
+    g.steps_per_split = (int)((steps + splits - 1) / splits);
     splits = (steps + g.steps_per_split - 1) / g.steps_per_split;
     g.part = splits > 1 ? part : nullptr;
-    flurka_status st = tm == 64 ? launch_gemm_tile<AKF, BKF, 64, 64>(g, splits, s)
-                       : tn == 64 ? launch_gemm_tile<AKF, BKF, 128, 64>(g, splits, s)
-                                  : launch_gemm_tile<AKF, BKF, 128, 128>(g, splits, s);
+    flurka_status st = tm == 64 ? launch_gemm_tile<AKF, BKF, TA, TB, 64, 64>(g, (int)splits, s)
+                       : tn == 64 ? launch_gemm_tile<AKF, BKF, TA, TB, 128, 64>(g, (int)splits, s)
+                                  : launch_gemm_tile<AKF, BKF, TA, TB, 128, 128>(g, (int)splits, s);
     if (st != FLURKA_OK || splits == 1) return st;
-    const long count = (long)g.batches * g.M * g.N;
-    hipLaunchKernelGGL(gemm_f32_sum_kernel, dim3((unsigned)((count + 255) / 256), g.C2 ? 2u : 1u), dim3(256), 0, s, (float*)g.C,
-                       (float*)g.C2, (const float*)g.part, splits, count);
+    hipLaunchKernelGGL(gemm_f32_sum_kernel, dim3((unsigned)((g.c_count + 255) / 256), g.C2 ? 2u : 1u), dim3(256), 0, s, (float*)g.C,
+                       (float*)g.C2, (const float*)g.part, (int)splits, g.c_count);
     FLURKA_CHECK_LAUNCH();
     return FLURKA_OK;
 }
 
 flurka_status launch_gemm_f32(GemmArgs g, int batches, float* part, size_t part_floats, hipStream_t s) {
     g.batches = batches;
+    g.c_count = (long)batches * g.M * g.N;
     if (g.C2 && 2L * batches > 65535) {        // more batches than a grid dimension takes: one GEMM at a time
         GemmArgs g2 = g;
         g2.A = g.A2; g2.B = g.B2; g2.C = g.C2;
@@ -81,9 +84,20 @@ flurka_status launch_gemm_f32(GemmArgs g, int batches, float* part, size_t part_
         const flurka_status st = launch_gemm_f32(g, batches, part, part_floats, s);
         return st != FLURKA_OK ? st : launch_gemm_f32(g2, batches, part, part_floats, s);
     }
+    // the layouts and storage types the path has: an fp32 x bf16 product has its bf16 operand on the right
+    // except where E stands on the left (transposed, in dK = E^T dK')
     const bool akf = g.sAki == 1, bkf = g.sBki == 1;
-    if (akf) return bkf ? launch_gemm_layout<true, true>(g, part, part_floats, s) : launch_gemm_layout<true, false>(g, part, part_floats, s);
-    return bkf ? launch_gemm_layout<false, true>(g, part, part_floats, s) : launch_gemm_layout<false, false>(g, part, part_floats, s);
+    if (akf && bkf)
+        return g.a_bf16 ? launch_gemm_layout<true, true, 1, 1>(g, part, part_floats, s)
+               : g.b_bf16 ? launch_gemm_layout<true, true, 3, 1>(g, part, part_floats, s)
+                          : launch_gemm_layout<true, true, 3, 3>(g, part, part_floats, s);
+    if (akf)
+        return g.a_bf16 ? launch_gemm_layout<true, false, 1, 1>(g, part, part_floats, s)
+               : g.b_bf16 ? launch_gemm_layout<true, false, 3, 1>(g, part, part_floats, s)
+                          : launch_gemm_layout<true, false, 3, 3>(g, part, part_floats, s);
+    return g.a_bf16 ? launch_gemm_layout<false, false, 1, 3>(g, part, part_floats, s)
+           : g.b_bf16 ? launch_gemm_layout<false, false, 3, 1>(g, part, part_floats, s)
+                      : launch_gemm_layout<false, false, 3, 3>(g, part, part_floats, s);
 }
 
 static flurka_status launch_gemm(const GemmArgs& g, int batches, hipStream_t s) { return launch_gemm_f32(g, batches, nullptr, 0, s); }
@@ -335,7 +349,10 @@ static flurka_status project(const Problem& p, const FwdArgs& a, float* Kp, floa
     g.sBn = 1; g.sBki = p.d; g.sBb = (long)p.H * p.n * p.d; g.sBh = (long)p.n * p.d;
     g.sCm = p.d; g.sCn = 1; g.sCb = (long)p.H * p.k * p.d; g.sCh = (long)p.k * p.d;
     g.H = p.H; g.a_bf16 = p.bf16; g.b_bf16 = p.bf16;
-    return launch_gemm_f32(g, p.BH, part, part_floats, s);
+    if (p.ef_per_head) return launch_gemm_f32(g, p.BH, part, part_floats, s);
+    // E, F shared: all heads side by side as one row of columns (head, t)
+    g.N = p.BH * p.d; g.Nin = p.d; g.sBno = (long)p.n * p.d; g.sCno = (long)p.k * p.d;
+    return launch_gemm_f32(g, 1, part, part_floats, s);
 }
 
 // PhiK (k x mf, shifted) from K' in ctx.  With `new_shift` the per-feature shifts c are computed
@@ -652,7 +669,12 @@ static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const fl
         g.sBn = 1; g.sBki = p.d; g.sBb = (long)p.H * p.k * p.d; g.sBh = (long)p.k * p.d;
         g.sCm = p.d; g.sCn = 1; g.sCb = (long)p.H * p.n * p.d; g.sCh = (long)p.n * p.d;
         g.H = p.H; g.a_bf16 = p.bf16; g.c_bf16 = p.bf16;
-        if ((st = launch_gemm(g, p.BH, s)) != FLURKA_OK) return st;
+        int batches = p.BH;
+        if (!p.ef_per_head) {    // E, F shared: all heads side by side as one row of columns (head, t)
+            g.N = p.BH * p.d; g.Nin = p.d; g.sBno = (long)p.k * p.d; g.sCno = (long)p.n * p.d;
+            batches = 1;
+        }
+        if ((st = launch_gemm(g, batches, s)) != FLURKA_OK) return st;
     }
     stage_end(s, STAGE_BWD_DKDV);
     // dE = sum_bh dK' K^T, dF = sum_bh dV' V^T   (k x n); reduction index = (bh, t)
