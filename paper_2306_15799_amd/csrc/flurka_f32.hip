@@ -1184,6 +1184,11 @@ F32BwdWs f32_bwd_ws_layout(const Problem& p) {
     W.dzpart = take(BH * y.R * p.mfp);
     W.dS = take(BH * p.mf * p.d);
     W.dz = take(BH * p.mf);
+    // dE, dF from bf16 operands: what lies in front of dK' takes split partials once the key side is done, four
+    // ranges where the results alone are fewer than two 128 x 128 tiles per compute unit (at most 32 MiB)
+    const long tiles = 2L * ((p.k + 127) / 128) * ((p.n + 127) / 128);
+    const size_t parts = (size_t)8 * p.k * p.n;
+    if (p.bf16 && !p.ef_per_head && tiles < 2L * chip_cus() && o < parts) o = round_up(parts, 64);
     W.dKp = take(BH * p.k * p.d);
     W.dVp = take(BH * p.k * p.d);
     W.plain = o;

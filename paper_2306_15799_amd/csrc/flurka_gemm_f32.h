@@ -106,17 +106,26 @@ __device__ __forceinline__ Raw4<T> ld4_raw(const void* p, long i) {
     else                  __builtin_memcpy(&r.v, (const float*)p + i, 16);
     return r;
 }
-// one element of a group at a time (edges of the operand); `keep` false: zero
+// Element e of a group (edges of the operand): element i, or zero if !keep.  i is a valid index either way, so
+// that the loads of a step go out together instead of one behind a branch each (a reduction of 187 had
+// spent most of its six steps in the last one).
 template <int T>
 __device__ __forceinline__ void set_elem(Raw4<T>& r, int e, const void* p, long i, bool keep) {
     uint32_t* w = (uint32_t*)&r.v;
     if constexpr (T == 1) {
-        uint32_t x = 0u;
-        if (keep) x = ((const uint16_t*)p)[i];
+        uint32_t x = ((const uint16_t*)p)[i];
+        x = keep ? x : 0u;
         w[e >> 1] = (e & 1) ? (w[e >> 1] | (x << 16)) : x;
     } else {
-        w[e] = keep ? ((const uint32_t*)p)[i] : 0u;
+        const uint32_t x = ((const uint32_t*)p)[i];
+        w[e] = keep ? x : 0u;
     }
+}
+template <int T>
+__device__ __forceinline__ void keep_group(Raw4<T>& r, bool keep) {
+    uint32_t* w = (uint32_t*)&r.v;
+#pragma unroll
+    for (int e = 0; e < (T == 1 ? 2 : 4); ++e) w[e] = keep ? w[e] : 0u;
 }
 template <int T>
 __device__ __forceinline__ void split4(const Raw4<T>& r, uint2 (&t)[T]) {
@@ -206,20 +215,32 @@ __device__ __forceinline__ floatx16 mfma_f32(float a, float b, floatx16 c) {
 template <bool C, class X, class Y> struct PickType { typedef X type; };
 template <class X, class Y> struct PickType<false, X, Y> { typedef Y type; };
 
-// Tile TM x TN of C per workgroup of four wavefronts (2 x 2, each TM/2 x TN/2), 32-deep steps through one
-// LDS buffer; the loads of the next step are in flight during the current one, and two or more workgroups
-// share a compute unit.  Bound by LDS traffic and the vector instructions of the split for bf16 operands
-// (one to three products per fragment), by the fp32 matrix rate for fp32 x fp32.
+// LDS of a workgroup: two buffers of both operand tiles
+template <bool AKF, bool BKF, int TA, int TB, int TM, int TN>
+struct GemmF32Lds {
+    static constexpr bool native = TA == 3 && TB == 3;         // fp32 x fp32
+    using LA = typename PickType<native, GemmTileF32<AKF, TM>, GemmTile<AKF, TM, TA>>::type;
+    using LB = typename PickType<native, GemmTileF32<BKF, TN>, GemmTile<BKF, TN, TB>>::type;
+    static constexpr int stage = LA::bytes + LB::bytes, bytes = 2 * stage;
+    // steps between the request of an operand and its use: two where the registers for a second staging set
+    // are there (128 x 128 tiles with an fp32 operand spill up to 56 registers with it and lose 3 to 7 us of 60)
+    static constexpr int ahead = TM == 128 && TN == 128 && (TA == 3 || TB == 3) ? 1 : 2;
+};
+
+// Tile TM x TN of C per workgroup of four wavefronts (2 x 2, each TM/2 x TN/2), 32-deep steps through two
+// LDS buffers, one barrier per step.  A step's operands are requested up to two steps before they are needed:
+// it has only 6 to 32 matrix instructions per wavefront (200 to 2000 cycles) to cover a load with.  Bound by
+// vector issue (splits, partial sums, the stores of short reductions) for bf16 operands, by the fp32 matrix
+// rate for fp32 x fp32.
 // Every 16 products (fp32 x fp32; else 32, every step) form a partial sum of their own that is then added to
 // the running sum, so that the rounding error of a long reduction grows with K/16, not with K.
 template <bool AKF, bool BKF, int TA, int TB, int TM, int TN>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-    constexpr bool NATIVE = TA == 3 && TB == 3;         // fp32 x fp32
-    using LA = typename PickType<NATIVE, GemmTileF32<AKF, TM>, GemmTile<AKF, TM, TA>>::type;
-    using LB = typename PickType<NATIVE, GemmTileF32<BKF, TN>, GemmTile<BKF, TN, TB>>::type;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[LA::bytes + LB::bytes];
-    unsigned char* const As = lds;
-    unsigned char* const Bs = lds + LA::bytes;
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmArgs g) {
+    using L = GemmF32Lds<AKF, BKF, TA, TB, TM, TN>;
+    using LA = typename L::LA;
+    using LB = typename L::LB;
+    constexpr bool NATIVE = L::native;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int MT = TM / 64, NT = TN / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, l32 = lane & 31;
@@ -252,34 +273,52 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
         const int no = r / Nin;
         return (long)no * g.sBno + (long)(r - no * Nin) * g.sBn;
     };
-    // Steps inside the range and inside one outer index take the short way: fixed offsets per thread, one
-    // uniform offset per step, and clamped row indices (rows past the end only feed results nobody stores).
+    // Three ways to load a step, the same for all threads of a workgroup:
+    //   short     whole steps inside one outer index: fixed offsets per thread, one uniform offset per step
+    //   groups    every group of 4 lies inside or outside of the operand as a whole: one load per group
+    //   elements  anything else
+    // Row indices are clamped (rows past the end only feed results nobody stores), reduction indices past the
+    // end read a valid element and become zero.
     const bool whole_steps = one_level || g.Kin % F_GK == 0;
+    const bool a_group = a_vec && (AKF ? g.K % 4 == 0 : (g.M % 4 == 0 || m0 + TM <= g.M));
+    const bool b_group = b_vec && (BKF ? g.K % 4 == 0 : (g.N % 4 == 0 || n0 + TN <= g.N));
     const bool a_short = a_vec && whole_steps && (AKF || g.M % 4 == 0 || m0 + TM <= g.M);
     const bool b_short = b_vec && whole_steps && (BKF || g.N % 4 == 0 || n0 + TN <= g.N);
-    long pa[LA::groups], pb[LB::groups];
+    long pa[LA::groups], pb[LB::groups];      // offsets of this thread's groups at reduction index 0
 #pragma unroll
     for (int i = 0; i < LA::groups; ++i) {
         int r, kk;
         LA::place(tid, i, r, kk);
         const int rc = m0 + r < g.M ? m0 + r : (AKF ? g.M - 1 : 0);
-        pa[i] = aoff + a_row(rc) + (long)kk * g.sAki;
+        pa[i] = aoff + a_row(rc);
     }
 #pragma unroll
     for (int i = 0; i < LB::groups; ++i) {
         int r, kk;
         LB::place(tid, i, r, kk);
         const int rc = n0 + r < g.N ? n0 + r : (BKF ? g.N - 1 : 0);
-        pb[i] = boff + b_row(rc) + (long)kk * g.sBki;
+        pb[i] = boff + b_row(rc);
     }
-    Raw4<TA> ra[LA::groups];
-    Raw4<TB> rb[LB::groups];
-    auto fetch = [&](int k0) {
+    struct Stage { Raw4<TA> a[LA::groups]; Raw4<TB> b[LB::groups]; };
+    auto fetch = [&](int k0, Stage& st) {
         const bool inside = k0 + F_GK <= k_end;
         if (inside && a_short) {
             const long ko = k_offset(k0, g.sAki, g.sAko);
 #pragma unroll
-            for (int i = 0; i < LA::groups; ++i) ra[i] = ld4_raw<TA>(A, pa[i] + ko);
+            for (int i = 0; i < LA::groups; ++i) {
+                int r, kk;
+                LA::place(tid, i, r, kk);
+                st.a[i] = ld4_raw<TA>(A, pa[i] + (long)kk * g.sAki + ko);
+            }
+        } else if (a_group) {
+#pragma unroll
+            for (int i = 0; i < LA::groups; ++i) {
+                int r, kk;
+                LA::place(tid, i, r, kk);
+                const bool ok = k0 + kk < k_end;
+                st.a[i] = ld4_raw<TA>(A, pa[i] + k_offset(ok ? k0 + kk : k0, g.sAki, g.sAko));
+                keep_group<TA>(st.a[i], ok);
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < LA::groups; ++i) {
@@ -288,14 +327,28 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int re = m0 + (AKF ? r : r + e), ke = k0 + (AKF ? kk + e : kk);
-                    set_elem<TA>(ra[i], e, A, aoff + a_row(re) + k_offset(ke, g.sAki, g.sAko), re < g.M && ke < k_end);
+                    set_elem<TA>(st.a[i], e, A, aoff + a_row(re < g.M ? re : g.M - 1) + k_offset(ke < k_end ? ke : k0, g.sAki, g.sAko),
+                                 re < g.M && ke < k_end);
                 }
             }
         }
         if (inside && b_short) {
             const long ko = k_offset(k0, g.sBki, g.sBko);
 #pragma unroll
-            for (int i = 0; i < LB::groups; ++i) rb[i] = ld4_raw<TB>(B, pb[i] + ko);
+            for (int i = 0; i < LB::groups; ++i) {
+                int r, kk;
+                LB::place(tid, i, r, kk);
+                st.b[i] = ld4_raw<TB>(B, pb[i] + (long)kk * g.sBki + ko);
+            }
+        } else if (b_group) {
+#pragma unroll
+            for (int i = 0; i < LB::groups; ++i) {
+                int r, kk;
+                LB::place(tid, i, r, kk);
+                const bool ok = k0 + kk < k_end;
+                st.b[i] = ld4_raw<TB>(B, pb[i] + k_offset(ok ? k0 + kk : k0, g.sBki, g.sBko));
+                keep_group<TB>(st.b[i], ok);
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < LB::groups; ++i) {
@@ -304,9 +357,24 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int re = n0 + (BKF ? r : r + e), ke = k0 + (BKF ? kk + e : kk);
-                    set_elem<TB>(rb[i], e, B, boff + b_row(re) + k_offset(ke, g.sBki, g.sBko), re < g.N && ke < k_end);
+                    set_elem<TB>(st.b[i], e, B, boff + b_row(re < g.N ? re : g.N - 1) + k_offset(ke < k_end ? ke : k0, g.sBki, g.sBko),
+                                 re < g.N && ke < k_end);
                 }
             }
+        }
+    };
+    auto put = [&](const Stage& st, unsigned char* buf) {
+#pragma unroll
+        for (int i = 0; i < LA::groups; ++i) {
+            int r, kk;
+            LA::place(tid, i, r, kk);
+            LA::store(buf, r, kk, st.a[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < LB::groups; ++i) {
+            int r, kk;
+            LB::place(tid, i, r, kk);
+            LB::store(buf + LA::bytes, r, kk, st.b[i]);
         }
     };
     floatx16 acc[MT][NT];
@@ -315,22 +383,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = zero16();
 
-    if (k_begin < k_end) fetch(k_begin);
-    for (int k0 = k_begin; k0 < k_end; k0 += F_GK) {
-#pragma unroll
-        for (int i = 0; i < LA::groups; ++i) {
-            int r, kk;
-            LA::place(tid, i, r, kk);
-            LA::store(As, r, kk, ra[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < LB::groups; ++i) {
-            int r, kk;
-            LB::place(tid, i, r, kk);
-            LB::store(Bs, r, kk, rb[i]);
-        }
-        __syncthreads();
-        if (k0 + F_GK < k_end) fetch(k0 + F_GK);
+    // step k0 out of `buf`; `mine` is free and takes the step `ahead` steps on, `next` holds the next step's
+    // operands (ahead = 1: it is the same set), which go to `other` for it
+    auto step = [&](int k0, unsigned char* buf, unsigned char* other, Stage& mine, const Stage& next) {
+        const unsigned char* const As = buf;
+        const unsigned char* const Bs = buf + LA::bytes;
+        if (k0 + L::ahead * F_GK < k_end) fetch(k0 + L::ahead * F_GK, mine);
         floatx16 part[MT][NT];
         auto clear = [&]() {
 #pragma unroll
@@ -377,30 +435,86 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
             }
         }
         if constexpr (!NATIVE) flush();
-        __syncthreads();
+        if (k0 + F_GK < k_end) {
+            put(next, other);
+            __syncthreads();     // `other` complete; everybody is done with `buf`, which the next step fills
+        }
+    };
+    if (k_begin < k_end) {
+        unsigned char* const b0 = lds;
+        unsigned char* const b1 = lds + L::stage;
+        if constexpr (L::ahead == 2) {
+            Stage s0, s1;
+            fetch(k_begin, s0);
+            if (k_begin + F_GK < k_end) fetch(k_begin + F_GK, s1);
+            put(s0, b0);
+            __syncthreads();
+            for (int k0 = k_begin; k0 < k_end; k0 += 2 * F_GK) {
+                step(k0, b0, b1, s0, s1);
+                if (k0 + F_GK < k_end) step(k0 + F_GK, b1, b0, s1, s0);
+            }
+        } else {
+            Stage st;
+            fetch(k_begin, st);
+            put(st, b0);
+            __syncthreads();
+            int buf = 0;
+            for (int k0 = k_begin; k0 < k_end; k0 += F_GK, buf ^= 1)
+                step(k0, lds + buf * L::stage, lds + (buf ^ 1) * L::stage, st, st);
+        }
     }
-    // this lane holds column 32j + l32 and rows 32i + 8(e/4) + 4 half + e%4 of each MFMA tile
+    // this lane holds column 32j + l32 and rows 32i + 8(e/4) + 4 half + e%4 of each MFMA tile.  Rows advance by
+    // uniform distances; tiles inside the result store without a check per element (a short reduction spends as
+    // long here as in its steps).
     float* const part_out = g.part ? g.part + ((long)blockIdx.y * (g.C2 ? 2 : 1) + which) * g.c_count : nullptr;
     void* const C = part_out ? (void*)part_out : which ? g.C2 : g.C;
     const bool c_bf16 = !part_out && g.c_bf16, accumulate = !part_out && g.accumulate;
     const long coff = (long)b * g.sCb + (long)h * g.sCh;
+    const int row0 = m0 + wm * (TM / 2) + 4 * half;
+    const bool whole = m0 + TM <= g.M;
+    auto store_column = [&](auto* c, const floatx16 (&t)[MT][NT], int j, auto&& keep, auto&& put1) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                auto* cq = c + (long)(32 * i + 8 * q) * g.sCm;
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    const int r = 32 * i + 8 * q + e;
+                    put1(cq + (long)e * g.sCm, cq + (long)(e + 1) * g.sCm, t[i][j][4 * q + e], t[i][j][4 * q + e + 1], keep(r), keep(r + 1));
+                }
+            }
+    };
+    auto all = [](int) { return true; };
+    auto some = [&](int r) { return row0 + r < g.M; };
+    auto two_bf16 = [](uint16_t* p0, uint16_t* p1, float x, float y, bool k0, bool k1) {
+        const uint32_t v = pack_bf16(x, y);
+        if (k0) *p0 = (uint16_t)v;
+        if (k1) *p1 = (uint16_t)(v >> 16);
+    };
+    auto two_f32 = [](float* p0, float* p1, float x, float y, bool k0, bool k1) {
+        if (k0) *p0 = x;
+        if (k1) *p1 = y;
+    };
+    auto two_add = [](float* p0, float* p1, float x, float y, bool k0, bool k1) {
+        if (k0) *p0 += x;
+        if (k1) *p1 += y;
+    };
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int gn = n0 + wn * (TN / 2) + 32 * j + l32;
         if (gn >= g.N) continue;
         const int no = g.Nin ? gn / Nin : 0;
-        const long cn = coff + (long)no * g.sCno + (long)(gn - no * Nin) * g.sCn;
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int gm = m0 + wm * (TM / 2) + 32 * i + 8 * (e >> 2) + 4 * half + (e & 3);
-                if (gm >= g.M) continue;
-                const long ci = cn + (long)gm * g.sCm;
-                float v = acc[i][j][e];
-                if (accumulate) v += ((const float*)C)[ci];
-                store_elem(C, ci, v, c_bf16);
-            }
+        const long ci = coff + (long)no * g.sCno + (long)(gn - no * Nin) * g.sCn + (long)row0 * g.sCm;
+        if (c_bf16) {
+            if (whole) store_column((uint16_t*)C + ci, acc, j, all, two_bf16);
+            else       store_column((uint16_t*)C + ci, acc, j, some, two_bf16);
+        } else if (!accumulate) {
+            if (whole) store_column((float*)C + ci, acc, j, all, two_f32);
+            else       store_column((float*)C + ci, acc, j, some, two_f32);
+        } else {
+            store_column((float*)C + ci, acc, j, some, two_add);
+        }
     }
 }
 

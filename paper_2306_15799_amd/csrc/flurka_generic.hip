@@ -17,22 +17,44 @@ namespace flurka {
 // ---------------------------------------------------------------------------
 // GEMM launches (flurka_gemm_f32.h)
 // ---------------------------------------------------------------------------
-// C (and C2), contiguous fp32, from the split partials
-__global__ __launch_bounds__(256) void gemm_f32_sum_kernel(float* C, float* C2, const float* part, int splits, long count) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+// C (and C2), contiguous, from the split partials; 4 consecutive elements per thread
+__global__ __launch_bounds__(256) void gemm_f32_sum_kernel(void* C, void* C2, const float* part, int splits, long count, int c_bf16) {
+    const long i = 4 * ((long)blockIdx.x * 256 + threadIdx.x);
     if (i >= count) return;
     const long plane = count * (C2 ? 2 : 1);
     const float* p = part + (blockIdx.y ? count : 0) + i;
-    float s = 0.f;
-    for (int u = 0; u < splits; ++u) s += p[u * plane];
-    (blockIdx.y ? C2 : C)[i] = s;
+    void* const c = blockIdx.y ? C2 : C;
+    if (i + 4 <= count) {
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < splits; ++u) {
+            float x[4];
+            __builtin_memcpy(x, p + u * plane, 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += x[e];
+        }
+        if (c_bf16) {
+            const uint2 v = {pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
+            __builtin_memcpy((uint16_t*)c + i, &v, 8);
+        } else {
+            __builtin_memcpy((float*)c + i, s, 16);
+        }
+        return;
+    }
+    for (int e = 0; i + e < count; ++e) {
+        float s = 0.f;
+        for (int u = 0; u < splits; ++u) s += p[u * plane + e];
+        store_elem(c, i + e, s, c_bf16);
+    }
 }
 
 template <bool AKF, bool BKF, int TA, int TB, int TM, int TN>
 static flurka_status launch_gemm_tile(const GemmArgs& g, int splits, hipStream_t s) {
     const long tiles = (long)((g.N + TN - 1) / TN) * ((g.M + TM - 1) / TM);
-    hipLaunchKernelGGL((gemm_f32_kernel<AKF, BKF, TA, TB, TM, TN>), dim3((unsigned)tiles, (unsigned)splits, (unsigned)(g.batches * (g.C2 ? 2 : 1))),
-                       dim3(256), 0, s, g);
+    const auto kern = gemm_f32_kernel<AKF, BKF, TA, TB, TM, TN>;
+    constexpr int ldsb = GemmF32Lds<AKF, BKF, TA, TB, TM, TN>::bytes;
+    KernelFacts facts;
+    if (!kernel_facts((const void*)kern, 256, ldsb, &facts)) return FLURKA_ERR_LAUNCH;      // raises the LDS limit
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)splits, (unsigned)(g.batches * (g.C2 ? 2 : 1))), dim3(256), ldsb, s, g);
     FLURKA_CHECK_LAUNCH();
     return FLURKA_OK;
 }
@@ -67,8 +89,8 @@ static flurka_status launch_gemm_layout(GemmArgs g, float* part, size_t part_flo
                        : tn == 64 ? launch_gemm_tile<AKF, BKF, TA, TB, 128, 64>(g, (int)splits, s)
                                   : launch_gemm_tile<AKF, BKF, TA, TB, 128, 128>(g, (int)splits, s);
     if (st != FLURKA_OK || splits == 1) return st;
-    hipLaunchKernelGGL(gemm_f32_sum_kernel, dim3((unsigned)((g.c_count + 255) / 256), g.C2 ? 2u : 1u), dim3(256), 0, s, (float*)g.C,
-                       (float*)g.C2, (const float*)g.part, (int)splits, g.c_count);
+    hipLaunchKernelGGL(gemm_f32_sum_kernel, dim3((unsigned)((g.c_count + 1023) / 1024), g.C2 ? 2u : 1u), dim3(256), 0, s, g.C,
+                       g.C2, (const float*)g.part, (int)splits, g.c_count, g.c_bf16);
     FLURKA_CHECK_LAUNCH();
     return FLURKA_OK;
 }
@@ -467,7 +489,9 @@ flurka_status generic_forward(const Problem& p, const FwdArgs& a, hipStream_t s)
 //   dK = E^T dK', dV = F^T dV', dE = sum_bh dK' K^T, dF = sum_bh dV' V^T
 // ---------------------------------------------------------------------------
 // The four sequence-length GEMMs from dK', dV' (fp32)
-static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const float* dKp, const float* dVp, hipStream_t s);
+// `part`: scratch for split partials of dE, dF
+static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const float* dKp, const float* dVp, float* part,
+                                    size_t part_floats, hipStream_t s);
 
 // head sizes up to 128: the query and key side on the fused kernels (flurka_f32.hip)
 static flurka_status fused_backward(const Problem& p, const BwdArgs& a, hipStream_t s) {
@@ -481,7 +505,9 @@ static flurka_status fused_backward(const Problem& p, const BwdArgs& a, hipStrea
         StageScope sc(s, STAGE_BWD_KEY);
         if ((st = f32_key_backward(p, a, s)) != FLURKA_OK) return st;
     }
-    return grad_gemms_f32(p, a, a.ws + W.dKp, a.ws + W.dVp, s);
+    // what lies in front of dK', dV' is done with
+    // (two fp32 operands: the fp32 matrix rate bounds the GEMM, splitting it only adds the sum: 67 us against 63)
+    return grad_gemms_f32(p, a, a.ws + W.dKp, a.ws + W.dVp, a.ws, p.bf16 ? W.dKp : 0, s);
 }
 
 size_t generic_ws_floats(const Problem& p, int bwd) {
@@ -653,10 +679,11 @@ flurka_status generic_backward(const Problem& p, const BwdArgs& a, hipStream_t s
     }
 
     stage_end(s, STAGE_BWD_KEY);
-    return grad_gemms_f32(p, a, dKp, dVp, s);
+    return grad_gemms_f32(p, a, dKp, dVp, a.ws, p.bf16 ? W.dKp : 0, s);
 }
 
-static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const float* dKp, const float* dVp, hipStream_t s) {
+static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const float* dKp, const float* dVp, float* part,
+                                    size_t part_floats, hipStream_t s) {
     flurka_status st;
     // dK = E^T dK', dV = F^T dV'   (n x d per head)
     stage_begin(s);
@@ -689,10 +716,10 @@ static flurka_status grad_gemms_f32(const Problem& p, const BwdArgs& a, const fl
         if (p.ef_per_head) {     // one (k x n) gradient per head, reduction index = (batch, t)
             g.K = p.B * p.d; g.sAko = (long)p.H * p.k * p.d; g.sAh = (long)p.k * p.d;
             g.sBko = (long)p.H * p.n * p.d; g.sBh = (long)p.n * p.d; g.sCh = (long)p.k * p.n; g.H = p.H;
-            if ((st = launch_gemm(g, p.H, s)) != FLURKA_OK) return st;
+            if ((st = launch_gemm_f32(g, p.H, part, part_floats, s)) != FLURKA_OK) return st;
         } else {                  // E, F shared: reduction index = (batch, head, t)
             g.K = p.BH * p.d; g.sAko = (long)p.k * p.d; g.sBko = (long)p.n * p.d; g.H = 1;
-            if ((st = launch_gemm(g, 1, s)) != FLURKA_OK) return st;
+            if ((st = launch_gemm_f32(g, 1, part, part_floats, s)) != FLURKA_OK) return st;
         }
     }
     stage_end(s, STAGE_BWD_DEDF);

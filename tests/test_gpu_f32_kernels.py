@@ -30,3 +30,16 @@ def test_tile_edges(shape, phi, dtype):
     w = Workload("f32_edges", B, H, n, d, k, d if phi == PHI_ELU1 else m, dtype, phi, True)
     errs = gu.check_forward_backward(w, seed=n + d, algo="generic")
     print(shape, phi, dtype, {x: f"{v:.2e}" for x, v in errs.items() if ":" not in x})
+
+
+# (B, H, n, d, k, m): reductions of dE, dF over many heads split over workgroups (bf16 storage) and summed 4
+# results at a time with 0 to 3 left over; reductions one group short of, at and past a 32-deep step; head
+# sizes whose heads do not end on a step
+@pytest.mark.parametrize("shape", [(4, 8, 301, 64, 70, 40), (4, 8, 303, 64, 71, 40), (2, 8, 129, 80, 33, 24),
+                                   (1, 6, 257, 128, 28, 33), (1, 3, 200, 12, 36, 16)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_split_gradients_and_short_reductions(shape, dtype):
+    B, H, n, d, k, m = shape
+    errs = gu.check_forward_backward(Workload("f32_split", B, H, n, d, k, m, dtype, PHI_PERFORMER, True), seed=n + k,
+                                     algo="generic")
+    print(shape, dtype, {x: f"{v:.2e}" for x, v in errs.items() if ":" not in x})
