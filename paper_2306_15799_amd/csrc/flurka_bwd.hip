@@ -808,11 +808,10 @@ __global__ void bwd_merge_kernel(uint16_t* dSimg, float* dS32, float* dz, const 
     const int pr = (int)(rest % (mf / 2));
     const long bh = rest / (mf / 2);
     float s0 = 0.f, s1 = 0.f;
-    for (int r = 0; r < R; ++r) {
-        const float* p = dSpart + ((bh * R + r) * mf + 2 * pr) * d + t;
-        s0 += p[0];
-        s1 += p[d];
-    }
+    const float* const ps = dSpart + (bh * R * mf + 2 * pr) * d + t;
+    for_parts<8, float2>(
+        R, [&](int r) { const float* p = ps + (long)r * mf * d; return make_float2(p[0], p[d]); },
+        [&](const float2& x) { s0 += x.x; s1 += x.y; });
     const long i0 = (bh * mf + 2 * pr) * d + t;
     if (dS32) {
         dS32[i0] = s0; dS32[i0 + d] = s1;
@@ -826,10 +825,10 @@ __global__ void bwd_merge_kernel(uint16_t* dSimg, float* dS32, float* dz, const 
     }
     if (t == 0) {
         float z0 = 0.f, z1 = 0.f;
-        for (int r = 0; r < R; ++r) {
-            z0 += dzpart[(bh * R + r) * mf + 2 * pr];
-            z1 += dzpart[(bh * R + r) * mf + 2 * pr + 1];
-        }
+        const float* const pz = dzpart + bh * R * mf + 2 * pr;
+        for_parts<8, float2>(
+            R, [&](int r) { const float* p = pz + (long)r * mf; return make_float2(p[0], p[1]); },
+            [&](const float2& x) { z0 += x.x; z1 += x.y; });
         dz[bh * mf + 2 * pr] = z0;
         dz[bh * mf + 2 * pr + 1] = z1;
     }

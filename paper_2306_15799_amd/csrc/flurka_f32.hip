@@ -723,10 +723,12 @@ __global__ __launch_bounds__(256) void f32_bwd_merge_kernel(float* dS, float* dz
     const long bh = rest / mf;
     float s = 0.f;
     if (t < d) {
-        for (int r = 0; r < R; ++r) s += dSpart[((bh * R + r) * mfp + j) * D + t];
+        const float* const ps = dSpart + (bh * R * mfp + j) * D + t;
+        for_parts<8, float>(R, [&](int r) { return ps[(long)r * mfp * D]; }, [&](float x) { s += x; });
         dS[(bh * mf + j) * d + t] = s;
     } else {
-        for (int r = 0; r < R; ++r) s += dzpart[(bh * R + r) * mfp + j];
+        const float* const pz = dzpart + bh * R * mfp + j;
+        for_parts<8, float>(R, [&](int r) { return pz[(long)r * mfp]; }, [&](float x) { s += x; });
         dz[bh * mf + j] = s;
     }
 }
@@ -745,7 +747,8 @@ __global__ __launch_bounds__(256) void f32_domega_merge_kernel(float* dW, const 
         for (int h = h0; h < h1; ++h) {
             const long bh = (long)b * H + h;
             float x = key_part[(bh * m + j) * d + t];
-            for (int r = 0; r < R; ++r) x += part[((bh * R + r) * mfp + j) * D + t];
+            const float* const pw = part + (bh * R * mfp + j) * D + t;
+            for_parts<8, float>(R, [&](int r) { return pw[(long)r * mfp * D]; }, [&](float y) { x += y; });
             s += x;
         }
     dW[idx] = s;

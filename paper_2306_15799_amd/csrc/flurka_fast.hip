@@ -442,10 +442,10 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(WideFinishArgs a) {
     const int tn = b * a.tiles_per_batch + c / GBN, tm = r0 / GBM;
     const int eo = partial_elem_offset(r0 % GBM, c % GBN);
     float4 sum = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < a.splits; ++s) {
-        const float4 x = *(const float4*)(a.part + partial_tile_index(which, s, tn, tm, a.splits, a.tilesN, a.tilesM) * G_TILE_ELEMS + eo);
-        sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
-    }
+    for_parts<8, float4>(
+        a.splits,
+        [&](int s) { return *(const float4*)(a.part + partial_tile_index(which, s, tn, tm, a.splits, a.tilesN, a.tilesM) * G_TILE_ELEMS + eo); },
+        [&](const float4& x) { sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w; });
     const float v[4] = {sum.x, sum.y, sum.z, sum.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {

@@ -26,12 +26,9 @@ __global__ __launch_bounds__(256) void gemm_f32_sum_kernel(void* C, void* C2, co
     void* const c = blockIdx.y ? C2 : C;
     if (i + 4 <= count) {
         float s[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int u = 0; u < splits; ++u) {
-            float x[4];
-            __builtin_memcpy(x, p + u * plane, 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] += x[e];
-        }
+        for_parts<8, float4>(
+            splits, [&](int u) { float4 x; __builtin_memcpy(&x, p + u * plane, 16); return x; },
+            [&](const float4& x) { s[0] += x.x; s[1] += x.y; s[2] += x.z; s[3] += x.w; });
         if (c_bf16) {
             const uint2 v = {pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3])};
             __builtin_memcpy((uint16_t*)c + i, &v, 8);

@@ -56,6 +56,21 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 __device__ __forceinline__ uint4 ld16(const void* p) { return *(const uint4*)p; }
 
+// Sum over `count` parts, in order, U loads in flight at a time (a loop over a run-time count waits for every
+// load before it asks for the next: 32 parts took 20 us, of which the transfer is 2).  load(r) is called with
+// indices 0 .. count - 1 only, some of them more than once; add(x) with every part once.
+template <int U, class T, class Load, class Add>
+__device__ __forceinline__ void for_parts(int count, Load&& load, Add&& add) {
+    for (int r0 = 0; r0 < count; r0 += U) {
+        T x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = load(r0 + u < count ? r0 + u : count - 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (r0 + u < count) add(x[u]);
+    }
+}
+
 // Combine the values that lanes l and l ^ 32 hold (the two halves of a wavefront carry the two
 // halves of an MFMA reduction).  v_permlane32_swap exchanges the upper half of one register with the
 // lower half of another, so two copies of x become {lo, lo} and {hi, hi}: no LDS round trip.
