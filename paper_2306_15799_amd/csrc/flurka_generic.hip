@@ -448,7 +448,7 @@ flurka_status generic_forward(const Problem& p, const FwdArgs& a, hipStream_t s)
     {
         StageScope sc(s, STAGE_PROJECT);
         // nothing of the workspace is in use yet: all of it may hold split partials
-        if ((st = project(p, a, a.ctx + L.Kp, a.ctx + L.Vp, a.ws, W.total, s)) != FLURKA_OK) return st;
+        if ((st = project(p, a, a.ctx + L.Kp, a.ctx + L.Vp, a.ws, generic_ws_floats(p, 0), s)) != FLURKA_OK) return st;
     }
     {
         StageScope sc(s, STAGE_KEY_STATE);
@@ -508,8 +508,12 @@ static flurka_status fused_backward(const Problem& p, const BwdArgs& a, hipStrea
 }
 
 size_t generic_ws_floats(const Problem& p, int bwd) {
-    if (bwd && f32_fused_supported(p)) return f32_bwd_ws_layout(p).total;
-    return generic_ws_layout(p, bwd).total;
+    const size_t unfused = generic_ws_layout(p, bwd).total;
+    if (!f32_fused_supported(p)) return unfused;
+    if (bwd) return f32_bwd_ws_layout(p).total;
+    // split partials of the projection: fewer than 512 tiles of 128 x 128 are split, into at most 1024 in all
+    const size_t partials = (size_t)1024 * 128 * 128;
+    return unfused < partials ? unfused : partials;
 }
 
 flurka_status generic_backward(const Problem& p, const BwdArgs& a, hipStream_t s) {

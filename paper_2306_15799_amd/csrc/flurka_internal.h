@@ -85,7 +85,7 @@ static inline GenericWs generic_ws_layout(const Problem& p, int bwd) {
 }
 
 // Scratch of the generic path in floats.  The fused kernels (d <= 128) need no room in the forward beyond
-// split partials of the projection, for which they use what the unfused ones would take.
+// split partials of the projection, for which they take what the unfused ones would, at most 64 MiB.
 size_t generic_ws_floats(const Problem& p, int bwd);
 
 struct FwdArgs {
