@@ -5,6 +5,7 @@
 
 namespace flurka {
 
+struct PartialTile;
 struct KeyStatePlan {
     int kpad;              // k rounded up to whole 32-key tiles
     int FT;                // 32-feature tiles
@@ -26,7 +27,7 @@ struct KeyStateBuffers {
 // Sums the projection's tile-ordered split partials (tilesM x tilesN tiles per split and tensor) into
 // ctx (K', V'), then fills S, z, c in ctx and the St/zp/cw images.
 flurka_status fast_key_state(const Problem& p, const void* omega, float* ctx, const float* partials,
-                             int tilesM, int tilesN, int splits, const KeyStateBuffers& b, hipStream_t s);
+                             const PartialTile& tile, int tilesM, int tilesN, int splits, const KeyStateBuffers& b, hipStream_t s);
 
 // Kernel attention without a sequence projection (p.k == p.n, K' = K, V' = V): packs the caller's bf16
 // K, V into the key-state operand images and fills S, z, c in ctx and the St/zp/cw images.
@@ -34,7 +35,7 @@ flurka_status fast_identity_key_state(const Problem& p, const void* K, const voi
                                       float* z, float* c, const KeyStateBuffers& b, hipStream_t s);
 // The projection's second stage alone: sums the split partials into K', V' (ctx) and, with `images`,
 // writes the key-state operand images.
-flurka_status fast_proj_finish(const Problem& p, float* ctx, const float* partials, int tilesM, int tilesN,
+flurka_status fast_proj_finish(const Problem& p, float* ctx, const float* partials, const PartialTile& tile, int tilesM, int tilesN,
                                int splits, bool images, const KeyStateBuffers& b, hipStream_t s);
 
 // Grid of a kernel whose workgroups split `items` evenly among themselves: as many workgroups as the

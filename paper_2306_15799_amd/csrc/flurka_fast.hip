@@ -14,6 +14,7 @@
 // Formulas: Eq. 2 with the App. D row normaliser; feature maps of Sec. 2, "Kernel Methods".
 #include "flurka_fast.h"
 #include "flurka_gemm.h"
+#include "flurka_gemm_tile.h"
 
 namespace flurka {
 
@@ -27,26 +28,83 @@ static inline dim3 grid1d(long total, int block) { return dim3((unsigned)((total
 // ===========================================================================
 // Stage "project": C[k x (BH*d)] = E[k x n] * X[n x (BH*d)] for X in {K, V}
 // ===========================================================================
-constexpr int PBM = GBM, PBN = GBN, PBK = GBK;   // tile of the shared GEMM main loop (flurka_gemm.h)
-
-struct ProjPlan {
+struct SplitGemmPlan {
+    int kind;              // index into SPLIT_GEMM_KINDS
+    PartialTile t;         // output tile
     int tilesM, tilesN, splits, steps_per_split, total_steps;
+    size_t partial_bytes() const { return (size_t)2 * splits * tilesM * tilesN * t.tm * t.tn * 4; }
 };
 
-static ProjPlan proj_plan(const Problem& p) {
-    ProjPlan q;
-    q.tilesM = (p.k + PBM - 1) / PBM;
-    const int heads_per_tile = PBN / p.d;
-    q.tilesN = (p.BH + heads_per_tile - 1) / heads_per_tile;
-    q.total_steps = (p.n + PBK - 1) / PBK;        // a ragged last step reads the missing positions as zero
-    const int tiles = q.tilesM * q.tilesN * 2;
-    int splits = chip_cus() / tiles;               // one workgroup per compute unit
-    if (splits < 1) splits = 1;
-    if (splits > 8) splits = splits / 8 * 8;       // keep each XCD on its own n-ranges
-    if (splits > q.total_steps) splits = q.total_steps;
-    q.steps_per_split = (q.total_steps + splits - 1) / splits;
-    q.splits = (q.total_steps + q.steps_per_split - 1) / q.steps_per_split;
-    return q;
+// Output tiles of the products that leave fp32 split partials, and the time of one 64-deep reduction step of a
+// workgroup that has a compute unit to itself.  Measured with operands from HBM: the 256 x 256 tile is bound by
+// its matrix instructions, the others by how fast a compute unit takes its operands in (50 - 57 GB/s).
+struct SplitGemmKind { PartialTile t; double step_us; };
+constexpr SplitGemmKind SPLIT_GEMM_KINDS[] = {
+    {{256, 256, 128, 128}, 1.78}, {{128, 256, 64, 64}, 0.95}, {{128, 128, 64, 64}, 0.6}, {{64, 128, 32, 64}, 0.45}};
+
+// Tile and split of two products of k rows, `batches` times `cols` columns (no tile crosses a batch) and `total_steps` steps whose operands are `bytes` long.
+// The partial results are the price of a split (written at the end, when nothing is left to read beside it, and
+// read again by the second stage, both at about 4.5 TB/s): 64 MiB with a 256 x 256 tile on every compute unit,
+// whatever the size of the problem.  Short reductions want the smaller tiles and few splits, long ones the large
+// tile.  Measured, forward passes, 256 x 256 with one split per compute unit against this rule's choice:
+//   k 256, n 4096, 64 heads of 64:    98.1 -> 81.0 us (128 x 128)     k 64, the same:    71.3 -> 56.7 us (64 x 128)
+//   k 256, n 16384, 64 heads of 64:  164.2 -> 156.7 us (128 x 256)    k 512, n 65536, 16 heads of 128: 437 us (stays)
+static SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_steps, double bytes) {
+    const int cus = chip_cus();
+    SplitGemmPlan best{};
+    double best_t = -1.0;
+    for (int kind = 0; kind < 4; ++kind) {
+        SplitGemmPlan q;
+        q.kind = kind;
+        q.t = SPLIT_GEMM_KINDS[kind].t;
+        q.tilesM = (k + q.t.tm - 1) / q.t.tm;
+        q.tilesN = batches * ((cols + q.t.tn - 1) / q.t.tn);
+        q.total_steps = total_steps;
+        const int tiles = q.tilesM * q.tilesN * 2;
+        const int most = tiles < cus ? (cus / tiles < total_steps ? cus / tiles : total_steps) : 1;
+        for (int want = 1; want <= most; want += want < 8 ? 1 : 8) {
+            q.steps_per_split = (total_steps + want - 1) / want;
+            q.splits = (total_steps + q.steps_per_split - 1) / q.steps_per_split;
+            const double read = bytes / 4.8e6;
+            double t = (double)q.steps_per_split * ((tiles + cus - 1) / cus) * SPLIT_GEMM_KINDS[kind].step_us;
+            if (t < read) t = read;
+            t += 2.0 * (double)q.partial_bytes() / 4.5e6 + 0.1 * q.splits;
+            if (best_t < 0.0 || t < best_t) { best_t = t; best = q; }
+        }
+    }
+    return best;
+}
+
+static SplitGemmPlan proj_plan(const Problem& p) {
+    return split_gemm_plan(p.k, 1, p.BH * p.d, (p.n + GBK - 1) / GBK, 4.0 * p.n * ((double)p.BH * p.d + p.k));
+}
+
+static void set_plan(GemmParams& gp, const SplitGemmPlan& q) {
+    gp.tilesM = q.tilesM; gp.tilesN = q.tilesN; gp.splits = q.splits;
+    gp.steps_per_split = q.steps_per_split; gp.total_steps = q.total_steps;
+}
+
+// one of the tiles behind the 256 x 256 one; Pol<TM, TN>
+template <template <int, int> class Pol>
+static flurka_status launch_split_gemm(const SplitGemmPlan& q, const GemmParams& gp, hipStream_t s) {
+    if (q.kind == 1) return launch_gemm_tile<Pol<128, 256>, 3>(gp, s);
+    if (q.kind == 2) return launch_gemm_tile<Pol<128, 128>, 4>(gp, s);
+    return launch_gemm_tile<Pol<64, 128>, 4>(gp, s);
+}
+template <int TM, int TN> using TProj64 = TProjPolicy<64, TM, TN>;
+template <int TM, int TN> using TProj128 = TProjPolicy<128, TM, TN>;
+
+static flurka_status launch_proj(const Problem& p, const SplitGemmPlan& q, const void* E, const void* F, const void* K,
+                                 const void* V, void* partial, hipStream_t s) {
+    StageScope sc(s, STAGE_K_PROJ_GEMM);
+    GemmParams gp{};
+    gp.A[0] = (const uint16_t*)E; gp.A[1] = (const uint16_t*)F;
+    gp.B[0] = (const uint16_t*)K; gp.B[1] = (const uint16_t*)V;
+    gp.C[0] = partial;
+    gp.n = p.n; gp.d = p.d; gp.k = p.k; gp.BH = p.BH; gp.kp = p.k;
+    set_plan(gp, q);
+    if (q.kind == 0) return p.d == 64 ? launch_gemm_mfma<ProjPolicy<64>>(gp, s) : launch_gemm_mfma<ProjPolicy<128>>(gp, s);
+    return p.d == 64 ? launch_split_gemm<TProj64>(q, gp, s) : launch_split_gemm<TProj128>(q, gp, s);
 }
 
 // ===========================================================================
@@ -293,8 +351,8 @@ bool fast_supported(const Problem& p, int bwd) {
     if (p.n % 8 != 0) return false;                // rows of E and F start on 16-byte boundaries
     if (query_lds_bytes(p) > 160 * 1024) return false;
     // 32-bit byte offsets inside the projection's buffer descriptors
-    if (((size_t)p.k + PBM) * (size_t)p.n * 2 >= ((size_t)1 << 31)) return false;
-    if ((size_t)(PBN / p.d) * (size_t)p.n * (size_t)p.d * 2 >= ((size_t)1 << 31)) return false;
+    if (((size_t)p.k + GBM) * (size_t)p.n * 2 >= ((size_t)1 << 31)) return false;
+    if ((size_t)(GBN / p.d) * (size_t)p.n * (size_t)p.d * 2 >= ((size_t)1 << 31)) return false;
     return true;
 }
 
@@ -312,12 +370,12 @@ struct FastWs {
 
 static FastWs fast_ws_layout(const Problem& p) {
     FastWs W{};
-    const ProjPlan q = proj_plan(p);
+    const SplitGemmPlan q = proj_plan(p);
     const KeyStatePlan ks = key_state_plan(p);
     const size_t BH = (size_t)p.BH;
     size_t o = 0;
     // tile-ordered fp32 partials of K' and V', one set per split
-    W.partial = o; o += round_up((size_t)2 * q.splits * q.tilesM * q.tilesN * G_TILE_ELEMS * 4, 256);
+    W.partial = o; o += round_up(q.partial_bytes(), 256);
     W.Kimg = o;    o += round_up(p.elu ? 0 : 3 * BH * ks.kpad * p.d * 2, 256);
     W.Vimg = o;    o += round_up(2 * BH * (ks.kpad / 2) * p.d * 4, 256);
     W.nrm = o;     o += round_up(BH * ks.kpad * 4, 256);
@@ -386,28 +444,13 @@ flurka_status fast_forward(const Problem& p, const FwdArgs& a, hipStream_t s) {
     const FastWs W = fast_ws_layout(p);
     unsigned char* wsb = (unsigned char*)a.ws;
     flurka_status st;
-    int proj_splits = 1;
-    {
-        StageScope sc(s, STAGE_K_PROJ_GEMM);
-        const ProjPlan q = proj_plan(p);
-        GemmParams gp{};
-        gp.A[0] = (const uint16_t*)a.E; gp.A[1] = (const uint16_t*)a.F;
-        gp.B[0] = (const uint16_t*)a.K; gp.B[1] = (const uint16_t*)a.V;
-        gp.C[0] = wsb + W.partial;
-        gp.C[1] = nullptr;
-        gp.n = p.n; gp.d = p.d; gp.k = p.k; gp.BH = p.BH; gp.kp = p.k;
-        gp.tilesM = q.tilesM; gp.tilesN = q.tilesN; gp.splits = q.splits;
-        gp.steps_per_split = q.steps_per_split; gp.total_steps = q.total_steps;
-        st = p.d == 64 ? launch_gemm_mfma<ProjPolicy<64>>(gp, s) : launch_gemm_mfma<ProjPolicy<128>>(gp, s);
-        if (st != FLURKA_OK) return st;
-        proj_splits = q.splits;
-    }
+    const SplitGemmPlan q = proj_plan(p);
+    if ((st = launch_proj(p, q, a.E, a.F, a.K, a.V, wsb + W.partial, s)) != FLURKA_OK) return st;
     {
         KeyStateBuffers kb{};
         kb.Kimg = (uint16_t*)(wsb + W.Kimg); kb.Vimg = (uint32_t*)(wsb + W.Vimg); kb.nrm = (float*)(wsb + W.nrm);
         kb.St = (uint16_t*)(wsb + W.St); kb.zp = (float*)(wsb + W.zp); kb.cw = (uint16_t*)(wsb + W.cw);
-        const ProjPlan q = proj_plan(p);
-        st = fast_key_state(p, a.omega, a.ctx, (const float*)(wsb + W.partial), q.tilesM, q.tilesN, proj_splits, kb, s);
+        st = fast_key_state(p, a.omega, a.ctx, (const float*)(wsb + W.partial), q.t, q.tilesM, q.tilesN, q.splits, kb, s);
         if (st != FLURKA_OK) return st;
     }
     return run_query_stream(p, a.Q, a.omega, a.out, a.ctx + ctx_layout(p).lse, (const uint16_t*)(wsb + W.St),
@@ -425,6 +468,7 @@ flurka_status fast_forward(const Problem& p, const FwdArgs& a, hipStream_t s) {
 struct WideFinishArgs {
     const float* part;
     uint16_t* img;
+    PartialTile tile;
     int splits, tilesM, tilesN, tiles_per_batch, k, dm, B;
 };
 
@@ -439,12 +483,13 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(WideFinishArgs a) {
     const int which = (int)(wid / a.B);
     const int c = 64 * cc + lane, r0 = 4 * rg;
     if (c >= a.dm) return;
-    const int tn = b * a.tiles_per_batch + c / GBN, tm = r0 / GBM;
-    const int eo = partial_elem_offset(r0 % GBM, c % GBN);
+    const int tn = b * a.tiles_per_batch + c / a.tile.tn, tm = r0 / a.tile.tm;
+    const int eo = partial_elem_offset(a.tile, r0 % a.tile.tm, c % a.tile.tn);
+    const long tile_elems = a.tile.tm * a.tile.tn;
     float4 sum = {0.f, 0.f, 0.f, 0.f};
     for_parts<8, float4>(
         a.splits,
-        [&](int s) { return *(const float4*)(a.part + partial_tile_index(which, s, tn, tm, a.splits, a.tilesN, a.tilesM) * G_TILE_ELEMS + eo); },
+        [&](int s) { return *(const float4*)(a.part + partial_tile_index(which, s, tn, tm, a.splits, a.tilesN, a.tilesM) * tile_elems + eo); },
         [&](const float4& x) { sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w; });
     const float v[4] = {sum.x, sum.y, sum.z, sum.w};
 #pragma unroll
@@ -459,36 +504,18 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(WideFinishArgs a) {
     }
 }
 
-struct SplitPlan { int splits, steps_per_split; };
-// split of a reduction of `total_steps` steps so that `tiles` output tiles give about one workgroup per
-// compute unit (the rule of proj_plan)
-static SplitPlan split_plan(int tiles, int total_steps) {
-    int splits = chip_cus() / tiles;
-    if (splits < 1) splits = 1;
-    if (splits > 8) splits = splits / 8 * 8;
-    if (splits > total_steps) splits = total_steps;
-    SplitPlan q;
-    q.steps_per_split = (total_steps + splits - 1) / splits;
-    q.splits = (total_steps + q.steps_per_split - 1) / q.steps_per_split;
-    return q;
-}
-
 struct FusedWPlan {
-    int tilesM, tpb1, tilesN1, steps1, tpb2, tilesN2, steps2;
-    SplitPlan s1, s2;
+    int tpb1, tpb2;                // column tiles per batch of the two products
+    SplitGemmPlan s1, s2;
 };
 
 static FusedWPlan fusedw_plan(const Problem& p, int dm) {
     FusedWPlan q;
-    q.tilesM = (p.k + GBM - 1) / GBM;
-    q.tpb1 = (dm + GBN - 1) / GBN;
-    q.tilesN1 = p.B * q.tpb1;
-    q.steps1 = (p.n + GBK - 1) / GBK;
-    q.s1 = split_plan(q.tilesM * q.tilesN1 * 2, q.steps1);
-    q.tpb2 = p.H * p.d / GBN;
-    q.tilesN2 = p.B * q.tpb2;
-    q.steps2 = 3 * dm / GBK;
-    q.s2 = split_plan(q.tilesM * q.tilesN2 * 2, q.steps2);
+    q.s1 = split_gemm_plan(p.k, p.B, dm, (p.n + GBK - 1) / GBK, 4.0 * p.n * ((double)p.B * dm + p.k));
+    q.tpb1 = q.s1.tilesN / p.B;
+    const double terms = 3.0 * dm * 2.0;
+    q.s2 = split_gemm_plan(p.k, p.B, p.H * p.d, 3 * dm / GBK, 2.0 * terms * p.B * p.k + 4.0 * p.H * p.d * dm);
+    q.tpb2 = q.s2.tilesN / p.B;
     return q;
 }
 
@@ -508,8 +535,7 @@ struct FusedWWs { size_t partial, img, rest, total; };
 static FusedWWs fusedw_ws_layout(const Problem& p, int dm) {
     const FusedWPlan q = fusedw_plan(p, dm);
     FusedWWs W{};
-    const size_t p1 = (size_t)2 * q.s1.splits * q.tilesM * q.tilesN1 * G_TILE_ELEMS * 4;
-    const size_t p2 = (size_t)2 * q.s2.splits * q.tilesM * q.tilesN2 * G_TILE_ELEMS * 4;
+    const size_t p1 = q.s1.partial_bytes(), p2 = q.s2.partial_bytes();
     size_t o = 0;
     W.partial = o; o += round_up(p1 > p2 ? p1 : p2, 256);    // the second product reuses the first one's room
     W.img = o;     o += round_up((size_t)2 * p.B * p.k * 3 * dm * 2, 256);
@@ -535,15 +561,16 @@ flurka_status fast_forward_fusedw(const Problem& p, const FusedWArgs& a, hipStre
         gp.C[0] = wsb + W.partial;
         gp.n = p.n; gp.d = p.d; gp.k = p.k; gp.BH = p.BH; gp.kp = p.k;
         gp.dm = a.dm; gp.tiles_per_batch = q.tpb1;
-        gp.tilesM = q.tilesM; gp.tilesN = q.tilesN1; gp.splits = q.s1.splits;
-        gp.steps_per_split = q.s1.steps_per_split; gp.total_steps = q.steps1;
-        if ((st = launch_gemm_mfma<ProjWidePolicy>(gp, s)) != FLURKA_OK) return st;
+        set_plan(gp, q.s1);
+        st = q.s1.kind == 0 ? launch_gemm_mfma<ProjWidePolicy>(gp, s) : launch_split_gemm<TWidePolicy>(q.s1, gp, s);
+        if (st != FLURKA_OK) return st;
     }
     {
         StageScope sc(s, STAGE_K_WIDE_FINISH);
         WideFinishArgs fa{};
         fa.part = (const float*)(wsb + W.partial); fa.img = (uint16_t*)(wsb + W.img);
-        fa.splits = q.s1.splits; fa.tilesM = q.tilesM; fa.tilesN = q.tilesN1; fa.tiles_per_batch = q.tpb1;
+        fa.tile = q.s1.t;
+        fa.splits = q.s1.splits; fa.tilesM = q.s1.tilesM; fa.tilesN = q.s1.tilesN; fa.tiles_per_batch = q.tpb1;
         fa.k = p.k; fa.dm = a.dm; fa.B = p.B;
         const long waves = (long)2 * p.B * ((p.k + 3) / 4) * ((a.dm + 63) / 64);
         hipLaunchKernelGGL(wide_finish_kernel, grid1d(waves, 4), dim3(256), 0, s, fa);
@@ -558,14 +585,14 @@ flurka_status fast_forward_fusedw(const Problem& p, const FusedWArgs& a, hipStre
         gp.C[0] = wsb + W.partial;
         gp.n = p.n; gp.d = p.d; gp.k = p.k; gp.BH = p.BH; gp.kp = p.k;
         gp.dm = a.dm; gp.tiles_per_batch = q.tpb2;
-        gp.tilesM = q.tilesM; gp.tilesN = q.tilesN2; gp.splits = q.s2.splits;
-        gp.steps_per_split = q.s2.steps_per_split; gp.total_steps = q.steps2;
-        if ((st = launch_gemm_mfma<TransformPolicy>(gp, s)) != FLURKA_OK) return st;
+        set_plan(gp, q.s2);
+        st = q.s2.kind == 0 ? launch_gemm_mfma<TransformPolicy>(gp, s) : launch_split_gemm<TTransformPolicy>(q.s2, gp, s);
+        if (st != FLURKA_OK) return st;
     }
     KeyStateBuffers kb{};
     kb.Kimg = (uint16_t*)(rest + R.Kimg); kb.Vimg = (uint32_t*)(rest + R.Vimg); kb.nrm = (float*)(rest + R.nrm);
     kb.St = (uint16_t*)(rest + R.St); kb.zp = (float*)(rest + R.zp); kb.cw = (uint16_t*)(rest + R.cw);
-    st = fast_key_state(p, a.omega, a.ctx, (const float*)(wsb + W.partial), q.tilesM, q.tilesN2, q.s2.splits, kb, s);
+    st = fast_key_state(p, a.omega, a.ctx, (const float*)(wsb + W.partial), q.s2.t, q.s2.tilesM, q.s2.tilesN, q.s2.splits, kb, s);
     if (st != FLURKA_OK) return st;
     return run_query_stream(p, a.Q, a.omega, a.out, a.ctx + ctx_layout(p).lse, kb.St, kb.zp, kb.cw, s);
 }
@@ -626,10 +653,10 @@ static Problem query_problem_linformer(const Problem& p) {
 struct LinformerWs { size_t partial, Wimg, St, zp, cw, total; };
 static LinformerWs linformer_ws_layout(const Problem& p) {
     LinformerWs W{};
-    const ProjPlan q = proj_plan(p);
+    const SplitGemmPlan q = proj_plan(p);
     const size_t BH = (size_t)p.BH, kpad = (size_t)(p.k + 31) / 32 * 32;
     size_t o = 0;
-    W.partial = o; o += round_up((size_t)2 * q.splits * q.tilesM * q.tilesN * G_TILE_ELEMS * 4, 256);
+    W.partial = o; o += round_up(q.partial_bytes(), 256);
     W.Wimg = o;    o += round_up(BH * kpad * p.d * 2, 256);
     W.St = o;      o += round_up(BH * p.d * kpad * 2, 256);
     W.zp = o;      o += round_up(BH * kpad * 4, 256);
@@ -639,7 +666,7 @@ static LinformerWs linformer_ws_layout(const Problem& p) {
 }
 
 bool fast_baseline_supported(int which, const Problem& p) {
-    if (!p.bf16 || (p.d != 64 && p.d != 128) || p.n % PBK != 0) return false;
+    if (!p.bf16 || (p.d != 64 && p.d != 128) || p.n % GBK != 0) return false;
     if (which == FLURKA_BASELINE_KERNEL_ATTN) {
         if (p.k != p.n || p.mf % 32 != 0) return false;
         if (query_lds_bytes(p) > 160 * 1024) return false;
@@ -676,23 +703,12 @@ flurka_status fast_kernel_attn_forward(const Problem& p, const FwdArgs& a, hipSt
 flurka_status fast_linformer_forward(const Problem& p, const FwdArgs& a, hipStream_t s) {
     const LinformerWs W = linformer_ws_layout(p);
     const CtxLayout L = ctx_layout(p);
-    const ProjPlan q = proj_plan(p);
+    const SplitGemmPlan q = proj_plan(p);
     unsigned char* wsb = (unsigned char*)a.ws;
     flurka_status st;
-    {
-        StageScope sc(s, STAGE_K_PROJ_GEMM);
-        GemmParams gp{};
-        gp.A[0] = (const uint16_t*)a.E; gp.A[1] = (const uint16_t*)a.F;
-        gp.B[0] = (const uint16_t*)a.K; gp.B[1] = (const uint16_t*)a.V;
-        gp.C[0] = wsb + W.partial;
-        gp.n = p.n; gp.d = p.d; gp.k = p.k; gp.BH = p.BH; gp.kp = p.k;
-        gp.tilesM = q.tilesM; gp.tilesN = q.tilesN; gp.splits = q.splits;
-        gp.steps_per_split = q.steps_per_split; gp.total_steps = q.total_steps;
-        st = p.d == 64 ? launch_gemm_mfma<ProjPolicy<64>>(gp, s) : launch_gemm_mfma<ProjPolicy<128>>(gp, s);
-        if (st != FLURKA_OK) return st;
-    }
+    if ((st = launch_proj(p, q, a.E, a.F, a.K, a.V, wsb + W.partial, s)) != FLURKA_OK) return st;
     KeyStateBuffers none{};
-    if ((st = fast_proj_finish(p, a.ctx, (const float*)(wsb + W.partial), q.tilesM, q.tilesN, q.splits, false, none, s)) != FLURKA_OK)
+    if ((st = fast_proj_finish(p, a.ctx, (const float*)(wsb + W.partial), q.t, q.tilesM, q.tilesN, q.splits, false, none, s)) != FLURKA_OK)
         return st;
     const Problem pq = query_problem_linformer(p);
     {

@@ -57,6 +57,15 @@ __host__ __device__ inline int partial_elem_offset(int r, int c) {
     return ((((wave * 4 + i) * 4 + j) * 4 + q) * 64 + lane) * 4 + e;
 }
 
+// The same for tiles of tm x tn elements whose wavefronts hold wr x wc each.
+struct PartialTile { int tm, tn, wr, wc; };
+__host__ __device__ inline int partial_elem_offset(const PartialTile& t, int r, int c) {
+    const int fi = t.wr / 32, fj = t.wc / 32;
+    const int wave = (r / t.wr) * (t.tn / t.wc) + c / t.wc, i = (r >> 5) % fi, j = (c >> 5) % fj, q = (r >> 3) & 3;
+    const int lane = 32 * ((r >> 2) & 1) + (c & 31), e = r & 3;
+    return ((((wave * fi + i) * fj + j) * 4 + q) * 64 + lane) * 4 + e;
+}
+
 struct GemmParams {
     const uint16_t* A[2];
     const uint16_t* B[2];
@@ -64,7 +73,7 @@ struct GemmParams {
                              // for policies with PARTIAL_TILES
     int tilesM, tilesN, splits, steps_per_split, total_steps;
     int n, d, k, BH, kp;     // problem sizes the policies need (kp: padded k of an image)
-    int dm, tiles_per_batch; // model width and 256-column tiles per batch (policies of the paper-order path)
+    int dm, tiles_per_batch; // model width and column tiles per batch (policies of the paper-order path)
 };
 
 template <int N>

@@ -48,6 +48,7 @@ struct FinishArgs {
     uint32_t* Vimg;         // 2 x (BH, kpad/2, d) dwords: hi, lo; low half = even key (nullptr: K', V' only)
     float* nrm;             // (BH, kpad): |k'|^2/2, +inf for the padding keys (nullptr for elu1)
     int splits, tilesM, tilesN, k, kpad, d, BH;
+    PartialTile tile;       // of the partial results
 };
 
 __global__ __launch_bounds__(256) void proj_finish_kernel(FinishArgs a) {
@@ -57,17 +58,18 @@ __global__ __launch_bounds__(256) void proj_finish_kernel(FinishArgs a) {
     if (wid >= (long)a.BH * groups_per_head) return;
     const int bh = (int)(wid / groups_per_head);
     const int r0 = 4 * (int)(wid % groups_per_head);           // keys r0 .. r0 + 3
-    const int hpt = GBN / a.d;                                  // heads per column tile
-    const int tn = bh / hpt, tm = r0 / GBM;
+    const int hpt = a.tile.tn / a.d;                                 // heads per column tile
+    const int tn = bh / hpt, tm = r0 / a.tile.tm;
+    const long tile_elems = a.tile.tm * a.tile.tn;
     const long img_plane = (long)a.BH * a.kpad * a.d;          // elements per K image plane
     const long vimg_plane = (long)a.BH * (a.kpad / 2) * a.d;
     float sq[4] = {0.f, 0.f, 0.f, 0.f};
     for (int t = lane; t < a.d; t += 64) {
-        const int eo = partial_elem_offset(r0 % GBM, (bh % hpt) * a.d + t);
+        const int eo = partial_elem_offset(a.tile, r0 % a.tile.tm, (bh % hpt) * a.d + t);
         float4 ks = {0.f, 0.f, 0.f, 0.f}, vs = {0.f, 0.f, 0.f, 0.f};
         for (int s = 0; s < a.splits; ++s) {
-            const float4 x = *(const float4*)(a.part + partial_tile_index(0, s, tn, tm, a.splits, a.tilesN, a.tilesM) * G_TILE_ELEMS + eo);
-            const float4 y = *(const float4*)(a.part + partial_tile_index(1, s, tn, tm, a.splits, a.tilesN, a.tilesM) * G_TILE_ELEMS + eo);
+            const float4 x = *(const float4*)(a.part + partial_tile_index(0, s, tn, tm, a.splits, a.tilesN, a.tilesM) * tile_elems + eo);
+            const float4 y = *(const float4*)(a.part + partial_tile_index(1, s, tn, tm, a.splits, a.tilesN, a.tilesM) * tile_elems + eo);
             ks.x += x.x; ks.y += x.y; ks.z += x.z; ks.w += x.w;
             vs.x += y.x; vs.y += y.y; vs.z += y.z; vs.w += y.w;
         }
@@ -456,13 +458,13 @@ static flurka_status launch_key_state(const Problem& p, const KeyStateArgs& ka, 
     return p.elu ? launch_key_state_impl<D, true, false>(p, ka, s) : launch_key_state_impl<D, false, false>(p, ka, s);
 }
 
-flurka_status fast_proj_finish(const Problem& p, float* ctx, const float* partials, int tilesM, int tilesN,
+flurka_status fast_proj_finish(const Problem& p, float* ctx, const float* partials, const PartialTile& tile, int tilesM, int tilesN,
                                int splits, bool images, const KeyStateBuffers& b, hipStream_t s) {
     const CtxLayout L = ctx_layout(p);
     const KeyStatePlan q = key_state_plan(p);
     StageScope sc(s, STAGE_K_PROJ_FINISH);
     FinishArgs fa{};
-    fa.part = partials; fa.ctx = ctx; fa.tilesM = tilesM; fa.tilesN = tilesN;
+    fa.part = partials; fa.ctx = ctx; fa.tile = tile; fa.tilesM = tilesM; fa.tilesN = tilesN;
     fa.Kp_off = (long)L.Kp; fa.Vp_off = (long)L.Vp;
     fa.Kimg = (p.elu || !images) ? nullptr : b.Kimg; fa.Vimg = images ? b.Vimg : nullptr;
     fa.nrm = (p.elu || !images) ? nullptr : b.nrm;
@@ -474,11 +476,11 @@ flurka_status fast_proj_finish(const Problem& p, float* ctx, const float* partia
 }
 
 flurka_status fast_key_state(const Problem& p, const void* omega, float* ctx, const float* partials,
-                             int tilesM, int tilesN, int splits, const KeyStateBuffers& b, hipStream_t s) {
+                             const PartialTile& tile, int tilesM, int tilesN, int splits, const KeyStateBuffers& b, hipStream_t s) {
     const CtxLayout L = ctx_layout(p);
     const KeyStatePlan q = key_state_plan(p);
     {
-        const flurka_status st = fast_proj_finish(p, ctx, partials, tilesM, tilesN, splits, true, b, s);
+        const flurka_status st = fast_proj_finish(p, ctx, partials, tile, tilesM, tilesN, splits, true, b, s);
         if (st != FLURKA_OK) return st;
     }
     {

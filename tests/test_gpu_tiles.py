@@ -1,0 +1,48 @@
+"""Tiled contractions over the sequence at the edges of their tiles: the projected keys and values that the forward
+leaves in ctx (fp32 sums of bf16 products) against float64."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2306_15799_amd import binding as fb
+from paper_2306_15799_amd import inputs
+from paper_2306_15799_amd.inputs import Workload, PHI_ELU1
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, n, d, k): key counts around the 64-, 128- and 256-row tiles, head counts that leave a column tile ragged, one
+# reduction step and a last one of 8 to 56 positions, one split and many, more tiles than compute units
+SHAPES = [(1, 1, 8, 64, 1), (1, 3, 56, 64, 63), (1, 3, 64, 128, 64), (1, 5, 72, 64, 65), (2, 3, 1000, 64, 100),
+          (1, 1, 2048, 128, 127), (1, 7, 520, 64, 128), (1, 3, 2056, 128, 129), (4, 8, 4096, 64, 255),
+          (4, 4, 4104, 128, 256), (2, 8, 2000, 64, 257), (1, 16, 1032, 128, 300), (8, 80, 136, 64, 33),
+          (4, 24, 200, 128, 400), (1, 2, 8200, 64, 20)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_projected_keys_and_values(shape):
+    B, H, n, d, k = shape
+    w = Workload("tiles", B, H, n, d, k, d, "bf16", PHI_ELU1, False)
+    t = inputs.make_inputs(w, 3)
+    if H > 1:
+        # what lies behind a head's last position in memory must not reach that head
+        t["K"][:, 1, 0, :] = np.inf
+        t["V"][:, 1, 0, :] = np.inf
+    g = gu.to_device(t, "bf16")
+    _, ctx = fb.flurka_attn_fwd(g["Q"], g["K"], g["V"], g["E"], g["F"], g["omega"], phi=w.phi, algo="fast")
+    torch.cuda.synchronize()
+    v = fb.ctx_views(ctx, B, H, n, d, k, d, fb.BF16, w.phi)
+    heads = [h for h in range(H) if h != 1]
+    for name, x, e in (("Kp", t["K"], t["E"]), ("Vp", t["V"], t["F"])):
+        ref = np.matmul(e.astype(np.float64), x[:, heads].astype(np.float64))
+        got = gu.to_host(v[name]).astype(np.float64)[:, heads]
+        # n products are exact in fp32 and added in an order of their own: each partial sum rounds by 2^-24 of
+        # itself, and a random walk of n such errors stays within sqrt(n) 2^-24 of the norm
+        bar = 2.0 * np.sqrt(n) * 2.0 ** -24
+        err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        print(shape, name, f"{err:.2e} of {bar:.2e}")
+        assert err <= bar
+        # no element far off (a wrong row, column or split), by the same walk: its terms have unit variance
+        # times that of one product
+        assert np.abs(got - ref).max() <= 8 * bar * np.sqrt((ref ** 2).mean())
