@@ -14,10 +14,15 @@ struct KeyStatePlan {
 };
 KeyStatePlan key_state_plan(const Problem& p);
 
+// Slot of feature f (0..31) inside a 32-feature tile of the S'^T image: the order in which the first
+// contraction's accumulator hands P'^T on as the B operand of the second (slot 8h + e of a group of 16
+// holds feature 8*(e/4) + 4*h + e%4; the map is its own inverse).
+__host__ __device__ inline int slot_of_feature_tile(int f) { return (f & 16) + 8 * ((f >> 2) & 1) + 4 * ((f >> 3) & 1) + (f & 3); }
+
 // Device scratch of the key-state stage (all inside the caller's workspace).
 struct KeyStateBuffers {
     uint16_t* Kimg;        // 3 x (BH, kpad * d) bf16, key_state's operand order (see proj_finish_kernel)
-    uint32_t* Vimg;        // 2 x (BH, kpad/2, d) dwords
+    uint32_t* Vimg;        // 2 x (BH, kpad/2 * d) dwords, key_state's operand order
     float* nrm;            // (BH, kpad)
     uint16_t* St;          // (BH, d, mf) bf16, feature slots in operand order; performer: S_j / z_j
     float* zp;             // (BH, mf)

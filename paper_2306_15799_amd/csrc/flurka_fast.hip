@@ -137,11 +137,6 @@ struct QueryLds {
     }
 };
 
-// Slot of feature f (0..31) inside a 32-feature tile of the S'^T image: the order in which the first
-// contraction's accumulator hands P'^T on as the B operand of the second (slot 8h + e of a group of 16
-// holds feature 8*(e/4) + 4*h + e%4; the map is its own inverse).
-__host__ __device__ inline int slot_of_feature_tile(int f) { return (f & 16) + 8 * ((f >> 2) & 1) + 4 * ((f >> 3) & 1) + (f & 3); }
-
 // One workgroup = NW wavefronts sharing the LDS image of omega, S^T and z of one head; each wavefront
 // streams QT tiles of 32 query rows at a time.  (QT = 2 would feed two MFMAs per operand fragment read
 // from LDS, but needs more than the 256 architectural VGPRs of a wavefront; the register allocator then

@@ -8,13 +8,20 @@
 //
 // Two kernels:
 //   proj_finish   sums the projection's split-n partials into K', V' (fp32, ctx) and writes the
-//                 operand images: K' as bf16 hi/mid/lo rows, V' as bf16 hi/lo with two consecutive
-//                 keys per dword, and |k'|^2 / 2 per key
+//                 operand images: K' as bf16 hi/mid/lo rows, V' as bf16 hi/lo, both in the order in which
+//                 key_state's wavefronts read them (1 KiB of consecutive bytes per operand), and
+//                 |k'|^2 / 2 per key
 //   key_state     one workgroup per (head, 32 features), one wavefront per key range: first
 //                 contraction on MFMA, column maximum, exp, second contraction on MFMA with PhiK taken
 //                 from the accumulator registers as the A operand; the ranges' partial S, z, c meet in
 //                 LDS, are joined there (log-sum-exp style) and leave as S, z, c (fp32, ctx) and as the
 //                 bf16 images the query-stream kernel loads into LDS
+// Both are bound by latency: a chain of loads, products, exponentials and the merge, on a chip that a few
+// hundred keys per head do not fill.  So every operand of a wavefront is requested before the first is used,
+// and the merge is one pass over LDS by the whole workgroup.  (Requests behind a branch per tile or per key, V' one
+// dword at a time and a merge in transposed 32-coordinate pieces took, key_state alone: 64 keys, 4 heads 15.6 us,
+// now 4.6; elu, 256 keys, 64 heads 19.9, now 6.8; 256 keys, 64 heads 14.4, now 11, where the eight workgroups of a
+// head read its 160 KiB of images eight times out of L2.)
 #include "flurka_fast.h"
 #include "flurka_gemm.h"
 
@@ -45,11 +52,38 @@ struct FinishArgs {
     float* ctx;             // K' at ctx + Kp_off, V' at ctx + Vp_off
     long Kp_off, Vp_off;
     uint16_t* Kimg;         // 3 x (BH, kpad * d) bf16: hi, mid, lo, in key_state's operand order (nullptr for elu1)
-    uint32_t* Vimg;         // 2 x (BH, kpad/2, d) dwords: hi, lo; low half = even key (nullptr: K', V' only)
+    uint32_t* Vimg;         // 2 x (BH, kpad/2 * d) dwords: hi, lo; low half = even key (nullptr: K', V' only)
     float* nrm;             // (BH, kpad): |k'|^2/2, +inf for the padding keys (nullptr for elu1)
     int splits, tilesM, tilesN, k, kpad, d, BH;
     PartialTile tile;       // of the partial results
 };
+
+// Dword of the V' image that holds keys (2 p, 2 p + 1), coordinate t, inside a head: [32-key tile][16-key step]
+// [32-coordinate tile][lane = 32 h + t % 32][4], the lane's four dwords being pairs 2h, 2h + 1, 2h + 4, 2h + 5 of the
+// step: the order in which the accumulator hands PhiK^T on.  Pairs 2i and 2i + 1 are neighbours.
+__device__ __forceinline__ int v_image_offset(int p, int t, int d) {
+    const int q = p & 7;
+    return ((((p >> 3) * (d / 32) + (t >> 5)) * 64) + 32 * ((q >> 1) & 1) + (t & 31)) * 4 + 2 * (q >> 2) + (q & 1);
+}
+// Element of the K' image that holds key r, coordinate t, inside a head: [32-key tile][16-coordinate step]
+// [8-coordinate half][key][8]
+__device__ __forceinline__ int k_image_offset(int r, int t, int d) {
+    return ((((r >> 5) * (d / 16) + (t >> 4)) * 2 + ((t >> 3) & 1)) * 32 + (r & 31)) * 8 + (t & 7);
+}
+
+// value of lane ^ 1 and of lane ^ 2 (DPP quad permutations)
+__device__ __forceinline__ uint32_t lane_xor1(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xb1, 0xf, 0xf, false); }
+__device__ __forceinline__ uint32_t lane_xor2(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4e, 0xf, 0xf, false); }
+// Four lanes t .. t + 3, each with one coordinate of four keys (k0 | k1, k2 | k3 as packed bf16): afterwards each has
+// the four coordinates of one key, lane t % 4 = 0, 1, 2, 3 that of key 0, 2, 1, 3
+__device__ __forceinline__ uint2 transpose_4x4(uint32_t p01, uint32_t p23, int lane) {
+    const bool odd = lane & 1, upper = lane & 2;
+    const uint32_t mine = odd ? p23 : p01, theirs = lane_xor1(odd ? p01 : p23);
+    const uint32_t even_t = odd ? theirs : mine, odd_t = odd ? mine : theirs;      // coordinates t & ~1 and t | 1
+    const uint32_t a = (even_t & 0xffffu) | (odd_t << 16), b = (even_t >> 16) | (odd_t & 0xffff0000u);
+    const uint32_t keep = upper ? b : a, got = lane_xor2(upper ? a : b);
+    return upper ? make_uint2(got, keep) : make_uint2(keep, got);
+}
 
 __global__ __launch_bounds__(256) void proj_finish_kernel(FinishArgs a) {
     const int lane = threadIdx.x & 63;
@@ -58,7 +92,7 @@ __global__ __launch_bounds__(256) void proj_finish_kernel(FinishArgs a) {
     if (wid >= (long)a.BH * groups_per_head) return;
     const int bh = (int)(wid / groups_per_head);
     const int r0 = 4 * (int)(wid % groups_per_head);           // keys r0 .. r0 + 3
-    const int hpt = a.tile.tn / a.d;                                 // heads per column tile
+    const int hpt = a.tile.tn / a.d;                            // heads per column tile
     const int tn = bh / hpt, tm = r0 / a.tile.tm;
     const long tile_elems = a.tile.tm * a.tile.tn;
     const long img_plane = (long)a.BH * a.kpad * a.d;          // elements per K image plane
@@ -66,13 +100,17 @@ __global__ __launch_bounds__(256) void proj_finish_kernel(FinishArgs a) {
     float sq[4] = {0.f, 0.f, 0.f, 0.f};
     for (int t = lane; t < a.d; t += 64) {
         const int eo = partial_elem_offset(a.tile, r0 % a.tile.tm, (bh % hpt) * a.d + t);
+        const float* const p0 = a.part + partial_tile_index(0, 0, tn, tm, a.splits, a.tilesN, a.tilesM) * tile_elems + eo;
+        const float* const p1 = a.part + partial_tile_index(1, 0, tn, tm, a.splits, a.tilesN, a.tilesM) * tile_elems + eo;
+        const long stride = (long)a.tilesN * a.tilesM * tile_elems;
+        struct Pair { float4 k, v; };
         float4 ks = {0.f, 0.f, 0.f, 0.f}, vs = {0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < a.splits; ++s) {
-            const float4 x = *(const float4*)(a.part + partial_tile_index(0, s, tn, tm, a.splits, a.tilesN, a.tilesM) * tile_elems + eo);
-            const float4 y = *(const float4*)(a.part + partial_tile_index(1, s, tn, tm, a.splits, a.tilesN, a.tilesM) * tile_elems + eo);
-            ks.x += x.x; ks.y += x.y; ks.z += x.z; ks.w += x.w;
-            vs.x += y.x; vs.y += y.y; vs.z += y.z; vs.w += y.w;
-        }
+        for_parts<4, Pair>(
+            a.splits, [&](int s) { return Pair{*(const float4*)(p0 + s * stride), *(const float4*)(p1 + s * stride)}; },
+            [&](const Pair& x) {
+                ks.x += x.k.x; ks.y += x.k.y; ks.z += x.k.z; ks.w += x.k.w;
+                vs.x += x.v.x; vs.y += x.v.y; vs.z += x.v.z; vs.w += x.v.w;
+            });
         float kv[4] = {ks.x, ks.y, ks.z, ks.w}, vv[4] = {vs.x, vs.y, vs.z, vs.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -85,25 +123,24 @@ __global__ __launch_bounds__(256) void proj_finish_kernel(FinishArgs a) {
                 kv[e] = 0.f; vv[e] = 0.f;                      // rows of a tile past k hold nothing useful
             }
             sq[e] = fmaf(kv[e], kv[e], sq[e]);
-            if (a.Kimg) {
-                uint16_t hi, mid, lo;
-                split3(kv[e], hi, mid, lo);
-                // operand order of key_state: [32-key tile][16-coordinate step][8-coordinate half][key][8],
-                // so that a wavefront's fragment load is 1 KiB of consecutive bytes
-                const long io = (long)bh * a.kpad * a.d +
-                                ((((long)(r >> 5) * (a.d / 16) + (t >> 4)) * 2 + ((t >> 3) & 1)) * 32 + (r & 31)) * 8 + (t & 7);
-                a.Kimg[io] = hi;
-                a.Kimg[img_plane + io] = mid;
-                a.Kimg[2 * img_plane + io] = lo;
-            }
         }
-#pragma unroll
-        for (int pr = 0; pr < 2 && a.Vimg; ++pr) {
-            uint32_t hp, lp;
-            split2_pair(vv[2 * pr], vv[2 * pr + 1], hp, lp);
-            const long vo = ((long)bh * (a.kpad / 2) + r0 / 2 + pr) * a.d + t;
-            a.Vimg[vo] = hp;
-            a.Vimg[vimg_plane + vo] = lp;
+        if (a.Kimg) {
+            uint32_t h0, m0, l0, h1, m1, l1;
+            split3_pair(kv[0], kv[1], h0, m0, l0);
+            split3_pair(kv[2], kv[3], h1, m1, l1);
+            const int key = ((lane & 1) << 1) | ((lane >> 1) & 1);
+            uint16_t* const o = a.Kimg + (long)bh * a.kpad * a.d + k_image_offset(r0 + key, t & ~3, a.d);
+            *(uint2*)o = transpose_4x4(h0, h1, lane);
+            *(uint2*)(o + img_plane) = transpose_4x4(m0, m1, lane);
+            *(uint2*)(o + 2 * img_plane) = transpose_4x4(l0, l1, lane);
+        }
+        if (a.Vimg) {
+            uint2 hp, lp;
+            split2_pair(vv[0], vv[1], hp.x, lp.x);
+            split2_pair(vv[2], vv[3], hp.y, lp.y);
+            uint32_t* const o = a.Vimg + (long)bh * (a.kpad / 2) * a.d + v_image_offset(r0 / 2, t, a.d);
+            *(uint2*)o = hp;
+            *(uint2*)(o + vimg_plane) = lp;
         }
     }
     if (a.nrm) {
@@ -132,27 +169,24 @@ struct KeyStateArgs {
     int BH, H, k, kpad, mf, mfp, FT, KR, tiles_per_range;   // mf features (ctx strides), mfp = mf rounded up to whole tiles (image strides)
 };
 
-// LDS of a workgroup: per key range the partial S tile (32 features x d, rows padded), z and c; then
-// the merge step's weights, 1/z and one 32 x 32 transposition tile.
+// LDS of a workgroup: per key range the partial S tile (32 features x d, rows padded), z and c
 template <int D>
 struct KeyStateLds {
     static constexpr int s_pitch = D + 4;                                   // floats
-    static __host__ __device__ int range_floats() { return 32 * s_pitch + 64; }
-    static __host__ __device__ int total(int KR) { return (KR * range_floats() + KR * 32 + 32 + 32 * 33) * 4; }
+    static constexpr int range_floats = 32 * s_pitch + 64;
+    static __host__ __device__ int total(int KR) { return KR * range_floats * 4; }
 };
 
-// key tiles of a range that stay in registers (head size 128 keeps fewer, and does without the
-// one-tile-ahead request of V' below: its eight wavefronts per workgroup share 256 registers each)
-template <int D> struct KeyStateKeep { static constexpr int value = D <= 64 ? 4 : 2; };
-
-// most wavefronts (key ranges) per workgroup: what the kernel's register need leaves room for
-template <int D> struct KeyStateMaxWaves { static constexpr int value = 8; };
+constexpr int KS_KEEP = 2;         // key tiles of a range that stay in registers between maximum and accumulation
+constexpr int KS_WAVES = 8;        // most wavefronts (key ranges) per workgroup: what the registers leave room for
+constexpr int KS_MERGERS = 4;      // fewest wavefronts per workgroup: the merge wants more than one
 
 // EXACT: the keys and values are bf16 numbers to begin with (kernel attention without a sequence
 // projection): one term of K and one of V carry everything, the other operand terms are skipped.
 template <int D, bool ELU, bool EXACT>
-__global__ __launch_bounds__(KeyStateMaxWaves<D>::value * 64) void key_state_kernel(KeyStateArgs a) {
+__global__ __launch_bounds__(KS_WAVES * 64) void key_state_kernel(KeyStateArgs a) {
     constexpr int KS = D / 16, TT = D / 32;
+    constexpr int TERMS = EXACT ? 1 : 3;
     extern __shared__ __attribute__((aligned(16))) float ks_lds[];
     using L = KeyStateLds<D>;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
@@ -169,11 +203,11 @@ __global__ __launch_bounds__(KeyStateMaxWaves<D>::value * 64) void key_state_ker
     if (kt1 > KT) kt1 = KT;
     const long plane = (long)a.BH * a.kpad * D;
     const long vplane = (long)a.BH * (a.kpad / 2) * D;
-    const uint32_t* vimg = a.Vimg + (long)bh * (a.kpad / 2) * D;
 
+    if (kr < a.KR) {           // the others only take part in the merge
     // B operand of the first contraction: omega rows of this feature tile
     uint4 wf[KS];
-    if (!ELU) {
+    if constexpr (!ELU) {
         // features past mf (a ragged last tile) take the last real row; their results are replaced below
         const int fr = 32 * ft + l32 < a.mf ? 32 * ft + l32 : a.mf - 1;
         const uint16_t* og = a.omega + (long)(bh % a.H) * a.omega_head_stride + (long)fr * D + 8 * half;
@@ -181,101 +215,65 @@ __global__ __launch_bounds__(KeyStateMaxWaves<D>::value * 64) void key_state_ker
         for (int s = 0; s < KS; ++s) wf[s] = ld16(og + 16 * s);
     }
 
-    // exponents (performer) or features (elu1) of one 32-key tile: lane = feature 32*ft + l32,
-    // element g = key 32*kt + 8*(g/4) + 4*half + g%4
-    auto tile_values = [&](int kt) -> floatx16 {
-        floatx16 e = zero16();
-        if (!ELU) {
+    // What one 32-key tile needs of memory for its exponents (performer) or features (elu1)
+    struct KFrag { uint4 k[ELU ? 1 : TERMS * KS]; float4 n[ELU ? 1 : 4]; float x[ELU ? 16 : 1]; };
+    auto load_k = [&](int kt, KFrag& f) {
+        if constexpr (!ELU) {
             const uint16_t* kg = a.Kimg + (long)bh * a.kpad * D + ((long)kt * KS * 64 + lane) * 8;
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                e = mfma32(ld16(kg + 512 * s), wf[s], e);
-                if constexpr (!EXACT) {
-                    e = mfma32(ld16(kg + plane + 512 * s), wf[s], e);
-                    e = mfma32(ld16(kg + 2 * plane + 512 * s), wf[s], e);
-                }
-            }
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int u = 0; u < TERMS; ++u) f.k[TERMS * s + u] = ld16(kg + u * plane + 512 * s);
             const float* ng = a.nrm + (long)bh * a.kpad + 32 * kt + 4 * half;
 #pragma unroll
+            for (int q = 0; q < 4; ++q) f.n[q] = *(const float4*)(ng + 8 * q);
+        } else {
+#pragma unroll
+            for (int g = 0; g < 16; ++g) {
+                int r = 32 * kt + 8 * (g >> 2) + 4 * half + (g & 3);
+                if (r >= a.k) r = a.k - 1;
+                const long idx = ((long)bh * a.k + r) * D + 32 * ft + l32;
+                f.x[g] = EXACT ? bf16_to_f32(a.Kb[idx]) : a.Kp[idx];
+            }
+        }
+    };
+    // exponents or features of a tile: lane = feature 32*ft + l32, element g = key 32*kt + 8*(g/4) + 4*half + g%4
+    auto tile_values = [&](int kt, const KFrag& f) -> floatx16 {
+        floatx16 e = zero16();
+        if constexpr (!ELU) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int u = 0; u < TERMS; ++u) e = mfma32(f.k[TERMS * s + u], wf[s], e);
+#pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float4 nq = *(const float4*)(ng + 8 * q);
-                e[4 * q] -= nq.x; e[4 * q + 1] -= nq.y; e[4 * q + 2] -= nq.z; e[4 * q + 3] -= nq.w;
+                e[4 * q] -= f.n[q].x; e[4 * q + 1] -= f.n[q].y; e[4 * q + 2] -= f.n[q].z; e[4 * q + 3] -= f.n[q].w;
             }
         } else {
 #pragma unroll
             for (int g = 0; g < 16; ++g) {
                 const int r = 32 * kt + 8 * (g >> 2) + 4 * half + (g & 3);
-                float v = 0.f;                                    // padding keys contribute nothing
-                if (r < a.k) {
-                    const long idx = ((long)bh * a.k + r) * D + 32 * ft + l32;
-                    const float x = EXACT ? bf16_to_f32(a.Kb[idx]) : a.Kp[idx];
-                    v = x > 0.f ? x + 1.f : __expf(x);
-                }
-                e[g] = v;
+                const float v = f.x[g] > 0.f ? f.x[g] + 1.f : __expf(f.x[g]);
+                e[g] = r < a.k ? v : 0.f;                      // padding keys contribute nothing
             }
         }
         return e;
     };
 
     // B operands of the second contraction for one key tile: V' columns 32*tt + l32, key pairs in the
-    // order in which the accumulator hands PhiK^T on.  They are requested a tile ahead, so that the trip
-    // to memory runs under the exponentials of the tile before (one wavefront per SIMD: nobody else
-    // would hide it).
-    struct VFrag { uint4 h[2][TT], l[2][TT]; };
+    // order in which the accumulator hands PhiK^T on
+    struct VFrag { uint4 h[2][TT], l[EXACT ? 1 : 2][TT]; };
     auto load_v = [&](int kt, VFrag& f) {
+        const uint32_t* vb = a.Vimg + (long)bh * (a.kpad / 2) * D + ((long)kt * 2 * TT * 64 + lane) * 4;
 #pragma unroll
-        for (int sp = 0; sp < 2; ++sp) {
-            const uint32_t* vb = vimg + (long)(16 * kt + 8 * sp + 2 * half) * D + l32;
+        for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
-                f.h[sp][tt].x = vb[32 * tt];
-                f.h[sp][tt].y = vb[32 * tt + D];
-                f.h[sp][tt].z = vb[32 * tt + 4 * D];
-                f.h[sp][tt].w = vb[32 * tt + 5 * D];
-                if constexpr (!EXACT) {
-                    f.l[sp][tt].x = vb[vplane + 32 * tt];
-                    f.l[sp][tt].y = vb[vplane + 32 * tt + D];
-                    f.l[sp][tt].z = vb[vplane + 32 * tt + 4 * D];
-                    f.l[sp][tt].w = vb[vplane + 32 * tt + 5 * D];
-                }
+                f.h[sp][tt] = *(const uint4*)(vb + (sp * TT + tt) * 256);
+                if constexpr (!EXACT) f.l[sp][tt] = *(const uint4*)(vb + vplane + (sp * TT + tt) * 256);
             }
-        }
     };
-    // Up to KS_MT tiles per range (what the plan aims for) are evaluated once, all their loads in flight
-    // together, and kept in registers between the maximum and the accumulation; longer ranges are
-    // evaluated twice.
-    const int nt = kt1 - kt0;
-    constexpr int KS_MT = KeyStateKeep<D>::value;
-    constexpr bool V_AHEAD = D <= 64;
-    const bool keep = nt <= KS_MT;
-    floatx16 ev[KS_MT];
-    if (keep) {
-#pragma unroll
-        for (int i = 0; i < KS_MT; ++i)
-            if (i < nt) ev[i] = tile_values(kt0 + i);
-    }
-    VFrag vcur, vnext;
-    load_v(kt0, vcur);
-    float c = 0.f;
-    if (!ELU) {
-        c = -INFINITY;
-        if (keep) {
-#pragma unroll
-            for (int i = 0; i < KS_MT; ++i)
-                if (i < nt) {
-#pragma unroll
-                    for (int g = 0; g < 16; ++g) c = fmaxf(c, ev[i][g]);
-                }
-        } else {
-            for (int kt = kt0; kt < kt1; ++kt) {
-                const floatx16 e = tile_values(kt);
-#pragma unroll
-                for (int g = 0; g < 16; ++g) c = fmaxf(c, e[g]);
-            }
-        }
-        c = half_max(c);
-    }
-
+    float c = 0.f;                                 // stays 0 for elu1
     floatx16 accS[TT];
 #pragma unroll
     for (int t = 0; t < TT; ++t) accS[t] = zero16();
@@ -286,7 +284,7 @@ __global__ __launch_bounds__(KeyStateMaxWaves<D>::value * 64) void key_state_ker
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             float p0 = e[2 * q], p1 = e[2 * q + 1];
-            if (!ELU) {
+            if constexpr (!ELU) {
                 p0 = fast_exp2((p0 - c) * LOG2E);
                 p1 = fast_exp2((p1 - c) * LOG2E);
             }
@@ -305,37 +303,67 @@ __global__ __launch_bounds__(KeyStateMaxWaves<D>::value * 64) void key_state_ker
                 if constexpr (!EXACT) accS[tt] = mfma32(ah[sp], f.l[sp][tt], accS[tt]);
             }
     };
-    {
-        if (keep) {
+    // The registers of head size 128 do not hold the operands of K' and V' at once: the barriers to scheduling
+    // keep the loads of one behind the products of the other there.
+    constexpr bool V_EARLY = D <= 64;
+    auto behind = [&]() { if constexpr (!V_EARLY) __builtin_amdgcn_sched_barrier(0); };
+    auto raise = [&](const floatx16& e) {
 #pragma unroll
-            for (int i = 0; i < KS_MT; ++i)
-                if (i < nt) {
-                    if constexpr (V_AHEAD) {
-                        if (i + 1 < nt) load_v(kt0 + i + 1, vnext);
-                        accumulate(ev[i], vcur);
-                        if (i + 1 < nt) vcur = vnext;
-                    } else {
-                        if (i > 0) load_v(kt0 + i, vcur);
-                        accumulate(ev[i], vcur);
-                    }
-                }
-        } else {
+        for (int g = 0; g < 16; ++g) c = fmaxf(c, e[g]);
+    };
+    const int nt = kt1 - kt0;
+    if constexpr (!ELU) c = -INFINITY;
+    // Ranges of one or two tiles (what the plan aims for) are evaluated once and kept in registers between
+    // the maximum and the accumulation, their loads in flight together; longer ranges are evaluated twice.
+    if (nt <= KS_KEEP) {
+        floatx16 ev[KS_KEEP];
+        KFrag kf;
+        VFrag vf;
+        load_k(kt0, kf);
+        if constexpr (V_EARLY) load_v(kt0, vf);
+        ev[0] = tile_values(kt0, kf);
+        behind();
+        if (nt > 1) {
+            load_k(kt0 + 1, kf);
+            ev[1] = tile_values(kt0 + 1, kf);
+        }
+        behind();
+        if constexpr (!V_EARLY) load_v(kt0, vf);
+        if constexpr (!ELU) {
+            raise(ev[0]);
+            if (nt > 1) raise(ev[1]);
+            c = half_max(c);
+        }
+        accumulate(ev[0], vf);
+        behind();
+        if (nt > 1) {
+            load_v(kt0 + 1, vf);
+            accumulate(ev[1], vf);
+        }
+    } else {
+        KFrag kf;
+        if constexpr (!ELU) {
             for (int kt = kt0; kt < kt1; ++kt) {
-                if constexpr (V_AHEAD) {
-                    if (kt + 1 < kt1) load_v(kt + 1, vnext);
-                    accumulate(tile_values(kt), vcur);
-                    if (kt + 1 < kt1) vcur = vnext;
-                } else {
-                    if (kt > kt0) load_v(kt, vcur);
-                    accumulate(tile_values(kt), vcur);
-                }
+                load_k(kt, kf);
+                raise(tile_values(kt, kf));
             }
+            c = half_max(c);
+        }
+        for (int kt = kt0; kt < kt1; ++kt) {
+            VFrag vf;
+            load_k(kt, kf);
+            if constexpr (V_EARLY) load_v(kt, vf);
+            const floatx16 e = tile_values(kt, kf);
+            behind();
+            if constexpr (!V_EARLY) load_v(kt, vf);
+            accumulate(e, vf);
+            behind();
         }
     }
     zsum = half_sum(zsum);
 
     // this range's partial results into LDS: S tile [feature][t], then z[32], c[32]
-    float* const mine = ks_lds + kr * L::range_floats();
+    float* const mine = ks_lds + kr * L::range_floats;
     if (half == 0) {
         mine[32 * L::s_pitch + l32] = zsum;
         mine[32 * L::s_pitch + 32 + l32] = c;
@@ -347,45 +375,43 @@ __global__ __launch_bounds__(KeyStateMaxWaves<D>::value * 64) void key_state_ker
             const int f = 8 * (g >> 2) + 4 * half + (g & 3);
             mine[f * L::s_pitch + 32 * tt + l32] = accS[tt][g];
         }
+    }
     __syncthreads();
 
-    // Merge of the key ranges, by the whole workgroup:
+    // Merge of the key ranges, by the whole workgroup, thread = (feature, 4 coordinates):
     //   c_j = max_r c_jr,  S_j = sum_r exp(c_jr - c_j) S_jr,  z_j likewise
     //   St (d x mf) bf16: St[t][slot] = S[feature(slot)][t];  zp: z in accumulator order of a tile
     // For the random-feature map the query stream works with p'_ij = p_ij z_j, so that its denominator
     // is the plain sum of p': St holds S_j / z_j, and cw the exponent shift c_j + ln z_j as three bf16
     // terms (it enters the query kernel's first contraction as extra reduction slots against ones).
     // The slot -> feature order inside each group of 16 is the order in which the first MFMA of the
-    // query-stream kernel hands P^T on as the B operand of the second:
-    //   slot 16*q + 8*h + e  <->  feature 16*q + 8*(e/4) + 4*h + e%4          (natural order for elu1)
+    // query-stream kernel hands P^T on as the B operand of the second (slot_of_feature_tile; natural for elu1).
     const int KR = a.KR, tid = threadIdx.x, nthreads = blockDim.x;
-    float* const wgt = ks_lds + KR * L::range_floats();      // [range][feature]
-    float* const zinv = wgt + KR * 32;
-    float* const tile = zinv + 32;                           // [32][33]
+    const int fl = tid & 31, f = 32 * ft + fl;
+    const bool real = f < a.mf;                  // a feature of the padding: weight exp(-1e30) = 0 in the query stream
+    const float* const pz = ks_lds + 32 * L::s_pitch + fl;      // + range: z, + 32: c
+    float w[KS_WAVES], cm = -INFINITY, zs = 0.f;
+#pragma unroll
+    for (int r = 0; r < KS_WAVES; ++r) {
+        w[r] = pz[(r < KR ? r : 0) * L::range_floats + 32];
+        cm = fmaxf(cm, w[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < KS_WAVES; ++r) {
+        const float zr = pz[(r < KR ? r : 0) * L::range_floats];
+        w[r] = r >= KR ? 0.f : ELU ? 1.f : expf(w[r] - cm);
+        if (r < KR) zs = fmaf(w[r], zr, zs);
+    }
     if (tid < 32) {
-        const int f = 32 * ft + tid;
-        float cm = -INFINITY;
-        for (int r = 0; r < KR; ++r) cm = fmaxf(cm, ks_lds[r * L::range_floats() + 32 * L::s_pitch + 32 + tid]);
-        float zs = 0.f;
-        for (int r = 0; r < KR; ++r) {
-            const float* pr = ks_lds + r * L::range_floats() + 32 * L::s_pitch;
-            const float wr = ELU ? 1.f : expf(pr[32 + tid] - cm);
-            wgt[r * 32 + tid] = wr;
-            zs = fmaf(wr, pr[tid], zs);
-        }
-        const bool real = f < a.mf;              // a feature of the padding: weight exp(-1e30) = 0 in the query stream
         if (real) {
             a.z[(long)bh * a.mf + f] = zs;
             a.c[(long)bh * a.mf + f] = cm;
         }
         // accumulator order of a 32-feature tile: position 16*h + g <-> feature 8*(g/4) + 4*h + g%4
         int pos = tid;
-        if (!ELU) {
-            const int q = tid >> 3, h = (tid >> 2) & 1, e = tid & 3;
-            pos = 16 * h + 4 * q + e;
-        }
+        if constexpr (!ELU) pos = 16 * ((tid >> 2) & 1) + 4 * (tid >> 3) + (tid & 3);
         a.zp[(long)bh * a.mfp + 32 * ft + pos] = zs;
-        if (!ELU) {
+        if constexpr (!ELU) {
             uint16_t hi, mid, lo;
             split3(real ? cm + logf(zs) : -1e30f, hi, mid, lo);
             uint2 pk;
@@ -393,29 +419,24 @@ __global__ __launch_bounds__(KeyStateMaxWaves<D>::value * 64) void key_state_ker
             pk.y = (uint32_t)lo;
             *(uint2*)(a.cw + ((long)bh * a.mfp + f) * 4) = pk;
         }
-        zinv[tid] = ELU ? 1.f : (real ? 1.f / zs : 0.f);
     }
-    __syncthreads();
-    for (int t0 = 0; t0 < D; t0 += 32) {
-        for (int i = tid; i < 32 * 32; i += nthreads) {
-            const int fl = i / 32, t = t0 + i % 32;
-            float sv = 0.f;
-            for (int r = 0; r < KR; ++r)
-                sv = fmaf(wgt[r * 32 + fl], ks_lds[r * L::range_floats() + fl * L::s_pitch + t], sv);
-            if (32 * ft + fl < a.mf) a.S[((long)bh * a.mf + 32 * ft + fl) * D + t] = sv;
-            tile[fl * 33 + i % 32] = sv;
+    const float zinv = ELU ? 1.f : (real ? 1.f / zs : 0.f);
+    uint16_t* const st = a.St + (long)bh * D * a.mfp + 32 * ft + (ELU ? fl : slot_of_feature_tile(fl));
+    for (int t = 4 * (tid >> 5); t < D; t += nthreads / 8) {
+        float4 sv = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < KS_WAVES; ++r) {
+            if (r >= KR) break;
+            const float4 x = *(const float4*)(ks_lds + r * L::range_floats + fl * L::s_pitch + t);
+            sv.x = fmaf(w[r], x.x, sv.x); sv.y = fmaf(w[r], x.y, sv.y);
+            sv.z = fmaf(w[r], x.z, sv.z); sv.w = fmaf(w[r], x.w, sv.w);
         }
-        __syncthreads();
-        for (int i = tid; i < 32 * 32; i += nthreads) {
-            const int tl = i / 32, sl = i % 32;
-            int fl = sl;
-            if (!ELU) {
-                const int e = sl & 7, h = (sl >> 3) & 1;
-                fl = (sl & 16) + 8 * (e >> 2) + 4 * h + (e & 3);
-            }
-            a.St[((long)bh * D + t0 + tl) * a.mfp + 32 * ft + sl] = f32_to_bf16(tile[fl * 33 + tl] * zinv[fl]);
-        }
-        __syncthreads();
+        if (real) *(float4*)(a.S + ((long)bh * a.mf + f) * D + t) = sv;
+        const uint32_t p0 = pack_bf16(sv.x * zinv, sv.y * zinv), p1 = pack_bf16(sv.z * zinv, sv.w * zinv);
+        st[(long)t * a.mfp] = (uint16_t)p0;
+        st[(long)(t + 1) * a.mfp] = (uint16_t)(p0 >> 16);
+        st[(long)(t + 2) * a.mfp] = (uint16_t)p1;
+        st[(long)(t + 3) * a.mfp] = (uint16_t)(p1 >> 16);
     }
 }
 
@@ -427,15 +448,11 @@ KeyStatePlan key_state_plan(const Problem& p) {
     q.kpad = (p.k + 31) / 32 * 32;
     q.FT = p.mfp / 32;
     const int KT = q.kpad / 32;
-    // Key ranges = wavefronts of a workgroup: about two key tiles per wavefront (measured best at the
-    // benchmark shapes: fewer wavefronts leave the latency of the operand loads exposed, more of them
-    // make the merge longer), at most KeyStateMaxWaves (the ranges' partial tiles meet in LDS).  Ranges
-    // of more than KeyStateKeep tiles are evaluated twice (maximum, then accumulation).
-    const int max_kr = p.d <= 64 ? KeyStateMaxWaves<64>::value : KeyStateMaxWaves<128>::value;
-    const int want = (KT + 1) / 2;
-    int KR = 1;
-    while (KR < want && KR < max_kr) KR *= 2;
-    while (KR > KT && KR > 1) KR /= 2;
+    // Key ranges = wavefronts of a workgroup, at most KS_WAVES (the ranges' partial tiles meet in LDS): one key tile
+    // each while the chip holds them all at once (two wavefronts per SIMD), two each otherwise.  Ranges of more than
+    // KS_KEEP tiles are evaluated twice (maximum, then accumulation).
+    int KR = KT < KS_WAVES ? KT : KS_WAVES;
+    if ((long)p.BH * q.FT * KR > 8L * chip_cus() && KR > (KT + 1) / 2) KR = (KT + 1) / 2;
     q.tiles_per_range = (KT + KR - 1) / KR;
     q.KR = (KT + q.tiles_per_range - 1) / q.tiles_per_range;
     return q;
@@ -445,9 +462,10 @@ template <int D, bool ELU, bool EXACT>
 static flurka_status launch_key_state_impl(const Problem& p, const KeyStateArgs& ka, hipStream_t s) {
     auto kern = key_state_kernel<D, ELU, EXACT>;
     const int ldsb = KeyStateLds<D>::total(ka.KR);
+    const int waves = ka.KR < KS_MERGERS ? KS_MERGERS : ka.KR;
     KernelFacts facts;
-    if (!kernel_facts((const void*)kern, ka.KR * 64, ldsb, &facts)) return FLURKA_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((p.BH + 7) / 8 * 8 * ka.FT)), dim3(ka.KR * 64), ldsb, s, ka);
+    if (!kernel_facts((const void*)kern, waves * 64, ldsb, &facts)) return FLURKA_ERR_LAUNCH;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((p.BH + 7) / 8 * 8 * ka.FT)), dim3(waves * 64), ldsb, s, ka);
     FLURKA_CHECK_LAUNCH();
     return FLURKA_OK;
 }
@@ -524,14 +542,12 @@ __global__ __launch_bounds__(256) void identity_pack_kernel(const uint16_t* K, c
             sq[e] = fmaf(x, x, sq[e]);
             const int r = r0 + e;
             if (Kimg) {
-                const long io = (long)bh * n * d +
-                                ((((long)(r >> 5) * (d / 16) + (t >> 4)) * 2 + ((t >> 3) & 1)) * 32 + (r & 31)) * 8 + (t & 7);
-                Kimg[io] = kv[e];
+                Kimg[(long)bh * n * d + k_image_offset(r, t, d)] = kv[e];
             }
         }
 #pragma unroll
         for (int pr = 0; pr < 2; ++pr)
-            Vimg[((long)bh * (n / 2) + r0 / 2 + pr) * d + t] = (uint32_t)vv[2 * pr] | ((uint32_t)vv[2 * pr + 1] << 16);
+            Vimg[(long)bh * (n / 2) * d + v_image_offset(r0 / 2 + pr, t, d)] = (uint32_t)vv[2 * pr] | ((uint32_t)vv[2 * pr + 1] << 16);
     }
     if (nrm) {
 #pragma unroll
