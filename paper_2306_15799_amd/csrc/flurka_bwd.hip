@@ -32,6 +32,9 @@
 // leaves the small key side to the generic kernels.
 #include "flurka_fast.h"
 #include "flurka_gemm.h"
+#include "flurka_gemm_tile.h"
+
+#include <string.h>
 
 namespace flurka {
 
@@ -1141,6 +1144,32 @@ __global__ __launch_bounds__(256) void sum_splits_bf16_kernel(SumSplitsArgs a) {
         if (r0 + e < a.k) *(uint32_t*)(o + (long)e * a.n) = pack_bf16(v0[e], v1[e]);
 }
 
+// The same from the partials of the 128 x 128 tiles, whose rows are positions and whose columns are slots.  One
+// wavefront = 32 positions of 16 slots, lane = (slot, 8 positions: two 16-byte elements a lane half apart): reads of
+// 256 consecutive bytes, writes of 64 to each row of dE.
+__global__ __launch_bounds__(256) void sum_splits_fine_kernel(SumSplitsArgs a) {
+    const int lane = threadIdx.x & 63;
+    const long wid = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int slot_groups = (a.k + 15) / 16;
+    const int c = 16 * (int)(wid % slot_groups) + (lane & 15), r = 32 * (int)(wid / slot_groups) + 8 * (lane >> 4);
+    if (r >= a.n || c >= a.k) return;
+    const PartialTile tile = {128, 128, 64, 64};
+    const int which = blockIdx.y;
+    const float* const p = a.part + partial_tile_index(which, 0, c / tile.tn, r / tile.tm, a.splits, a.tilesN, a.tilesM) * (tile.tm * tile.tn) +
+                           partial_elem_offset(tile, r % tile.tm, c % tile.tn);
+    const long stride = (long)a.tilesN * a.tilesM * (tile.tm * tile.tn);
+    struct Rows { float4 lo, hi; };
+    float4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    for_parts<4, Rows>(
+        a.splits, [&](int s) { return Rows{*(const float4*)(p + s * stride), *(const float4*)(p + s * stride + 128)}; },
+        [&](const Rows& x) {
+            s0.x += x.lo.x; s0.y += x.lo.y; s0.z += x.lo.z; s0.w += x.lo.w;
+            s1.x += x.hi.x; s1.y += x.hi.y; s1.z += x.hi.z; s1.w += x.hi.w;
+        });
+    *(uint4*)(a.dst[which] + (long)c * a.n + r) =
+        make_uint4(pack_bf16(s0.x, s0.y), pack_bf16(s0.z, s0.w), pack_bf16(s1.x, s1.y), pack_bf16(s1.z, s1.w));
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -1168,46 +1197,71 @@ bool fast_bwd_supported(const Problem& p) {
 }
 
 struct GradEPlan {
-    int tilesM, tilesN, total_steps, splits, steps_per_split;
+    bool fine;             // 128 x 128 tiles (two workgroups per compute unit) instead of 256 x 256
+    int tilesM, tilesN;    // of the dE/dF GEMM: slots x positions, fine: positions x slots
+    int total_steps, splits, steps_per_split;
     int resident;          // workgroups of the launch dE/dF share with dK/dV
     PairPlan pair;
+    size_t partial_bytes() const {
+        return splits == 1 ? 0 : (size_t)2 * splits * tilesM * tilesN * (fine ? 128 * 128 : G_TILE_ELEMS) * 4;
+    }
 };
 
 // dE/dF (few items with a reduction over all B*H*d/64 steps) share their launch with dK/dV (many items of
 // kp/64 steps).  Unsplit, the long items are the critical path whenever there are fewer of them than
-// compute units (64 at the headline size: 89 us, the short items done after 46); split s ways they
-// finish sooner, their workgroups go on with short items, and a second pass sums the s partial results.
-// The split that the cost model (plan_pair, plus the traffic of the second pass) expects to finish first
-// wins.
-static GradEPlan grad_e_plan(const Problem& p) {
-    GradEPlan q;
-    q.tilesM = (p.k + GBM - 1) / GBM;
-    q.tilesN = (p.n + GBN - 1) / GBN;
-    q.total_steps = p.BH * p.d / GBK;
-    q.resident = chip_cus() / 8 * 8;
-    const int kp = (p.k + 63) / 64 * 64;
-    const int items_b = 8 * ((p.BH * p.d + GBM - 1) / GBM) * ((q.tilesN * 2 + 7) / 8);
-    const int steps_b = kp / GBK;
-    double best = -1.0;
-    for (int want = 1; want <= 8; ++want) {
-        if (want > q.total_steps) break;
-        const int sps = (q.total_steps + want - 1) / want;
-        const int splits = (q.total_steps + sps - 1) / sps;
-        if (splits != want) continue;
-        const int items_a = 8 * q.tilesM * ((splits * q.tilesN * 2 + 7) / 8);
-        double t = 0.0;
-        const PairPlan pl = plan_pair(items_a, sps, items_b, steps_b, q.resident, &t);
-        if (splits > 1) {
+// compute units (64 at the headline size with 256 x 256 tiles: 89 us, the short items done after 46); split s
+// ways they finish sooner, their workgroups go on with short items, and a second pass sums the s partial
+// results.  The tile and the split that the cost model (plan_pair, plus the traffic of the second pass) expects
+// to finish first win.  128 x 128 tiles: 1.15 us per step with two workgroups to a compute unit, 2.0 and 2.2 us
+// for the epilogues.  They take twice the operand traffic, so long reductions on both sides stay with 256 x 256;
+// elsewhere they need no or fewer partial results and fill the chip.  Training steps, 256 x 256 -> this rule:
+// 48 heads of 64, n 8192, k 256: 341 -> 333 us; 16 heads of 128, n 6016, k 300: 218 -> 204;
+// 64 heads of 128, n 65536, k 512 (stays): 1810, with 128 x 128 1905.
+constexpr double T_PAIR_STEP_US = 1.15, T_PAIR_EPILOGUE_E_US = 2.0, T_PAIR_EPILOGUE_X_US = 2.2;
+
+static GradEPlan make_grad_e_plan(const Problem& p) {
+    GradEPlan best{};
+    double best_t = -1.0;
+    const int kp = (p.k + 63) / 64 * 64, steps_b = kp / GBK, rows_b = p.BH * p.d;
+    for (int fine = 0; fine < 2; ++fine) {
+        GradEPlan q{};
+        const int tile = fine ? 128 : GBM;
+        const int slots = (p.k + tile - 1) / tile, positions = (p.n + tile - 1) / tile;
+        q.fine = fine != 0;
+        q.tilesM = fine ? positions : slots;
+        q.tilesN = fine ? slots : positions;
+        q.total_steps = p.BH * p.d / GBK;
+        q.resident = fine ? 2 * chip_cus() / 8 * 8 : chip_cus() / 8 * 8;
+        const int items_b = 8 * ((rows_b + tile - 1) / tile) * ((positions * 2 + 7) / 8);
+        const double tb = fine ? steps_b * T_PAIR_STEP_US + T_PAIR_EPILOGUE_X_US : ((steps_b + 1) & ~1) * G_STEP_US + G_EPILOGUE_T_US;
+        for (int want = 1; want <= (fine ? 32 : 8) && want <= q.total_steps; want += want < 8 ? 1 : 8) {
+            const int sps = (q.total_steps + want - 1) / want;
+            const int splits = (q.total_steps + sps - 1) / sps;
+            if (want <= 8 && splits != want) continue;
+            const int items_a = 8 * slots * ((splits * positions * 2 + 7) / 8);
+            q.splits = splits; q.steps_per_split = sps;
+            double t = 0.0;
+            q.pair = plan_pair(items_a, fine ? sps * T_PAIR_STEP_US + T_PAIR_EPILOGUE_E_US : ((sps + 1) & ~1) * G_STEP_US + G_EPILOGUE_US,
+                               items_b, tb, q.resident, &t);
             // second pass: reads the fp32 partials, writes bf16; about 4 TB/s plus a launch
-            const double bytes = 2.0 * q.tilesM * q.tilesN * G_TILE_ELEMS * 4.0 * splits + 4.0 * p.k * (double)p.n;
-            t += 4.0 + bytes / 4.0e6;
-        }
-        if (best < 0.0 || t < best) {
-            best = t;
-            q.splits = splits; q.steps_per_split = sps; q.pair = pl;
+            if (splits > 1) t += 4.0 + ((double)q.partial_bytes() + 4.0 * p.k * (double)p.n) / 4.0e6;
+            if (best_t < 0.0 || t < best_t) { best_t = t; best = q; }
         }
     }
-    return q;
+    return best;
+}
+
+// The plan depends on sizes alone and a backward call asks for it four times (buffer sizes, layout, launch): the
+// thread's last one is kept.
+static const GradEPlan& grad_e_plan(const Problem& p) {
+    static thread_local int key[5] = {0, 0, 0, 0, 0};
+    static thread_local GradEPlan plan{};
+    const int now[5] = {p.BH, p.n, p.d, p.k, chip_cus()};
+    if (memcmp(key, now, sizeof(now)) != 0) {
+        plan = make_grad_e_plan(p);
+        memcpy(key, now, sizeof(now));
+    }
+    return plan;
 }
 
 struct BwdYPlan { int FT, NW, R, tiles_per_range; };
@@ -1250,7 +1304,7 @@ static FastBwdWs fast_bwd_ws_layout(const Problem& p) {
     W.img = o;    o += round_up(2 * BH * W.kp * p.d * 2, 256);        // dK' then dV'
     W.imgT = o;   o += round_up(2 * BH * W.kp * p.d * 2, 256);
     // tile-ordered dE, dF partials (none when the reduction is not split)
-    W.epart = o;  o += e.splits == 1 ? 0 : round_up((size_t)2 * e.splits * e.tilesM * e.tilesN * G_TILE_ELEMS * 4, 256);
+    W.epart = o;  o += round_up(e.partial_bytes(), 256);
     W.total = o;
     return W;
 }
@@ -1274,7 +1328,7 @@ static EluBwdWs elu_bwd_ws_layout(const Problem& p) {
     W.kp = (p.k + 63) / 64 * 64;
     W.img = o;    o += round_up(2 * BH * W.kp * p.d * 2, 256);
     W.imgT = o;   o += round_up(2 * BH * W.kp * p.d * 2, 256);
-    W.epart = o;  o += e.splits == 1 ? 0 : round_up((size_t)2 * e.splits * e.tilesM * e.tilesN * G_TILE_ELEMS * 4, 256);
+    W.epart = o;  o += round_up(e.partial_bytes(), 256);
     W.total = o;
     return W;
 }
@@ -1320,30 +1374,33 @@ static flurka_status grad_gemms_d(const Problem& p, const BwdArgs& a, const uint
                                   int kp, float* part, hipStream_t s) {
     const size_t img_elems = (size_t)p.BH * kp * p.d;
     const GradEPlan e = grad_e_plan(p);
+    const int tile = e.fine ? 128 : GBM;
     GemmParams gx{};       // dK = E^T dK', dV = F^T dV'
     gx.A[0] = imgT; gx.A[1] = imgT + img_elems;
     gx.B[0] = (const uint16_t*)a.E; gx.B[1] = (const uint16_t*)a.F;
     gx.C[0] = a.dK; gx.C[1] = a.dV;
     gx.n = p.n; gx.d = p.d; gx.k = p.k; gx.BH = p.BH; gx.kp = kp;
-    gx.tilesM = (p.BH * p.d + GBM - 1) / GBM; gx.tilesN = (p.n + GBN - 1) / GBN;
+    gx.tilesM = (p.BH * p.d + tile - 1) / tile; gx.tilesN = (p.n + tile - 1) / tile;
     gx.splits = 1; gx.total_steps = kp / GBK; gx.steps_per_split = gx.total_steps;
-    GemmParams ge{};       // dE = sum_bh dK' K^T, dF = sum_bh dV' V^T
-    ge.A[0] = img; ge.A[1] = img + img_elems;
-    ge.B[0] = (const uint16_t*)a.K; ge.B[1] = (const uint16_t*)a.V;
+    GemmParams ge{};       // dE = sum_bh dK' K^T, dF = sum_bh dV' V^T; fine: transposed, K dK'^T
+    const uint16_t* const images[2] = {img, img + img_elems};
+    const uint16_t* const rows[2] = {(const uint16_t*)a.K, (const uint16_t*)a.V};
+    for (int i = 0; i < 2; ++i) { ge.A[i] = e.fine ? rows[i] : images[i]; ge.B[i] = e.fine ? images[i] : rows[i]; }
     ge.n = p.n; ge.d = p.d; ge.k = p.k; ge.BH = p.BH; ge.kp = kp;
     ge.tilesM = e.tilesM; ge.tilesN = e.tilesN; ge.splits = e.splits;
     ge.total_steps = e.total_steps; ge.steps_per_split = e.steps_per_split;
+    // results leave as bf16 where the reduction is not split
+    ge.C[0] = e.splits == 1 ? a.dE : part; ge.C[1] = e.splits == 1 ? a.dF : nullptr;
     flurka_status st;
     {
         StageScope sc(s, STAGE_K_GRAD_PAIR);
-        if (e.splits == 1) {
-            // enough tiles to fill the chip without splitting the reduction: results leave as bf16
-            ge.C[0] = a.dE; ge.C[1] = a.dF;
-            st = launch_gemm_mfma_pair<GradEPolicy<D, true>, GradXPolicy<D>>(ge, gx, e.pair, e.resident, s);
-        } else {
-            ge.C[0] = part; ge.C[1] = nullptr;
-            st = launch_gemm_mfma_pair<GradEPolicy<D, false>, GradXPolicy<D>>(ge, gx, e.pair, e.resident, s);
-        }
+        typedef TGradXPolicy<D, 128, 128> FineX;
+        if (e.fine)
+            st = e.splits == 1 ? launch_gemm_tile_pair<TGradEPolicy<D, true, 128, 128>, FineX>(ge, gx, e.pair, e.resident, s)
+                               : launch_gemm_tile_pair<TGradEPolicy<D, false, 128, 128>, FineX>(ge, gx, e.pair, e.resident, s);
+        else
+            st = e.splits == 1 ? launch_gemm_mfma_pair<GradEPolicy<D, true>, GradXPolicy<D>>(ge, gx, e.pair, e.resident, s)
+                               : launch_gemm_mfma_pair<GradEPolicy<D, false>, GradXPolicy<D>>(ge, gx, e.pair, e.resident, s);
         if (st != FLURKA_OK) return st;
     }
     if (e.splits > 1) {
@@ -1351,8 +1408,13 @@ static flurka_status grad_gemms_d(const Problem& p, const BwdArgs& a, const uint
         SumSplitsArgs sa{};
         sa.dst[0] = (uint16_t*)a.dE; sa.dst[1] = (uint16_t*)a.dF; sa.part = part;
         sa.k = p.k; sa.n = p.n; sa.splits = e.splits; sa.tilesM = e.tilesM; sa.tilesN = e.tilesN;
-        const long threads = (long)((p.k + 3) / 4) * (p.n / 2);
-        hipLaunchKernelGGL(sum_splits_bf16_kernel, dim3((unsigned)((threads + 255) / 256), 2), dim3(256), 0, s, sa);
+        if (e.fine) {
+            const long waves = (long)(p.n / 32) * ((p.k + 15) / 16);
+            hipLaunchKernelGGL(sum_splits_fine_kernel, dim3((unsigned)((waves + 3) / 4), 2), dim3(256), 0, s, sa);
+        } else {
+            const long threads = (long)((p.k + 3) / 4) * (p.n / 2);
+            hipLaunchKernelGGL(sum_splits_bf16_kernel, dim3((unsigned)((threads + 255) / 256), 2), dim3(256), 0, s, sa);
+        }
         FLURKA_CHECK_LAUNCH();
     }
     return FLURKA_OK;

@@ -362,6 +362,68 @@ struct TTransformPolicy {
     static __device__ __forceinline__ int b_soff(const Ctx& c, int step) { return (step % c.steps_per_term) * (T_BK * 2); }
 };
 
+// dK = E^T dK': rows = (head, t) of the (BH*D x kp) image, columns = positions, reduction = projected slots
+template <int D, int TM_, int TN_>
+struct TGradXPolicy {
+    static constexpr int TM = TM_, TN = TN_, NW = TileShape<TM, TN>::NW;
+    static constexpr bool SHARE_A = false, B_TRANSPOSE = true, PARTIAL_TILES = false, TRANSPOSED_STORE = true, B_ROW_LIMIT = false;
+    struct Ctx : TileCtx {};
+    static __device__ __forceinline__ Ctx make(const GemmParams& g, int which, int m0, int n0, int lane, int wave) {
+        Ctx c;
+        c.rsA = tile_rsrc(g.A[which], (unsigned)(g.BH * D) * (unsigned)g.kp * 2u);
+        c.rsB = tile_rsrc(g.B[which], (unsigned)g.k * (unsigned)g.n * 2u);
+        c.voffA = ((m0 + tile_a_row(lane, wave)) * g.kp + tile_a_elem(lane, wave)) * 2;
+        c.a_js = NW * 16 * g.kp;
+        c.voffB = (tile_b_row(lane, wave, TN) * g.n + n0 + tile_b_col(lane, wave, TN)) * 2;
+        c.b_js = (NW * 512 / TN) * g.n * 2;
+        c.b_step = T_BK * 2 * g.n;
+        return c;
+    }
+    static __device__ __forceinline__ int a_soff(const Ctx&, int step) { return step * (T_BK * 2); }
+    static __device__ __forceinline__ int b_soff(const Ctx& c, int step) { return step * c.b_step; }
+    // rows r0 + 8*k .. + 7 (64 rows from r0 lie inside one head) of column col, as 8 bf16
+    static __device__ __forceinline__ void store_rows(const GemmParams& g, int which, int r0, int col, int k,
+                                                      const uint4& v) {
+        if (col >= g.n || r0 >= g.BH * D) return;
+        const int bh = r0 / D, t = r0 % D + 8 * k;
+        *(uint4*)((uint16_t*)g.C[which] + ((long)bh * g.n + col) * D + t) = v;
+    }
+};
+
+// dE = sum_bh dK' K^T, transposed: rows = positions (A = rows of K), columns = projected slots (B = rows of
+// the (BH, kp, D) image), reduction = (head, t) pairs.  FINAL: not split, bf16 results to dE, dF.
+template <int D, bool FINAL, int TM_, int TN_>
+struct TGradEPolicy {
+    static constexpr int TM = TM_, TN = TN_, NW = TileShape<TM, TN>::NW;
+    static constexpr bool SHARE_A = true, B_TRANSPOSE = false, PARTIAL_TILES = !FINAL, TRANSPOSED_STORE = FINAL, B_ROW_LIMIT = false;
+    struct Ctx : TileCtx { int a_batch, b_batch; };
+    static __device__ __forceinline__ Ctx make(const GemmParams& g, int which, int m0, int n0, int lane, int wave) {
+        Ctx c;
+        c.rsA = tile_rsrc(g.A[which], (unsigned)g.BH * (unsigned)g.n * (unsigned)(D * 2));
+        c.rsB = tile_rsrc(g.B[which], (unsigned)g.BH * (unsigned)g.kp * (unsigned)(D * 2));
+        c.voffA = ((m0 + tile_a_row(lane, wave)) * D + tile_a_elem(lane, wave)) * 2;
+        c.voffB = ((n0 + tile_a_row(lane, wave)) * D + tile_a_elem(lane, wave)) * 2;
+        c.a_js = c.b_js = NW * 8 * D * 2;
+        c.a_batch = g.n * D * 2;
+        c.b_batch = g.kp * D * 2;
+        return c;
+    }
+    static __device__ __forceinline__ int a_soff(const Ctx& c, int step) {
+        constexpr int spb = D / T_BK;
+        return (step / spb) * c.a_batch + (step % spb) * (T_BK * 2);
+    }
+    static __device__ __forceinline__ int b_soff(const Ctx& c, int step) {
+        constexpr int spb = D / T_BK;
+        return (step / spb) * c.b_batch + (step % spb) * (T_BK * 2);
+    }
+    // positions r0 + 8*k .. + 7 of slot col; n is a multiple of 32 here
+    static __device__ __forceinline__ void store_rows(const GemmParams& g, int which, int r0, int col, int k,
+                                                      const uint4& v) {
+        if (col >= g.k || r0 + 8 * k >= g.n) return;
+        *(uint4*)((uint16_t*)g.C[which] + (long)col * g.n + r0 + 8 * k) = v;
+    }
+};
+
 // ids handed to workgroups: the (split, tile along the large operand, which) index padded to a multiple of 8
 template <class Pol>
 __host__ __device__ inline int tile_item_count(const GemmParams& g) {
@@ -373,6 +435,20 @@ template <class Pol, int NST>
 __global__ __launch_bounds__(Pol::NW * 64) void gemm_tile_kernel(GemmParams g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     gemm_tile_body<Pol, NST>(g, (int)blockIdx.x, (int)gridDim.x, lds, 0, tile_item_count<Pol>(g));
+}
+
+// Two GEMMs in one launch (see gemm_mfma_pair_kernel).
+template <class PolA, class PolB, int NST>
+__global__ __launch_bounds__(PolA::NW * 64) void gemm_tile_pair_kernel(GemmParams ga, GemmParams gb, PairPlan pl) {
+    static_assert(PolA::NW == PolB::NW, "one workgroup size");
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int b = (int)blockIdx.x;
+    if (b < pl.blocks_a) {
+        gemm_tile_body<PolA, NST>(ga, b, pl.blocks_a, lds, 0, pl.items_a);
+        if (pl.main_b < pl.items_b) gemm_tile_body<PolB, NST>(gb, b, pl.blocks_a, lds, pl.main_b, pl.items_b);
+    } else {
+        gemm_tile_body<PolB, NST>(gb, b - pl.blocks_a, (int)gridDim.x - pl.blocks_a, lds, 0, pl.main_b);
+    }
 }
 
 // As many workgroups as stay resident; more items than that are streamed.
@@ -387,6 +463,26 @@ static inline flurka_status launch_gemm_tile(const GemmParams& g, hipStream_t s)
     if (grid < items) grid = grid / 8 * 8;
     if (grid < 8) return FLURKA_ERR_LAUNCH;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Pol::NW * 64), ldsb, s, g);
+    if (hipGetLastError() != hipSuccess) return FLURKA_ERR_LAUNCH;
+    return FLURKA_OK;
+}
+
+// Two workgroups of the pair share a compute unit (plan: 2 x compute units): one's products run while the other
+// waits for a step's operands or drains the stores of its epilogue.
+constexpr int T_PAIR_STAGES = 2;
+template <class PolA, class PolB>
+static inline flurka_status launch_gemm_tile_pair(const GemmParams& ga, const GemmParams& gb, const PairPlan& pl, int resident,
+                                                  hipStream_t s) {
+    auto kern = gemm_tile_pair_kernel<PolA, PolB, T_PAIR_STAGES>;
+    constexpr int ldsb = TileShape<PolB::TM, PolB::TN>::lds(T_PAIR_STAGES, true);
+    static_assert(PolA::TM == PolB::TM && PolA::TN == PolB::TN && PolB::TRANSPOSED_STORE, "one LDS size");
+    static_assert(2 * ldsb <= 160 * 1024, "two workgroups per compute unit");
+    KernelFacts facts;
+    if (!kernel_facts((const void*)kern, PolA::NW * 64, ldsb, &facts)) return FLURKA_ERR_LAUNCH;
+    // every workgroup strides over its items: a grid the device does not hold at once is slower, not wrong
+    int blocks_b = resident - pl.blocks_a;
+    if (blocks_b > pl.main_b) blocks_b = pl.main_b;
+    hipLaunchKernelGGL(kern, dim3(pl.blocks_a + blocks_b), dim3(PolA::NW * 64), ldsb, s, ga, gb, pl);
     if (hipGetLastError() != hipSuccess) return FLURKA_ERR_LAUNCH;
     return FLURKA_OK;
 }

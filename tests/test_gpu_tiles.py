@@ -6,7 +6,7 @@ import torch
 
 from paper_2306_15799_amd import binding as fb
 from paper_2306_15799_amd import inputs
-from paper_2306_15799_amd.inputs import Workload, PHI_ELU1
+from paper_2306_15799_amd.inputs import Workload, PHI_ELU1, PHI_PERFORMER
 
 import gpu_util as gu
 
@@ -46,3 +46,17 @@ def test_projected_keys_and_values(shape):
         # no element far off (a wrong row, column or split), by the same walk: its terms have unit variance
         # times that of one product
         assert np.abs(got - ref).max() <= 8 * bar * np.sqrt((ref ** 2).mean())
+
+
+# (B, H, n, d, k, m): position and slot counts around the 128- and 256-wide tiles of the gradient products, the
+# reduction over (head, coordinate) whole, split a few ways and split into many, tiles that cross a head
+GRAD_SHAPES = [(1, 1, 32, 64, 9, 32), (1, 3, 160, 64, 63, 32), (2, 2, 96, 128, 127, 64), (2, 5, 416, 64, 129, 64),
+               (6, 12, 288, 64, 65, 32), (1, 7, 1056, 64, 128, 64), (2, 8, 544, 128, 300, 64), (16, 8, 128, 64, 40, 32),
+               (1, 2, 4128, 64, 256, 64)]
+
+
+@pytest.mark.parametrize("shape", GRAD_SHAPES)
+def test_gradients(shape):
+    B, H, n, d, k, m = shape
+    w = Workload("tiles", B, H, n, d, k, m, "bf16", PHI_PERFORMER, True)
+    print(shape, gu.check_forward_backward(w, seed=5, algo="fast"))
