@@ -1063,13 +1063,19 @@ template <int D>
 struct F32KeyStateLds {
     static constexpr int s_pitch = D + 4;
     static constexpr int range_floats = 32 * s_pitch + 64;       // S tile, z, c
-    static __host__ __device__ int bytes(int KR) { return (KR * range_floats + KR * 32) * 4; }
+    static __host__ __device__ int bytes(int KR) { return KR * range_floats * 4; }
 };
 
 constexpr int F32_KEEP = 2;        // key tiles of a range whose exponents stay in registers
+constexpr int F32_RANGES = 8;      // most key ranges (wavefronts) of a workgroup
+constexpr int F32_MERGERS = 4;     // fewest wavefronts of a workgroup: the merge wants more than one
 
+// Bound by latency: per key tile a chain of D/2 + 16 D/32 matrix instructions (64 cycles each) behind two loads.
+// The first tile's V' is requested before its exponents (head size 64; others as the registers allow, four keys at
+// a time), and the merge is one pass over LDS by the whole workgroup, thread = (feature, 4 coordinates): 64 keys,
+// one head 10.8 -> 7.5 us, 128 keys 12.1 -> 9.8, 187 keys, 48 heads 14.8 -> 13.
 template <int D, bool ELU, bool BF16, bool FULL>
-__global__ __launch_bounds__(512) void f32_key_state_kernel(F32KeyArgs a) {
+__global__ __launch_bounds__(F32_RANGES * 64) void f32_key_state_kernel(F32KeyArgs a) {
     constexpr int TT = D / 32;
     using L = F32KeyStateLds<D>;
     extern __shared__ __attribute__((aligned(16))) float ks[];
@@ -1082,16 +1088,23 @@ __global__ __launch_bounds__(512) void f32_key_state_kernel(F32KeyArgs a) {
     if (kt1 > KT) kt1 = KT;
     const int f = 32 * ft + l32, fr = f < a.mf ? f : a.mf - 1;
 
+    if (kr < a.KR) {           // the others only take part in the merge
     F32Row<D> wf;
     if constexpr (!ELU) wf = load_row<D, BF16, FULL>(a.omega, (bh % a.H) * a.omega_head_stride + (long)fr * a.d, half, a.d);
     // lane = feature, element g = key 32 kt + 8(g/4) + 4 half + g%4: exponents, or elu1's features
     auto tile_values = [&](int kt) -> floatx16 {
         floatx16 e;
         if constexpr (ELU) {
+            float x[16];
 #pragma unroll
             for (int g = 0; g < 16; ++g) {
                 const int r = 32 * kt + 8 * (g >> 2) + 4 * half + (g & 3);
-                e[g] = r < a.k ? f32_elu1(a.Kp[(bh * a.k + r) * a.d + fr]) : 0.f;
+                x[g] = a.Kp[(bh * a.k + (r < a.k ? r : a.k - 1)) * a.d + fr];
+            }
+#pragma unroll
+            for (int g = 0; g < 16; ++g) {
+                const int r = 32 * kt + 8 * (g >> 2) + 4 * half + (g & 3);
+                e[g] = r < a.k ? f32_elu1(x[g]) : 0.f;
             }
         } else {
             const int r = 32 * kt + l32;
@@ -1104,6 +1117,25 @@ __global__ __launch_bounds__(512) void f32_key_state_kernel(F32KeyArgs a) {
         }
         return e;
     };
+    int col[TT];               // columns past d: any value does, nobody reads their sums
+#pragma unroll
+    for (int t = 0; t < TT; ++t) col[t] = 32 * t + l32 < a.d ? 32 * t + l32 : 0;
+    constexpr bool AHEAD = D == 64 && FULL;
+    struct VTile { float x[AHEAD ? 16 : 1][TT]; };
+    auto value = [&](int kt, int g, int t) -> float {
+        const int r = 32 * kt + 8 * (g >> 2) + 4 * half + (g & 3);
+        return a.Vp[(bh * a.k + (r < a.k ? r : a.k - 1)) * a.d + col[t]];
+    };
+    auto load_v = [&](int kt, VTile& v) {
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int g = 0; g < 16; ++g)
+#pragma unroll
+                for (int t = 0; t < TT; ++t) v.x[g][t] = value(kt, g, t);
+        }
+    };
+    VTile vt;
+    load_v(kt0, vt);
     const int nt = kt1 - kt0;
     const bool keep = nt <= F32_KEEP;
     floatx16 ev[F32_KEEP];
@@ -1132,9 +1164,8 @@ __global__ __launch_bounds__(512) void f32_key_state_kernel(F32KeyArgs a) {
         c = half_max(c);
     }
     floatx16 acc[TT];
-    int col[TT];               // columns past d: any value does, nobody reads their sums
 #pragma unroll
-    for (int t = 0; t < TT; ++t) { acc[t] = zero16(); col[t] = 32 * t + l32 < a.d ? 32 * t + l32 : 0; }
+    for (int t = 0; t < TT; ++t) acc[t] = zero16();
     float zsum = 0.f;
     // a range in which every |k'|^2 overflows has no finite exponent: its weights are 0, not exp(-inf + inf)
     const float shift = c == -INFINITY ? 0.f : c;
@@ -1151,13 +1182,14 @@ __global__ __launch_bounds__(512) void f32_key_state_kernel(F32KeyArgs a) {
             zsum += e[g];
             const int r = 32 * kt + 8 * (g >> 2) + 4 * half + (g & 3);
             const bool in = r < a.k;                       // past the end: 0 x 0 (V' may be infinite)
-            const float* v = a.Vp + (bh * a.k + (in ? r : a.k - 1)) * a.d;
 #pragma unroll
             for (int t = 0; t < TT; ++t) {
-                const float x = v[col[t]];
+                float x;
+                if constexpr (AHEAD) x = vt.x[g][t];
+                else                 x = value(kt, g, t);
                 part[t] = mfma_f32(e[g], in ? x : 0.f, part[t]);
             }
-            if ((g & 3) == 3) __builtin_amdgcn_sched_barrier(0);       // bounds the loads in flight (registers)
+            if (!AHEAD && (g & 3) == 3) __builtin_amdgcn_sched_barrier(0);       // bounds the loads in flight (registers)
         }
 #pragma unroll
         for (int t = 0; t < TT; ++t) acc[t] += part[t];
@@ -1165,10 +1197,16 @@ __global__ __launch_bounds__(512) void f32_key_state_kernel(F32KeyArgs a) {
     if (keep) {
 #pragma unroll
         for (int i = 0; i < F32_KEEP; ++i)
-            if (i < nt) accumulate(ev[i], kt0 + i);
+            if (i < nt) {
+                if (i > 0) load_v(kt0 + i, vt);
+                accumulate(ev[i], kt0 + i);
+            }
     } else {
 #pragma unroll 1
-        for (int kt = kt0; kt < kt1; ++kt) accumulate(tile_values(kt), kt);
+        for (int kt = kt0; kt < kt1; ++kt) {
+            if (kt > kt0) load_v(kt, vt);
+            accumulate(tile_values(kt), kt);
+        }
     }
     zsum = half_sum(zsum);
     float* const mine = ks + kr * L::range_floats;
@@ -1180,37 +1218,56 @@ __global__ __launch_bounds__(512) void f32_key_state_kernel(F32KeyArgs a) {
     for (int t = 0; t < TT; ++t)
 #pragma unroll
         for (int g = 0; g < 16; ++g) mine[(8 * (g >> 2) + 4 * half + (g & 3)) * L::s_pitch + 32 * t + l32] = acc[t][g];
-    __syncthreads();
-    // join the ranges: c = max, S and z rescaled
-    float* const wgt = ks + a.KR * L::range_floats;
-    if (tid < 32) {
-        float cm = -INFINITY, zs = 0.f;
-        for (int r = 0; r < a.KR; ++r) cm = fmaxf(cm, ks[r * L::range_floats + 32 * L::s_pitch + 32 + tid]);
-        for (int r = 0; r < a.KR; ++r) {
-            const float* pr = ks + r * L::range_floats + 32 * L::s_pitch;
-            const float w = ELU ? 1.f : expf(pr[32 + tid] - cm);
-            wgt[r * 32 + tid] = w;
-            zs = fmaf(w, pr[tid], zs);
-        }
-        if (32 * ft + tid < a.mf) {
-            a.z[bh * a.mf + 32 * ft + tid] = zs;
-            a.c[bh * a.mf + 32 * ft + tid] = cm;
-        }
     }
     __syncthreads();
-    for (int i = tid; i < 32 * D; i += a.KR * 64) {
-        const int fl = i / D, t = i % D;
-        float s = 0.f;
-        for (int r = 0; r < a.KR; ++r) s = fmaf(wgt[r * 32 + fl], ks[r * L::range_floats + fl * L::s_pitch + t], s);
-        if (32 * ft + fl < a.mf && t < a.d) a.S[(bh * a.mf + 32 * ft + fl) * a.d + t] = s;
+    // join the ranges: c = max, S and z rescaled
+    const int fl = tid & 31, fo = 32 * ft + fl;
+    const float* const pz = ks + 32 * L::s_pitch + fl;       // + range: z, + 32: c
+    float w[F32_RANGES], cm = -INFINITY, zs = 0.f;
+#pragma unroll
+    for (int r = 0; r < F32_RANGES; ++r) {
+        w[r] = pz[(r < a.KR ? r : 0) * L::range_floats + 32];
+        cm = fmaxf(cm, w[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < F32_RANGES; ++r) {
+        const float zr = pz[(r < a.KR ? r : 0) * L::range_floats];
+        w[r] = ELU ? 1.f : expf(w[r] - cm);
+        if (r < a.KR) zs = fmaf(w[r], zr, zs);
+    }
+    if (fo >= a.mf) return;
+    if (tid < 32) {
+        a.z[bh * a.mf + fo] = zs;
+        a.c[bh * a.mf + fo] = cm;
+    }
+    for (int t = 4 * (tid >> 5); t < D; t += (int)blockDim.x / 8) {
+        float4 sv = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < F32_RANGES; ++r) {
+            if (r >= a.KR) break;
+            const float4 x = *(const float4*)(ks + r * L::range_floats + fl * L::s_pitch + t);
+            sv.x = fmaf(w[r], x.x, sv.x); sv.y = fmaf(w[r], x.y, sv.y);
+            sv.z = fmaf(w[r], x.z, sv.z); sv.w = fmaf(w[r], x.w, sv.w);
+        }
+        float* const o = a.S + (bh * a.mf + fo) * a.d + t;
+        if (FULL) {
+            *(float4*)o = sv;
+        } else {
+            if (t < a.d) o[0] = sv.x;
+            if (t + 1 < a.d) o[1] = sv.y;
+            if (t + 2 < a.d) o[2] = sv.z;
+            if (t + 3 < a.d) o[3] = sv.w;
+        }
     }
 }
 
 // Backward, lane = key; the wavefronts take every fourth feature tile and add up through LDS.
 //     dPhi^T = dS V'^T + dz,  dU = dPhi * Phi,  dV' = Phi dS,  dK' = dU omega - rowsum(dU) K'
 //     elu1: dK' = dPhi * phi'(K')
-template <int D, bool ELU, bool BF16, bool FULL>
-__global__ __launch_bounds__(256, D == 64 && ELU ? 2 : 1) void f32_bwd_key_kernel(F32KeyArgs a) {
+// A feature tile is 2 D + 32 D/32 chained matrix instructions of 64 cycles for the performer map, with the loads of
+// dS and omega exposed between them; OCC wavefronts of a SIMD cover for each other.
+template <int D, bool ELU, bool BF16, bool FULL, int OCC>
+__global__ __launch_bounds__(256, OCC) void f32_bwd_key_kernel(F32KeyArgs a) {
     constexpr int TT = D / 32;
     extern __shared__ __attribute__((aligned(16))) float ks[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
@@ -1356,7 +1413,7 @@ flurka_status f32_key_state(const Problem& p, const void* omega, float* ctx, hip
     a.H = p.H; a.k = p.k; a.d = p.d; a.mf = p.mf; a.FT = p.mfp / 32;
     a.omega_head_stride = p.omega_per_head ? (long)p.m * p.d : 0;
     const int KT = (p.k + 31) / 32;
-    a.KR = KT < 8 ? KT : 8;
+    a.KR = KT < F32_RANGES ? KT : F32_RANGES;
     a.tiles_per_range = (KT + a.KR - 1) / a.KR;
     a.KR = (KT + a.tiles_per_range - 1) / a.tiles_per_range;
     const long grid = (long)p.BH * a.FT;
@@ -1364,7 +1421,7 @@ flurka_status f32_key_state(const Problem& p, const void* omega, float* ctx, hip
         constexpr int d = decltype(D)::value;
         const int ldsb = F32KeyStateLds<d>::bytes(a.KR);
         return by_row(p, d, [&](auto E, auto B, auto F) {
-            return launch_lds(f32_key_state_kernel<d, decltype(E)::value, decltype(B)::value, decltype(F)::value>, grid, a.KR * 64, ldsb, a, s);
+            return launch_lds(f32_key_state_kernel<d, decltype(E)::value, decltype(B)::value, decltype(F)::value>, grid, 64 * (a.KR < F32_MERGERS ? F32_MERGERS : a.KR), ldsb, a, s);
         });
     });
 }
@@ -1484,9 +1541,16 @@ flurka_status f32_key_backward(const Problem& p, const BwdArgs& b, const F32BwdW
     const long grid = (long)p.BH * ((p.k + 31) / 32);
     flurka_status st = by_shape(p, [&](auto D, auto) {
         constexpr int d = decltype(D)::value;
-        constexpr int ldsb = 4 * (2 * (d / 32) * 16 * 64 + 32) * 4;
+        constexpr int slot = (2 * (d / 32) * 16 * 64 + 32) * 4;
         return by_row(p, d, [&](auto E, auto B, auto F) {
-            return launch_lds(f32_bwd_key_kernel<d, decltype(E)::value, decltype(B)::value, decltype(F)::value>, grid, 256, ldsb, a, s);
+            constexpr int e = decltype(E)::value, bf = decltype(B)::value, full = decltype(F)::value;
+            if constexpr (d == 64 && !e && full) {
+                // More workgroups than compute units: two to each (16 spilled registers) rather than a second round.
+                // Head size 64, 48 heads, k 187, m 150: 49 -> 36 us; where one round holds them all, k 256, 16 heads,
+                // m 256, 25.5 -> 28 us.
+                if (grid > chip_cus()) return launch_lds(f32_bwd_key_kernel<d, e, bf, full, 2>, grid, 256, 4 * slot, a, s);
+            }
+            return launch_lds(f32_bwd_key_kernel<d, e, bf, full, d == 64 && e ? 2 : 1>, grid, 256, 4 * slot, a, s);
         });
     });
     if (st != FLURKA_OK || !b.dOmega) return st;
