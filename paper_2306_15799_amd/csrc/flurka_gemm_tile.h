@@ -27,7 +27,8 @@ namespace flurka {
 // Descriptor of a byte range, as four scalar registers
 __device__ __forceinline__ u32x4 tile_rsrc(const void* base, unsigned bytes) {
     const unsigned long p = (unsigned long)base;
-    return u32x4{(unsigned)p, (unsigned)(p >> 32) & 0xffffu, bytes, 0x00020000u};
+    return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((int)p), (unsigned)__builtin_amdgcn_readfirstlane((int)(p >> 32)) & 0xffffu,
+                 (unsigned)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
 }
 
 // 16 bytes per lane from a buffer straight into LDS, lane l's at dst + 16 * l; addresses past the descriptor's
@@ -37,6 +38,10 @@ __device__ __forceinline__ u32x4 tile_rsrc(const void* base, unsigned bytes) {
 // is set right before each use, by the compiler too.)  The two scalar additions keep m0's write and its use apart.
 template <int DST>
 __device__ __forceinline__ void lds_dma16(const u32x4& r, unsigned lds_dst, int voff, int soff, int js) {
+    // wave-uniform values all of them; said so for builds that do not find out
+    lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
+    soff = __builtin_amdgcn_readfirstlane(soff);
+    js = __builtin_amdgcn_readfirstlane(js);
     int t;
     asm volatile("s_add_u32 m0, %1, %2\n\ts_add_u32 %0, %3, %4\n\tbuffer_load_dwordx4 %5, %6, %0 offen lds"
                  : "=&s"(t)
