@@ -178,15 +178,29 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-def _check(t: torch.Tensor, name: str, shape, dtype, device):
-    if tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
+def _check(t: torch.Tensor, name: str, shape: tuple, dtype, device):
+    if t.shape == shape and t.dtype == dtype and t.device == device and t.is_cuda and t.is_contiguous():
+        return
+    if tuple(t.shape) != shape:
+        raise ValueError(f"{name}: expected shape {shape}, got {tuple(t.shape)}")
     if t.dtype != dtype:
         raise TypeError(f"{name}: expected dtype {dtype}, got {t.dtype}")
     if t.device != device or not t.is_cuda:
         raise ValueError(f"{name}: must live on {device}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name}: must be contiguous")
+    raise ValueError(f"{name}: must be contiguous")
+
+
+# The current stream's handle as an integer, without a Stream object on the way (1.5 us of a call whose kernels
+# may take 25 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_of(stream, dev) -> int:
+    if stream is not None:
+        return stream
+    if _raw_stream is not None:
+        return _raw_stream(dev.index)
+    return torch.cuda.current_stream(dev).cuda_stream
 
 
 def _shapes(Q, E, omega, phi):
@@ -197,9 +211,9 @@ def _shapes(Q, E, omega, phi):
     if _PHI[phi] == PHI_PERFORMER:
         if omega is None or omega.dim() != 3 or omega.shape[0] not in (1, H):
             raise ValueError("omega must be (H,m,d) or (1,m,d) for the performer map")
-        m = omega.shape[1]
-        per_head = 1 if (omega.shape[0] == H and H > 1) else 0
-        omega_shape = (omega.shape[0], m, d)
+        heads, m, _ = omega.shape
+        per_head = 1 if (heads == H and H > 1) else 0
+        omega_shape = (heads, m, d)
     else:
         m, per_head, omega_shape = d, 0, None
     return B, H, n, d, k, m, per_head, omega_shape
@@ -221,26 +235,28 @@ def flurka_attn_fwd(Q, K, V, E, F, omega, phi="performer", algo="auto", out=None
     B, H, n, d, k, m, per_head, omega_shape = _shapes(Q, E, omega, phi)
     dt, dev = Q.dtype, Q.device
     code = _dtype_code(Q)
-    for t, name in ((Q, "Q"), (K, "K"), (V, "V")):
-        _check(t, name, (B, H, n, d), dt, dev)
-    for t, name in ((E, "E"), (F, "F")):
-        _check(t, name, (k, n), dt, dev)
+    row, ef = (B, H, n, d), (k, n)
+    _check(Q, "Q", row, dt, dev)
+    _check(K, "K", row, dt, dev)
+    _check(V, "V", row, dt, dev)
+    _check(E, "E", ef, dt, dev)
+    _check(F, "F", ef, dt, dev)
     if omega_shape is not None:
         _check(omega, "omega", omega_shape, dt, dev)
     if out is None:
         out = torch.empty_like(Q)
-    _check(out, "out", (B, H, n, d), dt, dev)
+    else:
+        _check(out, "out", (B, H, n, d), dt, dev)
     cb = lib.flurka_ctx_bytes(B, H, n, d, k, m, code, _PHI[phi])
     wb = lib.flurka_workspace_bytes(B, H, n, d, k, m, code, _PHI[phi], PASS_FWD, _ALGO[algo])
     if ctx is None:
         ctx = alloc_buffer(cb, dev)
     if workspace is None:
         workspace = alloc_buffer(wb, dev)
-    s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
-    st = lib.flurka_attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(E), _ptr(F),
-                             _ptr(omega) if omega_shape is not None else None, _ptr(out),
-                             _ptr(ctx), ctx.numel() * ctx.element_size(),
-                             _ptr(workspace), workspace.numel() * workspace.element_size(),
+    s = _stream_of(stream, dev)
+    st = lib.flurka_attn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), E.data_ptr(), F.data_ptr(),
+                             omega.data_ptr() if omega_shape is not None else None, out.data_ptr(),
+                             ctx.data_ptr(), ctx.nbytes, workspace.data_ptr(), workspace.nbytes,
                              B, H, n, d, k, m, per_head, code, _PHI[phi], _ALGO[algo], s)
     if st != OK:
         raise FlurkaError(st, "flurka_attn_fwd")
@@ -272,12 +288,13 @@ def flurka_attn_fwd_fused_w(Q, XK, XV, E, F, WK, WV, omega, phi="performer", out
         _check(omega, "omega", omega_shape, dt, dev)
     if out is None:
         out = torch.empty_like(Q)
-    _check(out, "out", (B, H, n, d), dt, dev)
+    else:
+        _check(out, "out", (B, H, n, d), dt, dev)
     if ctx is None:
         ctx = alloc_buffer(lib.flurka_ctx_bytes(B, H, n, d, k, m, code, _PHI[phi]), dev)
     if workspace is None:
         workspace = alloc_buffer(lib.flurka_fused_w_workspace_bytes(B, H, n, d, k, m, dm, code, _PHI[phi]), dev)
-    s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+    s = _stream_of(stream, dev)
     st = lib.flurka_attn_fwd_fused_w(_ptr(Q), _ptr(XK), _ptr(XV), _ptr(E), _ptr(F), _ptr(WK), _ptr(WV),
                                      _ptr(omega) if omega_shape is not None else None, _ptr(out),
                                      _ptr(ctx), ctx.numel() * ctx.element_size(),
@@ -307,7 +324,7 @@ def flurka_attn_fwd_ex(Q, K, V, E, F, omega, phi="performer", algo="auto", ef_pe
     a = ALGO_GENERIC if ef_per_head else _ALGO[algo]
     ws = alloc_buffer(lib.flurka_workspace_bytes(B, H, n, d, k, m, code, _PHI[phi], PASS_FWD, a), dev)
     opt = FlurkaOptions(1 if ef_per_head else 0, 0, None)
-    s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+    s = _stream_of(stream, dev)
     st = lib.flurka_attn_fwd_ex(_ptr(Q), _ptr(K), _ptr(V), _ptr(E), _ptr(F),
                                 _ptr(omega) if omega_shape is not None else None, _ptr(out),
                                 _ptr(ctx), ctx.numel(), _ptr(ws), ws.numel(),
@@ -337,7 +354,7 @@ def flurka_attn_bwd_ex(Q, K, V, E, F, omega, out, dOut, ctx, phi="performer", al
     a = _ALGO[algo] if plain else ALGO_GENERIC
     ws = alloc_buffer(lib.flurka_workspace_bytes(B, H, n, d, k, m, code, _PHI[phi], PASS_BWD, a), dev)
     opt = FlurkaOptions(1 if ef_per_head else 0, 1 if grad_ef_f32 else 0, _ptr(d_omega))
-    s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+    s = _stream_of(stream, dev)
     st = lib.flurka_attn_bwd_ex(_ptr(Q), _ptr(K), _ptr(V), _ptr(E), _ptr(F),
                                 _ptr(omega) if omega_shape is not None else None, _ptr(out), _ptr(dOut),
                                 _ptr(ctx), ctx.numel(), _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(dE), _ptr(dF),
@@ -381,12 +398,13 @@ def flurka_baseline_fwd(which, Q, K, V, E=None, F=None, omega=None, phi="perform
         omega = None
     if out is None:
         out = torch.empty_like(Q)
-    _check(out, "out", (B, H, n, d), dt, dev)
+    else:
+        _check(out, "out", (B, H, n, d), dt, dev)
     if ctx is None:
         ctx = alloc_buffer(lib.flurka_baseline_ctx_bytes(which, B, H, n, d, k, m, code, _PHI[phi]), dev)
     if workspace is None:
         workspace = alloc_buffer(lib.flurka_baseline_workspace_bytes(which, B, H, n, d, k, m, code, _PHI[phi]), dev)
-    s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+    s = _stream_of(stream, dev)
     st = lib.flurka_baseline_fwd(which, _ptr(Q), _ptr(K), _ptr(V), _ptr(E), _ptr(F), _ptr(omega), _ptr(out),
                                  _ptr(ctx), ctx.numel() * ctx.element_size(),
                                  _ptr(workspace), workspace.numel() * workspace.element_size(),
@@ -412,7 +430,7 @@ def flurka_attn_fwd_static(Q, K, V, E, F, omega, out, ctx, phi="performer", algo
         _check(t, name, (k, n), dt, dev)
     if omega_shape is not None:
         _check(omega, "omega", omega_shape, dt, dev)
-    s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+    s = _stream_of(stream, dev)
     st = lib.flurka_attn_fwd_static(_ptr(Q), _ptr(K), _ptr(V), _ptr(E), _ptr(F),
                                     _ptr(omega) if omega_shape is not None else None, _ptr(out),
                                     _ptr(ctx), ctx.numel() * ctx.element_size(),
@@ -429,29 +447,34 @@ def flurka_attn_bwd(Q, K, V, E, F, omega, out, dOut, ctx, phi="performer", algo=
     B, H, n, d, k, m, per_head, omega_shape = _shapes(Q, E, omega, phi)
     dt, dev = Q.dtype, Q.device
     code = _dtype_code(Q)
-    for t, name in ((Q, "Q"), (K, "K"), (V, "V"), (out, "out"), (dOut, "dOut")):
-        _check(t, name, (B, H, n, d), dt, dev)
-    for t, name in ((E, "E"), (F, "F")):
-        _check(t, name, (k, n), dt, dev)
+    row, ef = (B, H, n, d), (k, n)
+    _check(Q, "Q", row, dt, dev)
+    _check(K, "K", row, dt, dev)
+    _check(V, "V", row, dt, dev)
+    _check(out, "out", row, dt, dev)
+    _check(dOut, "dOut", row, dt, dev)
+    _check(E, "E", ef, dt, dev)
+    _check(F, "F", ef, dt, dev)
     if omega_shape is not None:
         _check(omega, "omega", omega_shape, dt, dev)
     if grads is None:
-        grads = (torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V),
-                 torch.empty_like(E), torch.empty_like(F))
-    dQ, dK, dV, dE, dF = grads
-    for t, name in ((dQ, "dQ"), (dK, "dK"), (dV, "dV")):
-        _check(t, name, (B, H, n, d), dt, dev)
-    for t, name in ((dE, "dE"), (dF, "dF")):
-        _check(t, name, (k, n), dt, dev)
+        dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
+        dE, dF = torch.empty_like(E), torch.empty_like(F)
+    else:
+        dQ, dK, dV, dE, dF = grads
+        for t, name in ((dQ, "dQ"), (dK, "dK"), (dV, "dV")):
+            _check(t, name, row, dt, dev)
+        for t, name in ((dE, "dE"), (dF, "dF")):
+            _check(t, name, ef, dt, dev)
     wb = lib.flurka_workspace_bytes(B, H, n, d, k, m, code, _PHI[phi], PASS_BWD, _ALGO[algo])
     if workspace is None:
         workspace = alloc_buffer(wb, dev)
-    s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
-    st = lib.flurka_attn_bwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(E), _ptr(F),
-                             _ptr(omega) if omega_shape is not None else None, _ptr(out), _ptr(dOut),
-                             _ptr(ctx), ctx.numel() * ctx.element_size(),
-                             _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(dE), _ptr(dF),
-                             _ptr(workspace), workspace.numel() * workspace.element_size(),
+    s = _stream_of(stream, dev)
+    st = lib.flurka_attn_bwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), E.data_ptr(), F.data_ptr(),
+                             omega.data_ptr() if omega_shape is not None else None, out.data_ptr(), dOut.data_ptr(),
+                             ctx.data_ptr(), ctx.nbytes,
+                             dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), dE.data_ptr(), dF.data_ptr(),
+                             workspace.data_ptr(), workspace.nbytes,
                              B, H, n, d, k, m, per_head, code, _PHI[phi], _ALGO[algo], s)
     if st != OK:
         raise FlurkaError(st, "flurka_attn_bwd")
