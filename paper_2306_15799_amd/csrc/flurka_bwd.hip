@@ -28,8 +28,8 @@
 //   bwd_query_y  one wavefront per (head, 32 features, query range), lane = feature: recomputes W with
 //                the renormalised lambda, accumulates dS and dz over its queries; a merge kernel sums ranges
 // then bwd_key (dK', dV' from dS, dz) and the four sequence-length GEMMs of flurka_gemm.h.
-// phi = elu + 1 has dQ and dS kernels of its own (bwd_query_x_elu, the ELU variant of bwd_query_y) and
-// leaves the small key side to the generic kernels.
+// phi = elu + 1 has kernels of its own: bwd_query_elu (dQ, dS, dz in one pass, head size 64) or bwd_query_x_elu and
+// the ELU variant of bwd_query_y (head size 128), and bwd_key_elu.
 #include "flurka_fast.h"
 #include "flurka_gemm.h"
 #include "flurka_gemm_tile.h"
@@ -420,12 +420,11 @@ struct BwdXEluArgs {
 
 template <int D>
 struct BwdXEluLds {
-    static constexpr bool direct = D > 64;
+    static_assert(D > 64, "head size 64 has bwd_query_elu; rows move between memory and registers directly");
     static constexpr int nw = 8;
     static constexpr int sp_pitch = (D + 8) * 2;
     static constexpr int images = 2 * D * sp_pitch + D * 4;              // S hi, S lo, z
-    static constexpr int scratch = direct ? 0 : 32 * D * 2;
-    static constexpr int total = images + nw * scratch + 16;
+    static constexpr int total = images + 16;
 };
 
 __device__ __forceinline__ float elu1_of(float x) { return x > 0.f ? x + 1.f : __expf(x); }
@@ -434,7 +433,6 @@ template <int D>
 __global__ __launch_bounds__(512) void bwd_query_x_elu_kernel(BwdXEluArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     using L = BwdXEluLds<D>;
-    constexpr bool DIRECT = L::direct;
     constexpr int X_NW = L::nw;
     constexpr int KS = D / 16, TT = D / 32;         // TT feature tiles = coordinate tiles
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -442,7 +440,7 @@ __global__ __launch_bounds__(512) void bwd_query_x_elu_kernel(BwdXEluArgs a) {
     unsigned char* lsh = lds;
     unsigned char* lsl = lsh + D * L::sp_pitch;
     float* lz = (float*)(lsl + D * L::sp_pitch);    // z in accumulator order of a 32-feature tile
-    int* const next_tile = (int*)(lds + L::images + X_NW * L::scratch);
+    int* const next_tile = (int*)(lds + L::images);
 
     const long tile_begin = a.total_tiles * blockIdx.x / gridDim.x;
     const long tile_end = a.total_tiles * (blockIdx.x + 1) / gridDim.x;
@@ -481,45 +479,16 @@ __global__ __launch_bounds__(512) void bwd_query_x_elu_kernel(BwdXEluArgs a) {
     if (row_end > a.n) row_end = a.n;
     seg = seg_end;
 
-    constexpr int CPR = D / 8, ROWB = D * 2, LPT = 32 * CPR / 64;
-    unsigned char* const scr = lds + L::images + wave * L::scratch;
-    auto scr_at = [&](int row, int c) -> unsigned char* { return scr + row * ROWB + 16 * (c ^ ((row >> 1) & 7)); };
-    // this lane's row of Q and of dOut in accumulator slot order (see bwd_query_x_kernel for the staging)
+    // this lane's row of Q and of dOut in accumulator slot order
     uint4 qv[KS], gv[KS];
     auto load_tile = [&](int row0) {
-        if constexpr (DIRECT) {
-            const long off = head_off + (long)(row0 + l32) * D + 4 * half;
+        const long off = head_off + (long)(row0 + l32) * D + 4 * half;
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const uint2 q0 = *(const uint2*)(a.Q + off + 16 * s), q1 = *(const uint2*)(a.Q + off + 16 * s + 8);
-                const uint2 g0 = *(const uint2*)(a.G + off + 16 * s), g1 = *(const uint2*)(a.G + off + 16 * s + 8);
-                qv[s] = make_uint4(q0.x, q0.y, q1.x, q1.y);
-                gv[s] = make_uint4(g0.x, g0.y, g1.x, g1.y);
-            }
-        } else {
-            uint4 rq[LPT], rg[LPT];
-            const long off = head_off + (long)row0 * D + 8 * lane;
-#pragma unroll
-            for (int u = 0; u < LPT; ++u) {
-                rq[u] = ld16(a.Q + off + 512 * u);
-                rg[u] = ld16(a.G + off + 512 * u);
-            }
-#pragma unroll
-            for (int u = 0; u < LPT; ++u) *(uint4*)scr_at((64 * u + lane) / CPR, (64 * u + lane) % CPR) = rq[u];
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const uint2 x0 = *(const uint2*)(scr_at(l32, 2 * s) + 8 * half);
-                const uint2 x1 = *(const uint2*)(scr_at(l32, 2 * s + 1) + 8 * half);
-                qv[s] = make_uint4(x0.x, x0.y, x1.x, x1.y);
-            }
-#pragma unroll
-            for (int u = 0; u < LPT; ++u) *(uint4*)scr_at((64 * u + lane) / CPR, (64 * u + lane) % CPR) = rg[u];
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const uint2 x0 = *(const uint2*)(scr_at(l32, 2 * s) + 8 * half);
-                const uint2 x1 = *(const uint2*)(scr_at(l32, 2 * s + 1) + 8 * half);
-                gv[s] = make_uint4(x0.x, x0.y, x1.x, x1.y);
-            }
+        for (int s = 0; s < KS; ++s) {
+            const uint2 q0 = *(const uint2*)(a.Q + off + 16 * s), q1 = *(const uint2*)(a.Q + off + 16 * s + 8);
+            const uint2 g0 = *(const uint2*)(a.G + off + 16 * s), g1 = *(const uint2*)(a.G + off + 16 * s + 8);
+            qv[s] = make_uint4(q0.x, q0.y, q1.x, q1.y);
+            gv[s] = make_uint4(g0.x, g0.y, g1.x, g1.y);
         }
     };
 
@@ -579,18 +548,235 @@ __global__ __launch_bounds__(512) void bwd_query_x_elu_kernel(BwdXEluArgs a) {
                 ev.x = pack_bf16(v[0], v[1]); ev.y = pack_bf16(v[2], v[3]);
                 od.x = pack_bf16(v[4], v[5]); od.y = pack_bf16(v[6], v[7]);
                 const uint4 piece = join_halves(ev, od);
-                if constexpr (DIRECT) *(uint4*)(a.dQ + head_off + (long)qrow * D + 8 * (4 * t + q + half)) = piece;
-                else                  *(uint4*)scr_at(l32, 4 * t + q + half) = piece;
+                *(uint4*)(a.dQ + head_off + (long)qrow * D + 8 * (4 * t + q + half)) = piece;
             }
-        if constexpr (!DIRECT) {
-            uint16_t* ob = a.dQ + head_off + (long)row0 * D + 8 * lane;
-#pragma unroll
-            for (int u = 0; u < LPT; ++u)
-                *(uint4*)(ob + 512 * u) = *(const uint4*)scr_at((64 * u + lane) / CPR, (64 * u + lane) % CPR);
-        }
         row0 = row_next;
     }
     }   // head segments
+}
+
+// ---------------------------------------------------------------------------
+// bwd_query_x and bwd_query_y of phi = elu + 1 in one pass, head size 64: everything dS and dz need of a query row
+// (its weights P_i / D_i and g_i) is there once dQ is, so Q and dOut are read once instead of twice.  The two kernels
+// are bound by that traffic (dQ 402 MB in 87 us, dS 268 MB in 79 at 64 heads, n = 16384; joined 92 us).
+// One workgroup = one (head, query range), wavefront w takes every eighth 32-row tile of it.  The weights of a tile
+// (lane = query) cross LDS to become the A operand (row = feature) of dS += W^T dOut, dOut comes out of its own tile
+// through transposing reads; each wavefront keeps a 64 x 64 sum in registers, the eight meet in LDS at the end.
+// (Head size 128 would need 256 registers for that sum and keeps the two kernels.)
+// ---------------------------------------------------------------------------
+struct BwdEluArgs {
+    const uint16_t* Q;
+    const uint16_t* G;         // dOut
+    const float* S;            // ctx (BH, 64, 64): S[j][t]
+    const float* z;            // ctx (BH, 64)
+    uint16_t* dQ;
+    float* dSpart;             // (BH, R, 64, 64)
+    float* dzpart;             // (BH, R, 64)
+    int n, R, tiles_per_range;
+};
+
+struct BwdEluLds {
+    static constexpr int D = 64, nw = 8, tile = 32 * D * 2;
+    static constexpr int sp_pitch = (D + 8) * 2;
+    static constexpr int images = 2 * D * sp_pitch + D * 4;              // S hi, S lo, z
+    static constexpr int wave = 4 * tile + 128;                          // two buffers of Q (then dQ, then W) and dOut tiles, g
+    static constexpr int sums = nw * (D * D + D) * 4;
+    static constexpr int work = images + nw * wave;
+    static constexpr int total = work > sums ? work : sums;
+};
+
+__global__ __launch_bounds__(512) void bwd_query_elu_kernel(BwdEluArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    using L = BwdEluLds;
+    constexpr int D = L::D, KS = D / 16, TT = D / 32, CPR = D / 8, LPT = 32 * CPR / 64, NW = L::nw;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int half = lane >> 5, l32 = lane & 31;
+    const int r = (int)(blockIdx.x % a.R);
+    const long bh = blockIdx.x / a.R;
+    unsigned char* const lsh = lds;
+    unsigned char* const lsl = lsh + D * L::sp_pitch;
+    float* const lz = (float*)(lsl + D * L::sp_pitch);      // z in accumulator order of a 32-feature tile
+    unsigned char* const mytiles = lds + L::images + __builtin_amdgcn_readfirstlane(wave) * L::wave;
+    float* const lg = (float*)(mytiles + 4 * L::tile);      // g of the tile's rows
+    // chunk c of row r sits at chunk position c ^ ((r >> 1) & 7)
+    auto at = [&](unsigned char* t, int row, int c) -> unsigned char* { return t + row * 128 + 16 * (c ^ ((row >> 1) & 7)); };
+
+    const int QTn = a.n / 32;
+    const int t0 = r * a.tiles_per_range + wave;
+    int t1 = (r + 1) * a.tiles_per_range;
+    if (t1 > QTn) t1 = QTn;
+    const long head_off = bh * a.n * D;
+    // A tile goes from memory straight into LDS, the next one's while this one is worked on (staged through
+    // registers it cost 32 of them, and the spills' loads wait for every request in flight).  Transfer u: rows 8u .. + 7.
+    const u32x4 rsQ = tile_rsrc(a.Q + head_off, (unsigned)a.n * (D * 2)), rsG = tile_rsrc(a.G + head_off, (unsigned)a.n * (D * 2));
+    const int voff = (lane >> 3) * 128 + 16 * ((lane & 7) ^ (lane >> 4));
+    const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) unsigned char*)mytiles;
+    auto request = [&](int qtile, int buf) {
+        const unsigned dst = lds0 + buf * (2 * L::tile);
+        unroll<LPT>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            const int v = (u & 1) ? voff ^ 64 : voff;
+            lds_dma16<1024 * u>(rsQ, dst, v, qtile * L::tile, 1024 * u);
+            lds_dma16<L::tile + 1024 * u>(rsG, dst, v, qtile * L::tile, 1024 * u);
+        });
+    };
+    if (t0 < t1) request(t0, 0);
+    {
+        const float* Sg = a.S + bh * D * D;
+        const int row = tid >> 3, q = tid & 7;              // 512 threads = 64 rows x 8 chunks
+        const int s0 = 16 * (q >> 1) + 4 * (q & 1);
+        const float4 x = *(const float4*)(Sg + row * D + s0), y = *(const float4*)(Sg + row * D + s0 + 8);
+        uint4 hi, lo;
+        split2_pair(x.x, x.y, hi.x, lo.x); split2_pair(x.z, x.w, hi.y, lo.y);
+        split2_pair(y.x, y.y, hi.z, lo.z); split2_pair(y.z, y.w, hi.w, lo.w);
+        *(uint4*)(lsh + row * L::sp_pitch + 16 * q) = hi;
+        *(uint4*)(lsl + row * L::sp_pitch + 16 * q) = lo;
+        if (tid < D) {
+            const int g = tid & 15, h = (tid >> 4) & 1;
+            lz[tid] = a.z[bh * D + (tid & ~31) + 8 * (g >> 2) + 4 * h + (g & 3)];
+        }
+    }
+    __syncthreads();
+
+    floatx16 accS[TT][TT];
+    float dz[TT];
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+        dz[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < TT; ++j) accS[i][j] = zero16();
+    }
+    // transposing reads: row 4*half + s16/4 (+ 8 for the second) of a 16-row group, 8 bytes of a 32-column group
+    const int s16 = lane & 15, r4 = s16 >> 2;
+    const int tr_row = (4 * half + r4) * 128 + 8 * (s16 & 1);
+    const int tr_c = 2 * ((lane >> 4) & 1) + ((s16 >> 1) & 1), tr_x = 2 * half + (r4 >> 1);
+    auto columns = [&](const unsigned char* t, int sp, int tt) -> uint4 {
+        const int c = 4 * tt + tr_c;
+        const uint2 b0 = lds_read_tr16(t + 2048 * sp + tr_row + 16 * (c ^ tr_x));
+        const uint2 b1 = lds_read_tr16(t + 2048 * sp + 1024 + tr_row + 16 * (c ^ (tr_x | 4)));
+        return make_uint4(b0.x, b0.y, b1.x, b1.y);
+    };
+    int buf = 0;
+    for (int qtile = t0; qtile < t1; qtile += NW, buf ^= 1) {
+        unsigned char* const qt = mytiles + buf * (2 * L::tile);
+        unsigned char* const gt = qt + L::tile;
+        // this wavefront's transfers are its own: no barrier.  Everything it read of the other buffer has been used.
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        if (qtile + NW < t1) request(qtile + NW, buf ^ 1);
+        // this lane's rows in accumulator slot order
+        uint4 qv[KS], gv[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const uint2 x0 = *(const uint2*)(at(qt, l32, 2 * s) + 8 * half), x1 = *(const uint2*)(at(qt, l32, 2 * s + 1) + 8 * half);
+            const uint2 y0 = *(const uint2*)(at(gt, l32, 2 * s) + 8 * half), y1 = *(const uint2*)(at(gt, l32, 2 * s + 1) + 8 * half);
+            qv[s] = make_uint4(x0.x, x0.y, x1.x, x1.y);
+            gv[s] = make_uint4(y0.x, y0.y, y1.x, y1.y);
+        }
+        floatx16 tp[TT];
+#pragma unroll
+        for (int ft = 0; ft < TT; ++ft) {
+            tp[ft] = zero16();
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const int so = (32 * ft + l32) * L::sp_pitch + 32 * s + 16 * half;
+                tp[ft] = mfma32(*(const uint4*)(lsh + so), gv[s], tp[ft]);
+                tp[ft] = mfma32(*(const uint4*)(lsl + so), gv[s], tp[ft]);
+            }
+        }
+        auto q_of = [&](int ft, int g) -> float {           // element g of tile ft is slot g % 8 of step 2*ft + g / 8
+            const uint4& w4 = qv[2 * ft + (g >> 3)];
+            const uint32_t w = (g & 7) < 2 ? w4.x : (g & 7) < 4 ? w4.y : (g & 7) < 6 ? w4.z : w4.w;
+            return (g & 1) ? pair_hi(w) : pair_lo(w);
+        };
+        float p[TT][16];
+        float dsum = 0.f, gsum = 0.f;
+#pragma unroll
+        for (int ft = 0; ft < TT; ++ft)
+#pragma unroll
+            for (int g = 0; g < 16; ++g) {
+                p[ft][g] = elu1_of(q_of(ft, g));
+                dsum = fmaf(p[ft][g], lz[32 * ft + 16 * half + g], dsum);
+                gsum = fmaf(p[ft][g], tp[ft][g], gsum);
+            }
+        dsum = half_sum(dsum);
+        gsum = half_sum(gsum);
+        const float inv = 1.f / dsum;
+        const float gi = gsum * inv;
+        if (half == 0) lg[l32] = gi;
+        // dQ through the Q tile's area, whole chunks to memory
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int g = 4 * q + e;
+                    v[e] = (tp[t][g] - gi * lz[32 * t + 16 * half + g]) * inv * (q_of(t, g) > 0.f ? 1.f : p[t][g]);
+                }
+                uint2 ev, od;
+                ev.x = pack_bf16(v[0], v[1]); ev.y = pack_bf16(v[2], v[3]);
+                od.x = pack_bf16(v[4], v[5]); od.y = pack_bf16(v[6], v[7]);
+                *(uint4*)at(qt, l32, 4 * t + q + half) = join_halves(ev, od);
+            }
+        uint16_t* ob = a.dQ + head_off + (long)qtile * (32 * D) + 8 * lane;
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) *(uint4*)(ob + 512 * u) = *(const uint4*)at(qt, (64 * u + lane) / CPR, (64 * u + lane) % CPR);
+        // the tile's weights, rounded once, as [query][feature]
+#pragma unroll
+        for (int ft = 0; ft < TT; ++ft)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(uint2*)(at(qt, l32, 4 * ft + q) + 8 * half) =
+                    make_uint2(pack_bf16(p[ft][4 * q] * inv, p[ft][4 * q + 1] * inv), pack_bf16(p[ft][4 * q + 2] * inv, p[ft][4 * q + 3] * inv));
+#pragma unroll
+        for (int sp = 0; sp < 2; ++sp) {
+            const uint4 gb[TT] = {columns(gt, sp, 0), columns(gt, sp, 1)};
+            const float4 d0 = *(const float4*)(lg + 16 * sp + 4 * half), d1 = *(const float4*)(lg + 16 * sp + 8 + 4 * half);
+#pragma unroll
+            for (int ft = 0; ft < TT; ++ft) {
+                const uint4 wa = columns(qt, sp, ft);
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) accS[ft][tt] = mfma32(wa, gb[tt], accS[ft][tt]);
+                // dz from the rounded weights, the ones dS is formed with
+                dz[ft] = fmaf(-pair_lo(wa.x), d0.x, dz[ft]); dz[ft] = fmaf(-pair_hi(wa.x), d0.y, dz[ft]);
+                dz[ft] = fmaf(-pair_lo(wa.y), d0.z, dz[ft]); dz[ft] = fmaf(-pair_hi(wa.y), d0.w, dz[ft]);
+                dz[ft] = fmaf(-pair_lo(wa.z), d1.x, dz[ft]); dz[ft] = fmaf(-pair_hi(wa.z), d1.y, dz[ft]);
+                dz[ft] = fmaf(-pair_lo(wa.w), d1.z, dz[ft]); dz[ft] = fmaf(-pair_hi(wa.w), d1.w, dz[ft]);
+            }
+        }
+    }
+    // the wavefronts' sums, added in their order
+    __syncthreads();
+    float* const mine = (float*)lds + wave * (D * D + D);
+#pragma unroll
+    for (int ft = 0; ft < TT; ++ft) {
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+            for (int g = 0; g < 16; ++g)
+                mine[(32 * ft + 8 * (g >> 2) + 4 * half + (g & 3)) * D + 32 * tt + l32] = accS[ft][tt][g];
+        const float z = half_sum(dz[ft]);
+        if (half == 0) mine[D * D + 32 * ft + l32] = z;
+    }
+    __syncthreads();
+    const float* const all = (const float*)lds;
+    float* const ds = a.dSpart + (bh * a.R + r) * D * D;
+    for (int i = 4 * tid; i < D * D; i += 4 * 512) {
+        float4 s = *(const float4*)(all + i);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            const float4 x = *(const float4*)(all + w * (D * D + D) + i);
+            s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+        }
+        *(float4*)(ds + i) = s;
+    }
+    if (tid < D) {
+        float s = all[D * D + tid];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += all[w * (D * D + D) + D * D + tid];
+        a.dzpart[(bh * a.R + r) * D + tid] = s;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1266,9 +1452,29 @@ static const GradEPlan& grad_e_plan(const Problem& p) {
 
 struct BwdYPlan { int FT, NW, R, tiles_per_range; };
 
+// phi = elu + 1 at head size 64: dQ, dS and dz in one kernel, R query ranges per head
+static bool elu_joined(const Problem& p) { return p.elu && p.d == 64; }
+
 static BwdYPlan bwd_y_plan(const Problem& p) {
     BwdYPlan q;
     q.FT = p.mfp / 32;
+    if (elu_joined(p)) {
+        // The fewest ranges that leave at most a tenth of a round of workgroups (one per compute unit) empty, each with
+        // a tile for every wavefront: partial sums cost 33 KiB a range, written and read.
+        const int QT = p.n / 32, cus = chip_cus(), most = (QT + BwdEluLds::nw - 1) / BwdEluLds::nw;
+        int best = 1;
+        double best_fill = 0.0;
+        for (int R = 1; R <= most && R <= cus; ++R) {
+            const long wgs = (long)p.BH * R, rounds = (wgs + cus - 1) / cus;
+            const double fill = (double)wgs / (double)(rounds * cus);
+            if (fill > best_fill + 0.02) { best = R; best_fill = fill; }
+            if (best_fill >= 0.9) break;
+        }
+        q.NW = BwdEluLds::nw;
+        q.tiles_per_range = (QT + best - 1) / best;
+        q.R = (QT + q.tiles_per_range - 1) / q.tiles_per_range;
+        return q;
+    }
     q.NW = q.FT > 4 ? 8 : 4;                      // wavefronts (= feature tiles) per workgroup
     const int QT = p.n / 32;
     const int FG = (q.FT + q.NW - 1) / q.NW;
@@ -1349,7 +1555,7 @@ static flurka_status launch_bwd_y_impl(const BwdYArgs& ya, unsigned grid, hipStr
 static flurka_status launch_bwd_y(const Problem& p, const BwdYArgs& ya, const BwdYPlan& y, hipStream_t s) {
     const unsigned grid = (unsigned)((long)p.BH * y.R * ((y.FT + y.NW - 1) / y.NW));
     if (p.elu) {        // features = the d coordinates: 2 or 4 feature tiles
-        return p.d == 64 ? launch_bwd_y_impl<64, 4, true>(ya, grid, s) : launch_bwd_y_impl<128, 4, true>(ya, grid, s);
+        return launch_bwd_y_impl<128, 4, true>(ya, grid, s);
     }
     if (p.d == 64) return y.NW == 8 ? launch_bwd_y_impl<64, 8, false>(ya, grid, s) : launch_bwd_y_impl<64, 4, false>(ya, grid, s);
     return y.NW == 8 ? launch_bwd_y_impl<128, 8, false>(ya, grid, s) : launch_bwd_y_impl<128, 4, false>(ya, grid, s);
@@ -1610,25 +1816,38 @@ static flurka_status fast_backward_elu(const Problem& p, const BwdArgs& a, hipSt
     unsigned char* wsb = (unsigned char*)a.ws;
     flurka_status st;
     {
-        BwdXEluArgs xa{};
-        xa.Q = (const uint16_t*)a.Q; xa.G = (const uint16_t*)a.dOut;
-        xa.S = a.ctx + L.S; xa.z = a.ctx + L.z;
-        xa.dQ = (uint16_t*)a.dQ; xa.delta = (float*)(wsb + W.delta); xa.dinv = (float*)(wsb + W.dinv);
-        xa.n = p.n; xa.tiles_per_head = (p.n + 31) / 32;
-        xa.total_tiles = (long)p.BH * xa.tiles_per_head;
-        stage_begin(s);
-        st = p.d == 64 ? launch_bwd_x_elu<64>(xa, s) : launch_bwd_x_elu<128>(xa, s);
-        if (st != FLURKA_OK) return st;
-        stage_end(s, STAGE_K_BWD_X);
+        if (elu_joined(p)) {
+            BwdEluArgs ea{};
+            ea.Q = (const uint16_t*)a.Q; ea.G = (const uint16_t*)a.dOut;
+            ea.S = a.ctx + L.S; ea.z = a.ctx + L.z;
+            ea.dQ = (uint16_t*)a.dQ; ea.dSpart = (float*)(wsb + W.dSpart); ea.dzpart = (float*)(wsb + W.dzpart);
+            ea.n = p.n; ea.R = y.R; ea.tiles_per_range = y.tiles_per_range;
+            StageScope sc(s, STAGE_K_BWD_X);
+            KernelFacts facts;
+            if (!kernel_facts((const void*)bwd_query_elu_kernel, 512, BwdEluLds::total, &facts)) return FLURKA_ERR_LAUNCH;
+            hipLaunchKernelGGL(bwd_query_elu_kernel, dim3((unsigned)(p.BH * y.R)), dim3(512), BwdEluLds::total, s, ea);
+            FLURKA_CHECK_LAUNCH();
+        } else {
+            BwdXEluArgs xa{};
+            xa.Q = (const uint16_t*)a.Q; xa.G = (const uint16_t*)a.dOut;
+            xa.S = a.ctx + L.S; xa.z = a.ctx + L.z;
+            xa.dQ = (uint16_t*)a.dQ; xa.delta = (float*)(wsb + W.delta); xa.dinv = (float*)(wsb + W.dinv);
+            xa.n = p.n; xa.tiles_per_head = (p.n + 31) / 32;
+            xa.total_tiles = (long)p.BH * xa.tiles_per_head;
+            stage_begin(s);
+            st = launch_bwd_x_elu<128>(xa, s);
+            if (st != FLURKA_OK) return st;
+            stage_end(s, STAGE_K_BWD_X);
 
-        BwdYArgs ya{};
-        ya.Q = xa.Q; ya.G = xa.G; ya.lse = xa.dinv; ya.delta = xa.delta;
-        ya.dSpart = (float*)(wsb + W.dSpart); ya.dzpart = (float*)(wsb + W.dzpart);
-        ya.BH = p.BH; ya.H = p.H; ya.n = p.n; ya.mf = p.mfp; ya.mr = p.mf; ya.FT = y.FT; ya.R = y.R;
-        ya.tiles_per_range = y.tiles_per_range;
-        stage_begin(s);
-        if ((st = launch_bwd_y(p, ya, y, s)) != FLURKA_OK) return st;
-        stage_end(s, STAGE_K_BWD_Y);
+            BwdYArgs ya{};
+            ya.Q = xa.Q; ya.G = xa.G; ya.lse = xa.dinv; ya.delta = xa.delta;
+            ya.dSpart = (float*)(wsb + W.dSpart); ya.dzpart = (float*)(wsb + W.dzpart);
+            ya.BH = p.BH; ya.H = p.H; ya.n = p.n; ya.mf = p.mfp; ya.mr = p.mf; ya.FT = y.FT; ya.R = y.R;
+            ya.tiles_per_range = y.tiles_per_range;
+            stage_begin(s);
+            if ((st = launch_bwd_y(p, ya, y, s)) != FLURKA_OK) return st;
+            stage_end(s, STAGE_K_BWD_Y);
+        }
 
         stage_begin(s);
         const long mtotal = (long)p.BH * (p.mfp / 2) * p.d;

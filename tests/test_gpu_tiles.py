@@ -60,3 +60,13 @@ def test_gradients(shape):
     B, H, n, d, k, m = shape
     w = Workload("tiles", B, H, n, d, k, m, "bf16", PHI_PERFORMER, True)
     print(shape, gu.check_forward_backward(w, seed=5, algo="fast"))
+
+
+# elu map at head size 64 (dQ, dS and dz in one pass): one query tile, fewer tiles than wavefronts, ranges that leave some
+# wavefronts a tile short, one head over many ranges, more heads than compute units
+@pytest.mark.parametrize("shape", [(1, 1, 32, 64, 16), (1, 3, 288, 64, 40), (2, 5, 1056, 64, 100), (1, 1, 8224, 64, 64),
+                                   (9, 30, 64, 64, 33)])
+def test_elu_gradients(shape):
+    B, H, n, d, k = shape
+    w = Workload("tiles", B, H, n, d, k, d, "bf16", PHI_ELU1, True)
+    print(shape, gu.check_forward_backward(w, seed=6, algo="fast"))
