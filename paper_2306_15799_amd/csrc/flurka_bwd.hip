@@ -1718,14 +1718,14 @@ static flurka_status launch_bwd_x_elu(const BwdXEluArgs& xa, hipStream_t s) {
 // elu1 key side in one kernel (features = the d coordinates, so dS is d x d per head and everything a
 // key needs fits one workgroup): Phi = elu(K') + 1,
 //     dPhi_rj = sum_t V'_rt dS_jt + dz_j,   dK'_rj = dPhi_rj phi'(K'_rj),   dV'_rt = sum_j Phi_rj dS_jt,
-// all in fp32, results written straight as the bf16 operand images of the gradient GEMMs (img
+// on the fp32 matrix instruction, results written straight as the bf16 operand images of the gradient GEMMs (img
 // (BH, kp, d) with zero rows past k, imgT (BH * d, kp); dV' follows dK' in both).  One workgroup per
-// (head, 32 keys); thread = (key, 8 columns).  The work is 4 d^2 flop per key: what matters is that it
-// is one launch.
+// (head, 32 keys); its wavefronts share the 2 d/32 result tiles of 32 keys x 32 columns, d/2 matrix instructions
+// each.  (One thread per key and 8 columns, a multiply-add per LDS read: 30 us at 64 heads, k 256, d 64; now 12.)
 // ---------------------------------------------------------------------------
 template <int D>
 struct BwdKeyEluLds {
-    static constexpr int P = D + 1;                                        // padded row, floats
+    static constexpr int P = D + 4;                                        // row pitch, floats: 16-byte reads down a column of rows
     static constexpr int total = (D * P + 3 * 32 * P + D) * 4;            // dS, K', V', Phi tiles, dz
 };
 
@@ -1734,64 +1734,90 @@ __global__ __launch_bounds__(256) void bwd_key_elu_fused_kernel(const float* Kp,
                                                                 const float* dz, uint16_t* img, uint16_t* imgT,
                                                                 int BH, int k, int kp) {
     extern __shared__ __attribute__((aligned(16))) float elu_key_lds[];
-    constexpr int P = BwdKeyEluLds<D>::P;
+    constexpr int P = BwdKeyEluLds<D>::P, CPR = D / 4, TT = D / 32;
     float* sdS = elu_key_lds;                   // [D][P]: dS[j][t]
-    float* sK = sdS + D * P;           // [32][P]: K' tile, later dK'
-    float* sV = sK + 32 * P;           // [32][P]: V' tile, later dV'
-    float* sPhi = sV + 32 * P;         // [32][P]
-    float* sdz = sPhi + 32 * P;        // [D]
-    const int tid = threadIdx.x;
+    float* sK = sdS + D * P;                    // [32][P]
+    float* sV = sK + 32 * P;                    // [32][P]
+    float* sPhi = sV + 32 * P;                  // [32][P]
+    float* sdz = sPhi + 32 * P;                 // [D]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
     const int KT = kp / 32;
     const int kt = (int)(blockIdx.x % KT);
     const long bh = blockIdx.x / KT;
-    for (int i = tid; i < D * D; i += 256) sdS[(i / D) * P + i % D] = dS[bh * D * D + i];
-    for (int i = tid; i < D; i += 256) sdz[i] = dz[bh * D + i];
-    for (int i = tid; i < 32 * D; i += 256) {
-        const int r = i / D, t = i % D, key = 32 * kt + r;
-        const float kv = key < k ? Kp[(bh * k + key) * D + t] : 0.f;
-        sK[r * P + t] = kv;
-        sV[r * P + t] = key < k ? Vp[(bh * k + key) * D + t] : 0.f;
-        sPhi[r * P + t] = elu1_of(kv);
-    }
-    __syncthreads();
-    const int r = tid >> 3, g = tid & 7;
-    const bool live = 32 * kt + r < k;
-    float rk[D / 8], rv[D / 8];
+    {   // everything requested before the first use
+        constexpr int NS = D * CPR / 256, NK = 32 * CPR / 256;
+        float4 sv[NS], kv[NK], vv[NK];
 #pragma unroll
-    for (int i = 0; i < D / 8; ++i) { rk[i] = sdz[g + 8 * i]; rv[i] = 0.f; }
-    for (int t = 0; t < D; ++t) {
-        const float v = sV[r * P + t], ph = sPhi[r * P + t];
+        for (int u = 0; u < NS; ++u) sv[u] = *(const float4*)(dS + bh * D * D + 4 * (tid + 256 * u));
 #pragma unroll
-        for (int i = 0; i < D / 8; ++i) {
-            rk[i] = fmaf(v, sdS[(g + 8 * i) * P + t], rk[i]);        // dPhi_rc, c = g + 8i
-            rv[i] = fmaf(ph, sdS[t * P + g + 8 * i], rv[i]);         // dV'_rc
+        for (int u = 0; u < NK; ++u) {
+            const int i = tid + 256 * u, key = 32 * kt + i / CPR;
+            const long o = (bh * k + (key < k ? key : k - 1)) * D + 4 * (i % CPR);
+            kv[u] = *(const float4*)(Kp + o);
+            vv[u] = *(const float4*)(Vp + o);
+            if (key >= k) kv[u] = vv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const int i = tid + 256 * u;
+            *(float4*)(sdS + (i / CPR) * P + 4 * (i % CPR)) = sv[u];
+        }
+#pragma unroll
+        for (int u = 0; u < NK; ++u) {
+            const int i = tid + 256 * u, o = (i / CPR) * P + 4 * (i % CPR);
+            *(float4*)(sK + o) = kv[u];
+            *(float4*)(sV + o) = vv[u];
+            *(float4*)(sPhi + o) = make_float4(elu1_of(kv[u].x), elu1_of(kv[u].y), elu1_of(kv[u].z), elu1_of(kv[u].w));
         }
     }
-#pragma unroll
-    for (int i = 0; i < D / 8; ++i) {
-        const float x = sK[r * P + g + 8 * i];
-        rk[i] = live ? rk[i] * (x > 0.f ? 1.f : __expf(x)) : 0.f;
-        rv[i] = live ? rv[i] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < D / 8; ++i) {
-        sK[r * P + g + 8 * i] = rk[i];
-        sV[r * P + g + 8 * i] = rv[i];
-    }
+    if (tid < D) sdz[tid] = dz[bh * D + tid];
     __syncthreads();
     const long per_tensor = (long)BH * kp * D;
-    for (int i = tid; i < 32 * D; i += 256) {             // rows of the images: D consecutive columns
-        const int rr = i / D, c = i % D;
-        const long o = (bh * kp + 32 * kt + rr) * D + c;
-        img[o] = (uint16_t)pack_bf16(sK[rr * P + c], 0.f);
-        img[per_tensor + o] = (uint16_t)pack_bf16(sV[rr * P + c], 0.f);
-    }
-    for (int i = tid; i < 32 * D; i += 256) {             // transposed images: 32 consecutive keys
-        const int c = i / 32, rr = i % 32;
-        const long o = (bh * D + c) * kp + 32 * kt + rr;
-        imgT[o] = (uint16_t)pack_bf16(sK[rr * P + c], 0.f);
-        imgT[per_tensor + o] = (uint16_t)pack_bf16(sV[rr * P + c], 0.f);
+    for (int tile = wave; tile < 2 * TT; tile += 4) {
+        const bool dphi = tile < TT;                     // else dV'
+        const int c = 32 * (dphi ? tile : tile - TT) + l32;
+        // reduction slot order of both operands: lane half h takes 8q + 4h + e
+        floatx16 acc = zero16();
+        const float* const ar = (dphi ? sV : sPhi) + l32 * P + 4 * half;
+#pragma unroll
+        for (int q = 0; q < D / 8; ++q) {
+            const float4 x = *(const float4*)(ar + 8 * q);
+            float4 y;
+            if (dphi) {
+                y = *(const float4*)(sdS + c * P + 8 * q + 4 * half);
+            } else {
+                const float* const col = sdS + (8 * q + 4 * half) * P + c;
+                y = make_float4(col[0], col[P], col[2 * P], col[3 * P]);
+            }
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc, 0, 0, 0);
+        }
+        // lane = column, element g = key 8(g/4) + 4 half + g%4 of the tile
+        uint16_t* const im = img + (dphi ? 0 : per_tensor) + (bh * kp + 32 * kt) * D + c;
+        uint16_t* const it = imgT + (dphi ? 0 : per_tensor) + (bh * D + c) * kp + 32 * kt;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 8 * q + 4 * half + e;
+                v[e] = acc[4 * q + e];
+                if (dphi) {
+                    const float x = sK[r * P + c];
+                    v[e] = (v[e] + sdz[c]) * (x > 0.f ? 1.f : sPhi[r * P + c]);
+                }
+                if (32 * kt + r >= k) v[e] = 0.f;
+            }
+            const uint2 w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            const int r0 = 8 * q + 4 * half;
+            im[(long)r0 * D] = (uint16_t)w.x;
+            im[(long)(r0 + 1) * D] = (uint16_t)(w.x >> 16);
+            im[(long)(r0 + 2) * D] = (uint16_t)w.y;
+            im[(long)(r0 + 3) * D] = (uint16_t)(w.y >> 16);
+            *(uint2*)(it + r0) = w;
+        }
     }
 }
 
