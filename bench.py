@@ -92,7 +92,7 @@ def kernel_model(w, kernel: str):
         fl, by = stage_model(w, "key_state")
         return fl, by, by
     if kernel == "bwd_query_x":
-        fl = (6.0 if perf else 2.0) * n * mf * d * BH
+        fl = (6.0 if perf else 4.0 if d == 64 else 2.0) * n * mf * d * BH      # elu at head size 64: dS as well
         alg = es * 3 * BH * n * d                    # Q, dOut in; dQ out
         return fl, alg, alg + 12 * BH * n + state    # lse in, g and the renormalised lse out, S/z/c
     if kernel == "bwd_query_y":

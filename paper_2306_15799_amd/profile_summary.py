@@ -28,7 +28,9 @@ ROOT = os.path.dirname(PKG_DIR)
 # kernel name in a rocprofv3 trace (template arguments vary) -> name the library's stage timer uses
 TIMER_NAME_RULES = [
     ("gemm_mfma_kernel<ProjPolicy", "gemm_mfma_proj"),
+    ("gemm_tile_kernel<TProjPolicy", "gemm_mfma_proj"),
     ("gemm_mfma_pair_kernel", "gemm_mfma_grads"),
+    ("gemm_tile_pair_kernel", "gemm_mfma_grads"),
     ("gemm_mfma_kernel<GradXPolicy", "gemm_mfma_gradx"),
     ("gemm_mfma_kernel<GradEPolicy", "gemm_mfma_grade"),
     ("proj_finish_kernel", "proj_finish"),
@@ -36,10 +38,12 @@ TIMER_NAME_RULES = [
     ("merge_pack_kernel", "merge_pack"),
     ("query_stream_kernel", "query_stream"),
     ("bwd_query_x", "bwd_query_x"),
+    ("bwd_query_elu_kernel", "bwd_query_x"),
     ("bwd_query_y_kernel", "bwd_query_y"),
     ("bwd_merge_kernel", "bwd_merge"),
     ("bwd_key_kernel", "bwd_key"),
     ("sum_splits_bf16_kernel", "sum_splits"),
+    ("sum_splits_fine_kernel", "sum_splits"),
 ]
 
 
