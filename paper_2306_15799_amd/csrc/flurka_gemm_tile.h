@@ -88,9 +88,31 @@ __device__ __forceinline__ void unroll(F&& f) {
 
 // Work items and their order: id mod 8 (the XCD) is the low part of (tile along the large operand, which, split),
 // the tiles that share a tile of the large operand follow, so that they run on one XCD at about the same time and
-// that tile leaves HBM once, and each XCD keeps to few ranges of the other operand.  A workgroup's items are
-// streamed: the transfers run NST steps ahead of the products, into the next item.  nblocks is a multiple of 8 or
-// the item count; item_lo is a multiple of 8.
+// that tile leaves HBM once, and each XCD keeps to few ranges of the other operand.
+struct TileItem { int split, tm, tn, which; bool valid; };
+template <bool SHARE_A>
+__host__ __device__ inline TileItem tile_item(const GemmParams& g, int id, int item_hi) {
+    TileItem it;
+    it.valid = id < item_hi;
+    if (!it.valid) id = 0;
+    const int xcd = id & 7; id >>= 3;
+    const int shared = SHARE_A ? g.tilesN : g.tilesM;         // tiles that read the same large operand
+    const int inner = id % shared; id /= shared;
+    int u = 8 * id + xcd;                                     // (tile along the large operand, which, split)
+    it.split = u % g.splits;  u /= g.splits;
+    it.which = u & 1;
+    int outer = u >> 1;
+    // Only past the last real item of a workgroup.  Such an id still names a tile that exists: addresses and descriptor
+    // ranges are formed for it too, and a range computed for heads past the last one would wrap to nearly 4 GiB,
+    // which G_OOB lies inside of.
+    if (outer >= (SHARE_A ? g.tilesM : g.tilesN)) { it.valid = false; outer = 0; }
+    it.tm = SHARE_A ? outer : inner;
+    it.tn = SHARE_A ? inner : outer;
+    return it;
+}
+
+// A workgroup's items are streamed: the transfers run NST steps ahead of the products, into the next item.  nblocks
+// is a multiple of 8 or the item count; item_lo is a multiple of 8.
 template <class Pol, int NST>
 __device__ __forceinline__ void gemm_tile_body(const GemmParams& g, const int block, const int nblocks,
                                                unsigned char* const lds, const int item_lo, const int item_hi) {
@@ -104,21 +126,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& g, const int bl
     const int wm = wave / L::WN, wn = wave % L::WN;
     const int half = lane >> 5, l32 = lane & 31, s16 = lane & 15, r4 = s16 >> 2;
 
-    struct Item { int split, tm, tn, which, step0, step1; bool valid; };
+    struct Item : TileItem { int step0, step1; };
     auto decode = [&](int id) -> Item {
         Item it;
-        it.valid = id < item_hi;
-        if (!it.valid) id = 0;
-        const int xcd = id & 7; id >>= 3;
-        const int shared = Pol::SHARE_A ? g.tilesN : g.tilesM;    // tiles that read the same large operand
-        const int inner = id % shared; id /= shared;
-        int u = 8 * id + xcd;                                     // (tile along the large operand, which, split)
-        it.split = u % g.splits;  u /= g.splits;
-        it.which = u & 1;
-        const int outer = u >> 1;
-        it.tm = Pol::SHARE_A ? outer : inner;
-        it.tn = Pol::SHARE_A ? inner : outer;
-        if (outer >= (Pol::SHARE_A ? g.tilesM : g.tilesN)) it.valid = false;      // only past the last real item
+        (TileItem&)it = tile_item<Pol::SHARE_A>(g, id, item_hi);
         it.step0 = it.split * g.steps_per_split;
         it.step1 = it.step0 + g.steps_per_split;
         if (it.step1 > g.total_steps) it.step1 = g.total_steps;
@@ -430,16 +441,15 @@ struct TGradEPolicy {
 };
 
 // ids handed to workgroups: the (split, tile along the large operand, which) index padded to a multiple of 8
-template <class Pol>
+template <bool SHARE_A>
 __host__ __device__ inline int tile_item_count(const GemmParams& g) {
-    return Pol::SHARE_A ? 8 * g.tilesN * ((g.splits * g.tilesM * 2 + 7) / 8)
-                        : 8 * g.tilesM * ((g.splits * g.tilesN * 2 + 7) / 8);
+    return SHARE_A ? 8 * g.tilesN * ((g.splits * g.tilesM * 2 + 7) / 8) : 8 * g.tilesM * ((g.splits * g.tilesN * 2 + 7) / 8);
 }
 
 template <class Pol, int NST>
 __global__ __launch_bounds__(Pol::NW * 64) void gemm_tile_kernel(GemmParams g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    gemm_tile_body<Pol, NST>(g, (int)blockIdx.x, (int)gridDim.x, lds, 0, tile_item_count<Pol>(g));
+    gemm_tile_body<Pol, NST>(g, (int)blockIdx.x, (int)gridDim.x, lds, 0, tile_item_count<Pol::SHARE_A>(g));
 }
 
 // Two GEMMs in one launch (see gemm_mfma_pair_kernel).
@@ -462,7 +472,7 @@ static inline flurka_status launch_gemm_tile(const GemmParams& g, hipStream_t s)
     auto kern = gemm_tile_kernel<Pol, NST>;
     constexpr int ldsb = TileShape<Pol::TM, Pol::TN>::lds(NST, Pol::TRANSPOSED_STORE);
     static_assert(ldsb <= 160 * 1024, "LDS of a compute unit");
-    const int items = tile_item_count<Pol>(g);
+    const int items = tile_item_count<Pol::SHARE_A>(g);
     int grid = resident_grid((const void*)kern, Pol::NW * 64, ldsb, items);
     if (grid < 1) return FLURKA_ERR_LAUNCH;
     if (grid < items) grid = grid / 8 * 8;

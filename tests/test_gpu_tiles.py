@@ -18,6 +18,9 @@ SHAPES = [(1, 1, 8, 64, 1), (1, 3, 56, 64, 63), (1, 3, 64, 128, 64), (1, 5, 72, 
           (1, 1, 2048, 128, 127), (1, 7, 520, 64, 128), (1, 3, 2056, 128, 129), (4, 8, 4096, 64, 255),
           (4, 4, 4104, 128, 256), (2, 8, 2000, 64, 257), (1, 16, 1032, 128, 300), (8, 80, 136, 64, 33),
           (4, 24, 200, 128, 400), (1, 2, 8200, 64, 20)]
+# more tiles than compute units, in a number that is no multiple of 8: ids past the last tile
+SHAPES += [(7, 22, 72, 64, 618), (9, 9, 136, 128, 609), (1, 42, 24, 64, 853), (1, 41, 72, 128, 377), (5, 5, 200, 64, 514),
+           (7, 37, 72, 64, 33), (1, 33, 40, 128, 304)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
