@@ -279,14 +279,16 @@ __global__ __launch_bounds__(KS_WAVES * 64) void key_state_kernel(KeyStateArgs a
     for (int t = 0; t < TT; ++t) accS[t] = zero16();
     float zsum = 0.f;
     constexpr float LOG2E = 1.4426950408889634f;
+    // a range in which every |k'|^2 overflows has no finite exponent: its weights are 0, not exp(-inf + inf)
+    float shift = 0.f;
     auto accumulate = [&](const floatx16& e, const VFrag& f) {
         uint32_t hi[8], lo[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             float p0 = e[2 * q], p1 = e[2 * q + 1];
             if constexpr (!ELU) {
-                p0 = fast_exp2((p0 - c) * LOG2E);
-                p1 = fast_exp2((p1 - c) * LOG2E);
+                p0 = fast_exp2((p0 - shift) * LOG2E);
+                p1 = fast_exp2((p1 - shift) * LOG2E);
             }
             zsum += p0 + p1;
             split2_pair(p0, p1, hi[q], lo[q]);
@@ -311,6 +313,10 @@ __global__ __launch_bounds__(KS_WAVES * 64) void key_state_kernel(KeyStateArgs a
 #pragma unroll
         for (int g = 0; g < 16; ++g) c = fmaxf(c, e[g]);
     };
+    auto set_shift = [&]() {
+        c = half_max(c);
+        shift = c == -INFINITY ? 0.f : c;
+    };
     const int nt = kt1 - kt0;
     if constexpr (!ELU) c = -INFINITY;
     // Ranges of one or two tiles (what the plan aims for) are evaluated once and kept in registers between
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(KS_WAVES * 64) void key_state_kernel(KeyStateArgs a
         if constexpr (!ELU) {
             raise(ev[0]);
             if (nt > 1) raise(ev[1]);
-            c = half_max(c);
+            set_shift();
         }
         accumulate(ev[0], vf);
         behind();
@@ -347,7 +353,7 @@ __global__ __launch_bounds__(KS_WAVES * 64) void key_state_kernel(KeyStateArgs a
                 load_k(kt, kf);
                 raise(tile_values(kt, kf));
             }
-            c = half_max(c);
+            set_shift();
         }
         for (int kt = kt0; kt < kt1; ++kt) {
             VFrag vf;

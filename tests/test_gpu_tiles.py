@@ -73,3 +73,22 @@ def test_elu_gradients(shape):
     B, H, n, d, k = shape
     w = Workload("tiles", B, H, n, d, k, d, "bf16", PHI_ELU1, True)
     print(shape, gu.check_forward_backward(w, seed=6, algo="fast"))
+
+
+# the first key tile, a tile in the middle and the last third of the keys: one tile per wavefront, two, several
+@pytest.mark.parametrize("far", [slice(0, 32), slice(32, 64), slice(-40, None)], ids=["first", "second", "last"])
+@pytest.mark.parametrize("B,H,n,d,k,m", [(1, 2, 64, 64, 64, 64), (1, 2, 96, 128, 96, 40), (1, 2, 640, 64, 600, 32),
+                                         (3, 80, 128, 64, 128, 64), (1, 1, 1088, 64, 1056, 32)])
+def test_keys_too_long_for_their_squared_norm(B, H, n, d, k, m, far):
+    """Whole tiles of projected keys with |k'|^2 beyond float32: exponents of -inf, weights of 0."""
+    w = Workload("far_keys", B, H, n, d, k, m, "bf16", PHI_PERFORMER, True)
+    t = inputs.make_inputs(w, 3)
+    t["E"][far] *= np.float32(2.0 ** 66)
+    print((B, H, n, d, k, m), far, flush=True)
+    g, out, ctx = gu.run_forward(w, t, "fast")
+    grads = gu.run_backward(w, g, out, ctx, "fast")
+    errs = {"out": gu.rel_err(gu.to_host(out), gu.oracle_forward(w, t))}
+    for name, a, b in zip(("dQ", "dK", "dV", "dE", "dF"), grads, gu.oracle_backward(w, t)):
+        errs[name] = gu.rel_err(gu.to_host(a), b)
+    print({x: f"{v:.2e}" for x, v in errs.items()})
+    assert all(v <= gu.TOL["bf16"] for v in errs.values()), errs
