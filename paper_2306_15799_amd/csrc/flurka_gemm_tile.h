@@ -34,8 +34,13 @@ __device__ __forceinline__ u32x4 tile_rsrc(const void* base, unsigned bytes) {
 // 16 bytes per lane from a buffer straight into LDS, lane l's at dst + 16 * l; addresses past the descriptor's
 // range store zero.  Written as an instruction of its own because the compiler puts a wait for every transfer
 // in flight before any LDS read that follows the builtin, which would leave nothing in flight; nothing comes
-// back in registers, and wait_and_barrier below is what the reads of the data stand behind.  (m0, the LDS address,
-// is set right before each use, by the compiler too.)  The two scalar additions keep m0's write and its use apart.
+// back in registers, and wait_and_barrier below is what the reads of the data stand behind.
+// What the compiler does between instructions of its own is done here: a write of m0 (the LDS address) and its use are
+// one wait state apart, and a scalar register written by a vector instruction (v_readfirstlane, or v_readlane of a
+// spilled one) and a vector memory instruction that reads it are five apart, whatever stands before the block: two
+// scalar additions and s_nop 2.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"      // m0 is a register the allocator leaves alone: named all the same
 template <int DST>
 __device__ __forceinline__ void lds_dma16(const u32x4& r, unsigned lds_dst, int voff, int soff, int js) {
     // wave-uniform values all of them; said so for builds that do not find out
@@ -43,11 +48,12 @@ __device__ __forceinline__ void lds_dma16(const u32x4& r, unsigned lds_dst, int 
     soff = __builtin_amdgcn_readfirstlane(soff);
     js = __builtin_amdgcn_readfirstlane(js);
     int t;
-    asm volatile("s_add_u32 m0, %1, %2\n\ts_add_u32 %0, %3, %4\n\tbuffer_load_dwordx4 %5, %6, %0 offen lds"
+    asm volatile("s_add_u32 m0, %1, %2\n\ts_add_u32 %0, %3, %4\n\ts_nop 2\n\tbuffer_load_dwordx4 %5, %6, %0 offen lds"
                  : "=&s"(t)
                  : "s"(lds_dst), "n"(DST), "s"(soff), "s"(js), "v"(voff), "s"(r)
-                 : "scc", "memory");
+                 : "scc", "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 // s_waitcnt vmcnt(N) lgkmcnt(0), then the workgroup barrier: this wavefront's transfers but the last N have
 // landed and its LDS reads are done, and so are everybody else's once the barrier opens.
