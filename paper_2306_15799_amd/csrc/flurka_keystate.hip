@@ -177,13 +177,18 @@ struct KeyStateLds {
     static __host__ __device__ int total(int KR) { return KR * range_floats * 4; }
 };
 
-constexpr int KS_KEEP = 2;         // key tiles of a range that stay in registers between maximum and accumulation
+// Key tiles of a range that stay in registers between maximum and accumulation.  Ranges of three or four tiles (513 to
+// 1024 keys) keep them too where the registers allow (head size 64, random features): 48 heads of 64, m 256, key_state
+// evaluating such ranges twice 29.9 us at k 768, 36.3 at 1024; kept 23.5 and 27.6.  In a kernel of its own: the shorter
+// ranges need 20 registers less.
+constexpr int KS_KEEP = 2, KS_KEEP_LONG = 4;
 constexpr int KS_WAVES = 8;        // most wavefronts (key ranges) per workgroup: what the registers leave room for
 constexpr int KS_MERGERS = 4;      // fewest wavefronts per workgroup: the merge wants more than one
 
 // EXACT: the keys and values are bf16 numbers to begin with (kernel attention without a sequence
 // projection): one term of K and one of V carry everything, the other operand terms are skipped.
-template <int D, bool ELU, bool EXACT>
+// KEEP: key tiles of a range that are evaluated once.
+template <int D, bool ELU, bool EXACT, int KEEP>
 __global__ __launch_bounds__(KS_WAVES * 64) void key_state_kernel(KeyStateArgs a) {
     constexpr int KS = D / 16, TT = D / 32;
     constexpr int TERMS = EXACT ? 1 : 3;
@@ -319,33 +324,39 @@ __global__ __launch_bounds__(KS_WAVES * 64) void key_state_kernel(KeyStateArgs a
     };
     const int nt = kt1 - kt0;
     if constexpr (!ELU) c = -INFINITY;
-    // Ranges of one or two tiles (what the plan aims for) are evaluated once and kept in registers between
-    // the maximum and the accumulation, their loads in flight together; longer ranges are evaluated twice.
-    if (nt <= KS_KEEP) {
-        floatx16 ev[KS_KEEP];
+    // Ranges of up to KEEP tiles (one or two is what the plan aims for) are evaluated once and kept in registers between
+    // the maximum and the accumulation, the first tile's loads in flight together; longer ranges are evaluated twice.
+    if (nt <= KEEP) {
+        floatx16 ev[KEEP];
         KFrag kf;
         VFrag vf;
         load_k(kt0, kf);
         if constexpr (V_EARLY) load_v(kt0, vf);
         ev[0] = tile_values(kt0, kf);
         behind();
-        if (nt > 1) {
-            load_k(kt0 + 1, kf);
-            ev[1] = tile_values(kt0 + 1, kf);
-        }
+#pragma unroll
+        for (int i = 1; i < KEEP; ++i)
+            if (i < nt) {
+                load_k(kt0 + i, kf);
+                ev[i] = tile_values(kt0 + i, kf);
+            }
         behind();
         if constexpr (!V_EARLY) load_v(kt0, vf);
         if constexpr (!ELU) {
             raise(ev[0]);
-            if (nt > 1) raise(ev[1]);
+#pragma unroll
+            for (int i = 1; i < KEEP; ++i)
+                if (i < nt) raise(ev[i]);
             set_shift();
         }
         accumulate(ev[0], vf);
         behind();
-        if (nt > 1) {
-            load_v(kt0 + 1, vf);
-            accumulate(ev[1], vf);
-        }
+#pragma unroll
+        for (int i = 1; i < KEEP; ++i)
+            if (i < nt) {
+                load_v(kt0 + i, vf);
+                accumulate(ev[i], vf);
+            }
     } else {
         KFrag kf;
         if constexpr (!ELU) {
@@ -455,8 +466,8 @@ KeyStatePlan key_state_plan(const Problem& p) {
     q.FT = p.mfp / 32;
     const int KT = q.kpad / 32;
     // Key ranges = wavefronts of a workgroup, at most KS_WAVES (the ranges' partial tiles meet in LDS): one key tile
-    // each while the chip holds them all at once (two wavefronts per SIMD), two each otherwise.  Ranges of more than
-    // KS_KEEP tiles are evaluated twice (maximum, then accumulation).
+    // each while the chip holds them all at once (two wavefronts per SIMD), two each otherwise.  Ranges of more tiles
+    // than the kernel keeps are evaluated twice (maximum, then accumulation).
     int KR = KT < KS_WAVES ? KT : KS_WAVES;
     if ((long)p.BH * q.FT * KR > 8L * chip_cus() && KR > (KT + 1) / 2) KR = (KT + 1) / 2;
     q.tiles_per_range = (KT + KR - 1) / KR;
@@ -464,9 +475,9 @@ KeyStatePlan key_state_plan(const Problem& p) {
     return q;
 }
 
-template <int D, bool ELU, bool EXACT>
+template <int D, bool ELU, bool EXACT, int KEEP = KS_KEEP>
 static flurka_status launch_key_state_impl(const Problem& p, const KeyStateArgs& ka, hipStream_t s) {
-    auto kern = key_state_kernel<D, ELU, EXACT>;
+    auto kern = key_state_kernel<D, ELU, EXACT, KEEP>;
     const int ldsb = KeyStateLds<D>::total(ka.KR);
     const int waves = ka.KR < KS_MERGERS ? KS_MERGERS : ka.KR;
     KernelFacts facts;
@@ -479,6 +490,11 @@ static flurka_status launch_key_state_impl(const Problem& p, const KeyStateArgs&
 template <int D>
 static flurka_status launch_key_state(const Problem& p, const KeyStateArgs& ka, bool exact, hipStream_t s) {
     if (exact) return p.elu ? launch_key_state_impl<D, true, true>(p, ka, s) : launch_key_state_impl<D, false, true>(p, ka, s);
+    if constexpr (D == 64) {
+        // 513 to 1024 keys: three or four tiles a range
+        if (!p.elu && ka.tiles_per_range > KS_KEEP && ka.tiles_per_range <= KS_KEEP_LONG)
+            return launch_key_state_impl<D, false, false, KS_KEEP_LONG>(p, ka, s);
+    }
     return p.elu ? launch_key_state_impl<D, true, false>(p, ka, s) : launch_key_state_impl<D, false, false>(p, ka, s);
 }
 
