@@ -33,8 +33,7 @@
 #include "flurka_fast.h"
 #include "flurka_gemm.h"
 #include "flurka_gemm_tile.h"
-
-#include <string.h>
+#include "flurka_plan.h"
 
 namespace flurka {
 
@@ -1380,74 +1379,6 @@ bool fast_bwd_supported(const Problem& p) {
     const size_t kp = ((size_t)p.k + 63) / 64 * 64;
     if (((size_t)p.BH * p.d + GBM) * kp * 2 >= ((size_t)1 << 31)) return false;
     return true;
-}
-
-struct GradEPlan {
-    bool fine;             // 128 x 128 tiles (two workgroups per compute unit) instead of 256 x 256
-    int tilesM, tilesN;    // of the dE/dF GEMM: slots x positions, fine: positions x slots
-    int total_steps, splits, steps_per_split;
-    int resident;          // workgroups of the launch dE/dF share with dK/dV
-    PairPlan pair;
-    size_t partial_bytes() const {
-        return splits == 1 ? 0 : (size_t)2 * splits * tilesM * tilesN * (fine ? 128 * 128 : G_TILE_ELEMS) * 4;
-    }
-};
-
-// dE/dF (few items with a reduction over all B*H*d/64 steps) share their launch with dK/dV (many items of
-// kp/64 steps).  Unsplit, the long items are the critical path whenever there are fewer of them than
-// compute units (64 at the headline size with 256 x 256 tiles: 89 us, the short items done after 46); split s
-// ways they finish sooner, their workgroups go on with short items, and a second pass sums the s partial
-// results.  The tile and the split that the cost model (plan_pair, plus the traffic of the second pass) expects
-// to finish first win.  128 x 128 tiles: 1.15 us per step with two workgroups to a compute unit, 2.0 and 2.2 us
-// for the epilogues.  They take twice the operand traffic, so long reductions on both sides stay with 256 x 256;
-// elsewhere they need no or fewer partial results and fill the chip.  Training steps, 256 x 256 -> this rule:
-// 48 heads of 64, n 8192, k 256: 341 -> 333 us; 16 heads of 128, n 6016, k 300: 218 -> 204;
-// 64 heads of 128, n 65536, k 512 (stays): 1810, with 128 x 128 1905.
-constexpr double T_PAIR_STEP_US = 1.15, T_PAIR_EPILOGUE_E_US = 2.0, T_PAIR_EPILOGUE_X_US = 2.2;
-
-static GradEPlan make_grad_e_plan(const Problem& p) {
-    GradEPlan best{};
-    double best_t = -1.0;
-    const int kp = (p.k + 63) / 64 * 64, steps_b = kp / GBK, rows_b = p.BH * p.d;
-    for (int fine = 0; fine < 2; ++fine) {
-        GradEPlan q{};
-        const int tile = fine ? 128 : GBM;
-        const int slots = (p.k + tile - 1) / tile, positions = (p.n + tile - 1) / tile;
-        q.fine = fine != 0;
-        q.tilesM = fine ? positions : slots;
-        q.tilesN = fine ? slots : positions;
-        q.total_steps = p.BH * p.d / GBK;
-        q.resident = fine ? 2 * chip_cus() / 8 * 8 : chip_cus() / 8 * 8;
-        const int items_b = 8 * ((rows_b + tile - 1) / tile) * ((positions * 2 + 7) / 8);
-        const double tb = fine ? steps_b * T_PAIR_STEP_US + T_PAIR_EPILOGUE_X_US : ((steps_b + 1) & ~1) * G_STEP_US + G_EPILOGUE_T_US;
-        for (int want = 1; want <= (fine ? 32 : 8) && want <= q.total_steps; want += want < 8 ? 1 : 8) {
-            const int sps = (q.total_steps + want - 1) / want;
-            const int splits = (q.total_steps + sps - 1) / sps;
-            if (want <= 8 && splits != want) continue;
-            const int items_a = 8 * slots * ((splits * positions * 2 + 7) / 8);
-            q.splits = splits; q.steps_per_split = sps;
-            double t = 0.0;
-            q.pair = plan_pair(items_a, fine ? sps * T_PAIR_STEP_US + T_PAIR_EPILOGUE_E_US : ((sps + 1) & ~1) * G_STEP_US + G_EPILOGUE_US,
-                               items_b, tb, q.resident, &t);
-            // second pass: reads the fp32 partials, writes bf16; about 4 TB/s plus a launch
-            if (splits > 1) t += 4.0 + ((double)q.partial_bytes() + 4.0 * p.k * (double)p.n) / 4.0e6;
-            if (best_t < 0.0 || t < best_t) { best_t = t; best = q; }
-        }
-    }
-    return best;
-}
-
-// The plan depends on sizes alone and a backward call asks for it four times (buffer sizes, layout, launch): the
-// thread's last one is kept.
-static const GradEPlan& grad_e_plan(const Problem& p) {
-    static thread_local int key[5] = {0, 0, 0, 0, 0};
-    static thread_local GradEPlan plan{};
-    const int now[5] = {p.BH, p.n, p.d, p.k, chip_cus()};
-    if (memcmp(key, now, sizeof(now)) != 0) {
-        plan = make_grad_e_plan(p);
-        memcpy(key, now, sizeof(now));
-    }
-    return plan;
 }
 
 struct BwdYPlan { int FT, NW, R, tiles_per_range; };

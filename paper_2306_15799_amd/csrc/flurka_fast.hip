@@ -15,6 +15,7 @@
 #include "flurka_fast.h"
 #include "flurka_gemm.h"
 #include "flurka_gemm_tile.h"
+#include "flurka_plan.h"
 
 namespace flurka {
 
@@ -28,57 +29,6 @@ static inline dim3 grid1d(long total, int block) { return dim3((unsigned)((total
 // ===========================================================================
 // Stage "project": C[k x (BH*d)] = E[k x n] * X[n x (BH*d)] for X in {K, V}
 // ===========================================================================
-struct SplitGemmPlan {
-    int kind;              // index into SPLIT_GEMM_KINDS
-    PartialTile t;         // output tile
-    int tilesM, tilesN, splits, steps_per_split, total_steps;
-    size_t partial_bytes() const { return (size_t)2 * splits * tilesM * tilesN * t.tm * t.tn * 4; }
-};
-
-// Output tiles of the products that leave fp32 split partials, and the time of one 64-deep reduction step of a
-// workgroup that has a compute unit to itself.  Measured with operands from HBM: the 256 x 256 tile is bound by
-// its matrix instructions, the others by how fast a compute unit takes its operands in (50 - 57 GB/s).
-struct SplitGemmKind { PartialTile t; double step_us; };
-constexpr SplitGemmKind SPLIT_GEMM_KINDS[] = {
-    {{256, 256, 128, 128}, 1.78}, {{128, 256, 64, 64}, 0.95}, {{128, 128, 64, 64}, 0.6}, {{64, 128, 32, 64}, 0.45}};
-
-// Tile and split of two products of k rows, `batches` times `cols` columns (no tile crosses a batch) and `total_steps` steps whose operands are `bytes` long.
-// The partial results are the price of a split (written at the end, when nothing is left to read beside it, and
-// read again by the second stage, both at about 4.5 TB/s): 64 MiB with a 256 x 256 tile on every compute unit,
-// whatever the size of the problem.  Short reductions want the smaller tiles and few splits, long ones the large
-// tile.  Measured, forward passes, 256 x 256 with one split per compute unit against this rule's choice:
-//   k 256, n 4096, 64 heads of 64:    98.1 -> 81.0 us (128 x 128)     k 64, the same:    71.3 -> 56.7 us (64 x 128)
-//   k 256, n 16384, 64 heads of 64:  164.2 -> 156.7 us (128 x 256)    k 512, n 65536, 16 heads of 128: 437 us (stays)
-static SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_steps, double bytes) {
-    const int cus = chip_cus();
-    SplitGemmPlan best{};
-    double best_t = -1.0;
-    for (int kind = 0; kind < 4; ++kind) {
-        SplitGemmPlan q;
-        q.kind = kind;
-        q.t = SPLIT_GEMM_KINDS[kind].t;
-        q.tilesM = (k + q.t.tm - 1) / q.t.tm;
-        q.tilesN = batches * ((cols + q.t.tn - 1) / q.t.tn);
-        q.total_steps = total_steps;
-        const int tiles = q.tilesM * q.tilesN * 2;
-        const int most = tiles < cus ? (cus / tiles < total_steps ? cus / tiles : total_steps) : 1;
-        for (int want = 1; want <= most; want += want < 8 ? 1 : 8) {
-            q.steps_per_split = (total_steps + want - 1) / want;
-            q.splits = (total_steps + q.steps_per_split - 1) / q.steps_per_split;
-            const double read = bytes / 4.8e6;
-            double t = (double)q.steps_per_split * ((tiles + cus - 1) / cus) * SPLIT_GEMM_KINDS[kind].step_us;
-            if (t < read) t = read;
-            t += 2.0 * (double)q.partial_bytes() / 4.5e6 + 0.1 * q.splits;
-            if (best_t < 0.0 || t < best_t) { best_t = t; best = q; }
-        }
-    }
-    return best;
-}
-
-static SplitGemmPlan proj_plan(const Problem& p) {
-    return split_gemm_plan(p.k, 1, p.BH * p.d, (p.n + GBK - 1) / GBK, 4.0 * p.n * ((double)p.BH * p.d + p.k));
-}
-
 static void set_plan(GemmParams& gp, const SplitGemmPlan& q) {
     gp.tilesM = q.tilesM; gp.tilesN = q.tilesN; gp.splits = q.splits;
     gp.steps_per_split = q.steps_per_split; gp.total_steps = q.total_steps;
@@ -497,21 +447,6 @@ __global__ __launch_bounds__(256) void wide_finish_kernel(WideFinishArgs a) {
         row[a.dm] = (uint16_t)mid;
         row[2 * a.dm] = (uint16_t)lo;
     }
-}
-
-struct FusedWPlan {
-    int tpb1, tpb2;                // column tiles per batch of the two products
-    SplitGemmPlan s1, s2;
-};
-
-static FusedWPlan fusedw_plan(const Problem& p, int dm) {
-    FusedWPlan q;
-    q.s1 = split_gemm_plan(p.k, p.B, dm, (p.n + GBK - 1) / GBK, 4.0 * p.n * ((double)p.B * dm + p.k));
-    q.tpb1 = q.s1.tilesN / p.B;
-    const double terms = 3.0 * dm * 2.0;
-    q.s2 = split_gemm_plan(p.k, p.B, p.H * p.d, 3 * dm / GBK, 2.0 * terms * p.B * p.k + 4.0 * p.H * p.d * dm);
-    q.tpb2 = q.s2.tilesN / p.B;
-    return q;
 }
 
 bool fast_fusedw_supported(const Problem& p, int dm) {

@@ -636,41 +636,6 @@ static inline flurka_status launch_gemm_mfma(const GemmParams& g, hipStream_t s)
     return launch_gemm_mfma_impl<Pol, true>(g, resident, s);
 }
 
-// Split of one resident round of `resident` workgroups between two GEMMs of items_a items of ta us each
-// (items_a a multiple of 8) and items_b items of tb us; `us` receives the time the model expects.
-// Measured on MI355X with operands from HBM, 256 x 256 tiles: 1.8 us per reduction step of a
-// workgroup that has a compute unit to itself, about 3 us for an epilogue that stores its accumulators
-// as they are, 4.4 us for the transposing epilogue of dK, dV.
-constexpr double G_STEP_US = 1.8, G_EPILOGUE_US = 3.0, G_EPILOGUE_T_US = 4.4;
-
-inline PairPlan plan_pair(int items_a, double ta, int items_b, double tb, int resident, double* us) {
-    PairPlan best{};
-    double best_t = -1.0;
-    // as few starters as run their first-part items in `rounds` rounds
-    for (int rounds = 1; rounds <= 16; ++rounds) {
-        int ba = ((items_a + rounds - 1) / rounds + 7) / 8 * 8;
-        if (ba > resident - 8) ba = resident - 8;
-        const int bb = resident - ba;
-        const double t_first = ((items_a + ba - 1) / ba) * ta;
-        // items per workgroup of the second kind near the point where both kinds finish together
-        const int x0 = (int)((t_first / tb * ba + items_b) / resident);
-        for (int xb = x0 > 0 ? x0 : 1; xb <= x0 + 1; ++xb) {
-            long main_b = (long)bb * xb / 8 * 8;
-            if (main_b > items_b) main_b = items_b;
-            const int xa = (int)((items_b - main_b + ba - 1) / ba);
-            const double t_a = t_first + xa * tb, t_b = (double)((main_b + bb - 1) / bb) * tb;
-            const double t = t_a > t_b ? t_a : t_b;
-            if (best_t < 0.0 || t < best_t) {
-                best_t = t;
-                best.blocks_a = ba; best.main_b = (int)main_b; best.items_a = items_a; best.items_b = items_b;
-            }
-        }
-        if (ba <= 8) break;
-    }
-    if (us) *us = best_t;
-    return best;
-}
-
 // Both GEMMs in one launch (gemm_mfma_pair_kernel) with the split `pl` of a resident round of
 // `resident` workgroups (plan_pair).  Falls back to two launches where the kernel cannot keep 16
 // workgroups resident.
