@@ -20,11 +20,13 @@ struct SplitGemmPlan {
 };
 
 // Output tiles of the products that leave fp32 split partials, and the time of one 64-deep reduction step of a
-// workgroup that has a compute unit to itself.  Measured with operands from HBM: the 256 x 256 tile is bound by
-// its matrix instructions, the others by how fast a compute unit takes its operands in (50 - 57 GB/s).
-struct SplitGemmKind { PartialTile t; double step_us; };
-constexpr SplitGemmKind SPLIT_GEMM_KINDS[] = {
-    {{256, 256, 128, 128}, 1.78}, {{128, 256, 64, 64}, 0.95}, {{128, 128, 64, 64}, 0.6}, {{64, 128, 32, 64}, 0.45}};
+// workgroup that has a compute unit to itself: with all compute units at work, and with three quarters of them or fewer.
+// Measured with operands from HBM: the 256 x 256 tile is bound by its matrix instructions, which run faster where some of
+// the chip idles (1.51 - 1.55 us per step with 144 to 192 workgroups, 1.8 - 1.9 with 256); the others by how fast a
+// compute unit takes its operands in (50 - 57 GB/s).
+struct SplitGemmKind { PartialTile t; double step_us, step_us_part; };
+constexpr SplitGemmKind SPLIT_GEMM_KINDS[] = {{{256, 256, 128, 128}, 1.78, 1.55}, {{128, 256, 64, 64}, 0.95, 0.95},
+                                              {{128, 128, 64, 64}, 0.6, 0.6}, {{64, 128, 32, 64}, 0.45, 0.45}};
 
 // Tile and split of two products of k rows, `batches` times `cols` columns (no tile crosses a batch) and `total_steps`
 // steps whose operands are `bytes` long.
@@ -34,6 +36,7 @@ constexpr SplitGemmKind SPLIT_GEMM_KINDS[] = {
 // tile.  Measured, forward passes, 256 x 256 with one split per compute unit against this rule's choice:
 //   k 256, n 4096, 64 heads of 64:    98.1 -> 81.0 us (128 x 128)     k 64, the same:    71.3 -> 56.7 us (64 x 128)
 //   k 256, n 16384, 64 heads of 64:  164.2 -> 156.7 us (128 x 256)    k 512, n 65536, 16 heads of 128: 437 us (stays)
+//   k 768 - 1129, n 8192 - 13280, 24 to 48 heads: 256 x 256 (192 to 240 workgroups) 185 - 285 us, 128 x 256 4 % more
 inline SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_steps, double bytes) {
     const int cus = chip_cus();
     SplitGemmPlan best{};
@@ -54,7 +57,11 @@ inline SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_ste
             // rounds of workgroups: the smaller tiles hand out ids padded to a multiple of 8 per row tile
             const long ids = kind == 0 ? (long)tiles * q.splits : 8L * q.tilesM * ((2L * q.splits * q.tilesN + 7) / 8);
             const long rounds = (ids + cus - 1) / cus;
-            double t = (double)q.steps_per_split * (double)rounds * SPLIT_GEMM_KINDS[kind].step_us;
+            // share of the chip at work in a round, from three quarters (0) to all of it (1)
+            double full = 4.0 * (double)tiles * q.splits / (double)(rounds * cus) - 3.0;
+            if (full < 0.0) full = 0.0;
+            const SplitGemmKind& g = SPLIT_GEMM_KINDS[kind];
+            double t = (double)q.steps_per_split * (double)rounds * (g.step_us_part + full * (g.step_us - g.step_us_part));
             if (t < read) t = read;
             t += 2.0 * (double)q.partial_bytes() / 4.5e6 + 0.1 * q.splits;
             if (best_t < 0.0 || t < best_t) { best_t = t; best = q; }
