@@ -1446,23 +1446,25 @@ static FastBwdWs fast_bwd_ws_layout(const Problem& p) {
     return W;
 }
 
-// elu1: the key side runs on the generic kernels, whose workspace comes first
 struct EluBwdWs {
-    size_t delta, dinv, dSpart, dzpart, img, imgT, epart, total;
+    size_t delta, dinv, dSpart, dzpart, dS, dz, img, imgT, epart, total;
     int kp;
 };
 
 static EluBwdWs elu_bwd_ws_layout(const Problem& p) {
     EluBwdWs W{};
     const BwdYPlan y = bwd_y_plan(p);
-    const GradEPlan e = grad_e_plan(p);
     const size_t BH = (size_t)p.BH;
-    size_t o = round_up(generic_ws_layout(p, 1).total * sizeof(float), 256);
-    W.delta = o;  o += round_up(BH * p.n * 4, 256);
-    W.dinv = o;   o += round_up(BH * p.n * 4, 256);
+    const size_t rows = elu_joined(p) ? 0 : round_up(BH * p.n * 4, 256);      // the joined kernel hands nothing on per query row
+    size_t o = 0;
+    W.delta = o;  o += rows;
+    W.dinv = o;   o += rows;
     W.dSpart = o; o += round_up(BH * y.R * p.mfp * p.d * 4, 256);
     W.dzpart = o; o += round_up(BH * y.R * p.mfp * 4, 256);
+    W.dS = o;     o += round_up(BH * p.mfp * p.d * 4, 256);
+    W.dz = o;     o += round_up(BH * p.mfp * 4, 256);
     W.kp = (p.k + 63) / 64 * 64;
+    const GradEPlan e = grad_e_plan(p);
     W.img = o;    o += round_up(2 * BH * W.kp * p.d * 2, 256);
     W.imgT = o;   o += round_up(2 * BH * W.kp * p.d * 2, 256);
     W.epart = o;  o += round_up(e.partial_bytes(), 256);
@@ -1767,10 +1769,11 @@ static flurka_status launch_bwd_key_elu(const Problem& p, const float* Kp, const
 
 static flurka_status fast_backward_elu(const Problem& p, const BwdArgs& a, hipStream_t s) {
     const CtxLayout L = ctx_layout(p);
-    const GenericWs GW = generic_ws_layout(p, 1);
     const EluBwdWs W = elu_bwd_ws_layout(p);
     const BwdYPlan y = bwd_y_plan(p);
     unsigned char* wsb = (unsigned char*)a.ws;
+    float* const dS = (float*)(wsb + W.dS);
+    float* const dz = (float*)(wsb + W.dz);
     flurka_status st;
     {
         if (elu_joined(p)) {
@@ -1809,7 +1812,7 @@ static flurka_status fast_backward_elu(const Problem& p, const BwdArgs& a, hipSt
         stage_begin(s);
         const long mtotal = (long)p.BH * (p.mfp / 2) * p.d;
         hipLaunchKernelGGL(bwd_merge_kernel, grid1d(mtotal, 256), dim3(256), 0, s, (uint16_t*)nullptr,
-                           a.ws + GW.dS, a.ws + GW.dz, (const float*)(wsb + W.dSpart),
+                           dS, dz, (const float*)(wsb + W.dSpart),
                            (const float*)(wsb + W.dzpart), y.R, p.mfp, p.d, mtotal);
         FLURKA_CHECK_LAUNCH();
         stage_end(s, STAGE_K_BWD_MERGE);
@@ -1821,8 +1824,8 @@ static flurka_status fast_backward_elu(const Problem& p, const BwdArgs& a, hipSt
         StageScope sc(s, STAGE_K_BWD_KEY);
         const float* Kp = a.ctx + L.Kp;
         const float* Vp = a.ctx + L.Vp;
-        st = p.d == 64 ? launch_bwd_key_elu<64>(p, Kp, Vp, a.ws + GW.dS, a.ws + GW.dz, img, imgT, W.kp, s)
-                       : launch_bwd_key_elu<128>(p, Kp, Vp, a.ws + GW.dS, a.ws + GW.dz, img, imgT, W.kp, s);
+        st = p.d == 64 ? launch_bwd_key_elu<64>(p, Kp, Vp, dS, dz, img, imgT, W.kp, s)
+                       : launch_bwd_key_elu<128>(p, Kp, Vp, dS, dz, img, imgT, W.kp, s);
         if (st != FLURKA_OK) return st;
     }
     return grad_gemms(p, a, img, imgT, W.kp, (float*)(wsb + W.epart), s);
