@@ -155,6 +155,8 @@ inline GradEPlan make_grad_e_plan(const Problem& p) {
     double best_t = -1.0;
     const int kp = (p.k + 63) / 64 * 64, steps_b = kp / GBK, rows_b = p.BH * p.d;
     for (int fine = 0; fine < 2; ++fine) {
+        // no shape needs more scratch than with 256 x 256 tiles alone: a buffer that a caller keeps stays large enough
+        const size_t coarse_bytes = fine ? best.partial_bytes() : 0;
         GradEPlan q{};
         const int tile = fine ? 128 : GBM;
         const int slots = (p.k + tile - 1) / tile, positions = (p.n + tile - 1) / tile;
@@ -171,6 +173,7 @@ inline GradEPlan make_grad_e_plan(const Problem& p) {
             if (want <= 8 && splits != want) continue;
             const int items_a = 8 * slots * ((splits * positions * 2 + 7) / 8);
             q.splits = splits; q.steps_per_split = sps;
+            if (fine && q.partial_bytes() > coarse_bytes) continue;
             double t = 0.0;
             q.pair = plan_pair(items_a, fine ? sps * T_PAIR_STEP_US + T_PAIR_EPILOGUE_E_US : ((sps + 1) & ~1) * G_STEP_US + G_EPILOGUE_US,
                                items_b, tb, q.resident, &t);
