@@ -57,6 +57,33 @@ def test_forward_performer(shape):
     assert fo.rel_l2(gu.to_host(v["Vp"]), Vp) < 3e-6
 
 
+# (B, H, n, d, k, dm): every tile in the first product (128 x 128, 128 x 256, 256 x 256 at two sizes each) and in the
+# second, with a model width that leaves the last column tile half empty, ragged n and k, several batches; SHAPES above
+# run 64 x 128 in both.  test_plans.py holds the list to that.
+TILE_SHAPES = [
+    (3, 4, 16, 64, 1031, 192), (3, 4, 2376, 128, 754, 64), (1, 4, 48, 64, 839, 2240), (3, 4, 32, 128, 364, 1728),
+    (3, 4, 56, 64, 708, 1984), (2, 4, 104, 128, 1247, 1728),
+    (3, 26, 16, 128, 68, 64), (1, 28, 24, 64, 1032, 64), (3, 26, 8, 128, 9, 1856), (3, 28, 24, 64, 736, 64), (3, 14, 32, 128, 727, 64)]
+
+
+@pytest.mark.parametrize("shape", TILE_SHAPES)
+def test_projected_keys_and_values(shape):
+    B, H, n, d, k, dm = shape
+    w = Workload("paper_order_tiles", B, H, n, d, k, d, "bf16", PHI_ELU1, False)
+    t, g, out, ctx = _run(w, dm, 46)
+    v = fb.ctx_views(ctx, B, H, n, d, k, d, fb.BF16, w.phi)
+    for name, e, x, wt in (("Kp", t["E"], t["XK"], t["WK"]), ("Vp", t["F"], t["XV"], t["WV"])):
+        y = np.matmul(e.astype(np.float64), x.astype(np.float64))                          # (B, k, dm)
+        ref = np.matmul(y, wt.reshape(H * d, dm).astype(np.float64).T).reshape(B, k, H, d).transpose(0, 2, 1, 3)
+        got = gu.to_host(v[name])
+        # exact products added in fp32, n of them, then 3 dm: a random walk of rounding errors of 2^-24 each
+        bar = 2.0 * np.sqrt(n + 3 * dm) * 2.0 ** -24
+        err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        print(shape, name, f"{err:.2e} of {bar:.2e}")
+        assert err <= bar
+        assert np.abs(got - ref).max() <= 8 * bar * np.sqrt((ref ** 2).mean())
+
+
 def test_forward_elu():
     B, H, n, d, k, dm = 2, 4, 1024, 64, 128, 256
     w = Workload("paper_order_elu", B, H, n, d, k, d, "bf16", PHI_ELU1, False)

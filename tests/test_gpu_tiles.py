@@ -13,14 +13,22 @@ import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 # (B, H, n, d, k): key counts around the 64-, 128- and 256-row tiles, head counts that leave a column tile ragged, one
-# reduction step and a last one of 8 to 56 positions, one split and many, more tiles than compute units
-SHAPES = [(1, 1, 8, 64, 1), (1, 3, 56, 64, 63), (1, 3, 64, 128, 64), (1, 5, 72, 64, 65), (2, 3, 1000, 64, 100),
-          (1, 1, 2048, 128, 127), (1, 7, 520, 64, 128), (1, 3, 2056, 128, 129), (4, 8, 4096, 64, 255),
-          (4, 4, 4104, 128, 256), (2, 8, 2000, 64, 257), (1, 16, 1032, 128, 300), (8, 80, 136, 64, 33),
-          (4, 24, 200, 128, 400), (1, 2, 8200, 64, 20)]
-# more tiles than compute units, in a number that is no multiple of 8: ids past the last tile
-SHAPES += [(7, 22, 72, 64, 618), (9, 9, 136, 128, 609), (1, 42, 24, 64, 853), (1, 41, 72, 128, 377), (5, 5, 200, 64, 514),
-           (7, 37, 72, 64, 33), (1, 33, 40, 128, 304)]
+# reduction step and a last one of 8 to 56 positions, one split and many, more tiles than compute units (in a number that
+# is no multiple of 8: ids past the last tile).  test_plans.py holds the list to every tile at both head sizes, each with
+# ragged edges, a split reduction and several tiles to a workgroup.
+SHAPES = [
+    # 64 x 128 tiles
+    (1, 1, 8, 64, 1), (1, 3, 56, 64, 63), (1, 3, 64, 128, 64), (1, 5, 72, 64, 65), (2, 3, 1000, 64, 100),
+    (1, 1, 2048, 128, 127), (1, 7, 520, 64, 128), (1, 3, 2056, 128, 129), (2, 8, 2000, 64, 257), (1, 16, 1032, 128, 300),
+    (8, 80, 136, 64, 33), (1, 2, 8200, 64, 20), (7, 37, 72, 64, 33), (1, 33, 40, 128, 304),
+    # 128 x 128
+    (4, 8, 4096, 64, 255), (4, 4, 4104, 128, 256), (1, 42, 24, 64, 853), (5, 5, 200, 64, 514), (3, 3, 856, 64, 746),
+    (1, 17, 8, 64, 1376), (3, 1, 920, 128, 1036), (1, 13, 8, 128, 1405),
+    # 128 x 256
+    (7, 22, 72, 64, 618), (9, 9, 136, 128, 609), (1, 41, 72, 128, 377), (2, 7, 2280, 64, 1044), (2, 53, 8, 64, 875),
+    (1, 13, 2184, 128, 526), (5, 29, 8, 128, 373),
+    # 256 x 256
+    (4, 24, 200, 128, 400), (1, 17, 2352, 64, 1460), (1, 47, 8, 64, 1496), (3, 3, 2400, 128, 1421), (1, 77, 8, 128, 456)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -52,10 +60,15 @@ def test_projected_keys_and_values(shape):
 
 
 # (B, H, n, d, k, m): position and slot counts around the 128- and 256-wide tiles of the gradient products, the
-# reduction over (head, coordinate) whole, split a few ways and split into many, tiles that cross a head
-GRAD_SHAPES = [(1, 1, 32, 64, 9, 32), (1, 3, 160, 64, 63, 32), (2, 2, 96, 128, 127, 64), (2, 5, 416, 64, 129, 64),
-               (6, 12, 288, 64, 65, 32), (1, 7, 1056, 64, 128, 64), (2, 8, 544, 128, 300, 64), (16, 8, 128, 64, 40, 32),
-               (1, 2, 4128, 64, 256, 64)]
+# reduction over (head, coordinate) whole, split a few ways and split into many, tiles that cross a head.  test_plans.py
+# holds the list to both tile sizes, whole and split, at both head sizes.
+GRAD_SHAPES = [
+    # 128 x 128 tiles
+    (1, 1, 32, 64, 9, 32), (1, 3, 160, 64, 63, 32), (2, 2, 96, 128, 127, 64), (2, 5, 416, 64, 129, 64),
+    (6, 12, 288, 64, 65, 32), (1, 7, 1056, 64, 128, 64), (2, 8, 544, 128, 300, 64), (16, 8, 128, 64, 40, 32),
+    (1, 2, 4128, 64, 256, 64), (1, 2, 96, 128, 70, 32),
+    # 256 x 256
+    (5, 1, 5152, 64, 262, 32), (2, 1, 8352, 128, 204, 32), (3, 32, 160, 64, 699, 32), (3, 17, 192, 128, 693, 32)]
 
 
 @pytest.mark.parametrize("shape", GRAD_SHAPES)

@@ -36,3 +36,56 @@ def test_short_reductions_take_the_small_tiles():
     """Encoder inference 82 us with 128 x 128 tiles, 97 with 256 x 256; a small training step with 64 x 128."""
     a, b = plans.proj([(8, 8, 4096, 64, 256), (2, 2, 512, 64, 64)])
     assert (a.tm, a.tn) == (128, 128) and (b.tm, b.tn) == (64, 128)
+
+
+def _tile(p):
+    return p.tm, p.tn
+
+
+TILES = [(64, 128), (128, 128), (128, 256), (256, 256)]
+
+
+def test_the_projection_is_tested_with_every_tile():
+    """At both head sizes: a ragged last reduction step, ragged keys, a ragged column tile where heads can leave one, a
+    split reduction, and (the tiles that stream) more ids than workgroups, some of them past the last tile."""
+    import test_gpu_tiles
+    seen = set()
+    for s, p in zip(test_gpu_tiles.SHAPES, plans.proj(test_gpu_tiles.SHAPES)):
+        B, H, n, d, k = s
+        if n % 64 and k % p.tm:
+            seen.add((_tile(p), d, "ragged rows"))
+            if B * H * d % p.tn:
+                seen.add((_tile(p), d, "ragged columns"))
+            if p.splits > 1:
+                seen.add((_tile(p), d, "split"))
+        if plans.ids(p) > plans.CUS and p.splits * p.tilesN * 2 % 8:
+            seen.add((_tile(p), d, "ids past the end"))
+    want = {(t, d, x) for t in TILES for d in (64, 128) for x in ("ragged rows", "ragged columns", "split", "ids past the end")}
+    want -= {(t, 128, "ragged columns") for t in TILES if t[1] == 128}          # a head is a whole column tile
+    want -= {((256, 256), d, "ids past the end") for d in (64, 128)}            # ids of that tile are not padded here
+    assert want <= seen, sorted(want - seen)
+
+
+def test_the_paper_order_products_are_tested_with_every_tile():
+    import test_gpu_paper_order as t
+    shapes = [s[:5] + (s[6],) for s in t.SHAPES] + t.TILE_SHAPES
+    seen = [set(), set()]
+    for s, both in zip(shapes, plans.fused(shapes)):
+        B, H, n, d, k, dm = s
+        for i, p in enumerate(both):
+            if k % p.tm:
+                seen[i].add(_tile(p))
+                if B > 1:
+                    seen[i].add((_tile(p), "batches"))
+                if i == 0 and n % 64 and dm % p.tn:
+                    seen[i].add((_tile(p), "ragged"))
+    assert {x for t_ in TILES for x in (t_, (t_, "batches"), (t_, "ragged"))} <= seen[0]
+    assert {x for t_ in TILES for x in (t_, (t_, "batches"))} <= seen[1]
+
+
+def test_the_gradient_products_are_tested_with_both_tiles_whole_and_split():
+    import test_gpu_tiles
+    shapes = test_gpu_tiles.GRAD_SHAPES
+    seen = {(p.fine, p.splits > 1, s[3]) for s, p in zip(shapes, plans.grad(shapes))
+            if s[2] % (128 if p.fine else 256) and s[4] % 64}
+    assert seen == {(fine, split, d) for fine in (False, True) for split in (False, True) for d in (64, 128)}
