@@ -92,9 +92,10 @@ def kernel_model(w, kernel: str):
         fl, by = stage_model(w, "key_state")
         return fl, by, by
     if kernel == "bwd_query_x":
-        fl = (6.0 if perf else 4.0 if d == 64 else 2.0) * n * mf * d * BH      # elu at head size 64: dS as well
         alg = es * 3 * BH * n * d                    # Q, dOut in; dQ out
-        return fl, alg, alg + 12 * BH * n + state    # lse in, g and the renormalised lse out, S/z/c
+        if not perf and d == 64:                     # elu at head size 64: dS, dz as well, nothing per query row
+            return 4.0 * n * mf * d * BH, alg, alg + 2 * state      # S, z in; one set of dS, dz partials (times the ranges)
+        return (6.0 if perf else 2.0) * n * mf * d * BH, alg, alg + 12 * BH * n + state    # lse in, g and the renormalised lse out, S/z/c
     if kernel == "bwd_query_y":
         alg = es * 2 * BH * n * d                    # Q, dOut in (dS, dz are small intermediates)
         return 2.0 * n * mf * d * BH, alg, alg + 8 * BH * n + state

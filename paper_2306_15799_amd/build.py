@@ -55,8 +55,8 @@ SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=und
 def build_sanitized(verbose: bool = False):
     """AddressSanitizer + UBSan build of the library's HOST side (validation, layout and workspace
     arithmetic, launch-fact cache, stage timer) plus the small driver program that exercises it without a
-    GPU (tests/host/abi_sanitizer_driver.cpp).  Returns (library path, driver path).  CPU machines only:
-    sanitizer runs on the GPU machine are not what this is for."""
+    GPU (tests/host/abi_sanitizer_driver.cpp).  Returns (library path, driver path).  For machines without a
+    GPU."""
     hipcc = find_hipcc()
     lib_cmd = [hipcc, *[f for f in HIPCC_FLAGS if f != "-O3"], "-O1", *SAN_FLAGS, "-I", os.path.join(ROOT, "include"),
                "-I", CSRC, *[os.path.join(CSRC, s) for s in SOURCES], "-o", SAN_LIB_PATH]

@@ -1,13 +1,15 @@
-// One 256 x 256 x 64 bf16 MFMA GEMM main loop for gfx950, shared by the three large contractions
-// of FLuRKA attention.  What differs between them (where the operands live, how a reduction step
-// maps to addresses, where the result goes) is supplied by a policy type:
+// One 256 x 256 x 64 bf16 MFMA GEMM main loop for gfx950: the tile for long reductions, where the matrix rate is the
+// bound (flurka_gemm_tile.h has the smaller tiles, flurka_plan.h the choice).  What differs between the contractions of
+// FLuRKA attention (where the operands live, how a reduction step maps to addresses, where the result goes) is supplied
+// by a policy type:
 //
 //   ProjPolicy<D>   K' = E K, V' = F V          A = E rows, B = X (positions x columns, read out of LDS
 //                                               with transposing loads), fp32 split partials
+//   ProjWidePolicy, TransformPolicy             the paper-order products Y = E X and K' = Y W^K, fp32 split partials
 //   GradXPolicy<D>  dK = E^T dK', dV = F^T dV'  A = (dK')^T image rows, B = E (same path as X above),
 //                                               bf16 result stored transposed into (B,H,n,d)
 //   GradEPolicy<D>  dE = sum_bh dK' K^T         A = dK' image rows, B = K rows (both contiguous along
-//                                               the reduction), fp32 split partials
+//                                               the reduction), fp32 split partials or bf16 results
 //
 // Structure (one wavefront per SIMD, 4 per workgroup, wave tile 128 x 128 = 4 x 4 MFMA tiles, so all
 // latency hiding happens inside one instruction stream): a 64-deep step is four 16-deep sub-steps of

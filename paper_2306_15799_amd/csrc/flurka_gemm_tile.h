@@ -303,8 +303,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams& g, const int bl
 // ---------------------------------------------------------------------------
 // Policies.  make(g, which, m0, n0, lane, wave) gives the descriptors, this lane's byte offsets and the byte
 // stride between the 1 KiB transfers of a step:
-//   row-major operand (A, direct B): transfer j of a wavefront is rows 32*j + 8*wave .. + 7 of the tile
-//   transposed B: transfer j is positions 16*j + 4*wave .. + 3
+//   row-major operand (A, direct B): transfer j of a wavefront is rows 8*NW*j + 8*wave .. + 7 of the tile
+//   transposed B: transfer j is positions (512/TN)*(NW*j + wave) .. + 512/TN - 1 (4 at TN = 128, 2 at TN = 256)
 // ---------------------------------------------------------------------------
 struct TileCtx {
     u32x4 rsA, rsB;

@@ -33,10 +33,14 @@ constexpr SplitGemmKind SPLIT_GEMM_KINDS[] = {{{256, 256, 128, 128}, 1.78, 1.55}
 // The partial results are the price of a split (written at the end, when nothing is left to read beside it, and
 // read again by the second stage, both at about 4.5 TB/s): 64 MiB with a 256 x 256 tile on every compute unit,
 // whatever the size of the problem.  Short reductions want the smaller tiles and few splits, long ones the large
-// tile.  Measured, forward passes, 256 x 256 with one split per compute unit against this rule's choice:
-//   k 256, n 4096, 64 heads of 64:    98.1 -> 81.0 us (128 x 128)     k 64, the same:    71.3 -> 56.7 us (64 x 128)
-//   k 256, n 16384, 64 heads of 64:  164.2 -> 156.7 us (128 x 256)    k 512, n 65536, 16 heads of 128: 437 us (stays)
-//   k 768 - 1129, n 8192 - 13280, 24 to 48 heads: 256 x 256 (192 to 240 workgroups) 185 - 285 us, 128 x 256 4 % more
+// tile.  Measured, projection + second stage, 256 x 256 with one split per compute unit against this rule's choice:
+//   k 256, n 4096, 64 heads of 64:   29.2 + 17.2 -> 24.7 + 11.8 us (128 x 128)
+//   k 256, n 16384, 64 heads of 64:  92 + 14.8 -> 86.8 + 11.8 (128 x 256)
+//   k 256, n 8192, 48 heads of 64:   35.2 + 14.8 -> 30.7 + 13.0 (128 x 256; devices differ: 30.7 - 38 for the same tile)
+//   k 64, n 512, 4 heads of 64:      11.1 + 7.3 -> 6.3 + 6.5 (64 x 128)
+//   k 512, n 65536, 16 heads of 128: 229 + 21 (stays)
+//   k 768 - 1129, n 8192 - 13280, 24 to 48 heads (stay, 192 to 240 workgroups): 104 - 177 + 22 - 31, with 128 x 256
+//   tiles 110 - 197 + 20
 inline SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_steps, double bytes) {
     const int cus = chip_cus();
     SplitGemmPlan best{};
@@ -145,9 +149,10 @@ struct GradEPlan {
 // results.  The tile and the split that the cost model (plan_pair, plus the traffic of the second pass) expects
 // to finish first win.  128 x 128 tiles: 1.15 us per step with two workgroups to a compute unit, 2.0 and 2.2 us
 // for the epilogues.  They take twice the operand traffic, so long reductions on both sides stay with 256 x 256;
-// elsewhere they need no or fewer partial results and fill the chip.  Training steps, 256 x 256 -> this rule:
-// 48 heads of 64, n 8192, k 256: 341 -> 333 us; 16 heads of 128, n 6016, k 300: 218 -> 204;
-// 64 heads of 128, n 65536, k 512 (stays): 1810, with 128 x 128 1905.
+// elsewhere they need no or fewer partial results and fill the chip.  Both products and the second pass, 256 x 256 ->
+// this rule: 48 heads of 64, n 8192, k 256: 74 + 9.7 -> 76.8 us (no second pass); 16 heads of 128, n 6016, k 300:
+// 62.6 -> 49.9; 128 heads of 64, n 512, k 64: 27.9 + 6.6 -> 13.6 + 7.1; training step of 64 heads of 128, n 65536, k 512
+// (stays): 1810, with 128 x 128 1905.
 constexpr double T_PAIR_STEP_US = 1.15, T_PAIR_EPILOGUE_E_US = 2.0, T_PAIR_EPILOGUE_X_US = 2.2;
 
 inline GradEPlan make_grad_e_plan(const Problem& p) {

@@ -72,7 +72,7 @@ def short(name: str) -> str:
 def trace(path: str, out: str, cmd: str) -> None:
     rows = list(csv.DictReader(open(path)))
     with open(out, "w") as f:
-        f.write("rocprofv3 kernel-trace summary\ncommand (run from the repository root on the GPU box):\n  " + cmd + "\n\n")
+        f.write("rocprofv3 kernel-trace summary\ncommand (run from the repository root):\n  " + cmd + "\n\n")
         f.write(f"{'kernel':90s} {'calls':>6s} {'avg_us':>10s} {'min_us':>10s} {'max_us':>10s} {'pct':>6s}\n")
         for r in rows:
             if "flurka" not in r["Name"]:
@@ -104,7 +104,7 @@ def traffic(raw_dir, workloads) -> None:
         cmd = ("rocprofv3 --pmc {c} --output-format csv -d " + raw_dir.rstrip("/") + "/pmc_{f}_{w} -o r -- python3 bench.py "
                "--workload {w} --steps 3 --warmup 1 --no-cpu-baseline --no-measured-peaks --no-configs")
         lines = [f"HBM traffic per dispatch, workload {w} (rocprofv3 --pmc, KiB per dispatch, mean over dispatches)",
-                 "commands (run from the repository root on the GPU box, one counter per run):",
+                 "commands (run from the repository root, one counter per run):",
                  "  " + cmd.format(c="FETCH_SIZE", f="fetch", w=w),
                  "  " + cmd.format(c="WRITE_SIZE", f="write", w=w),
                  f"calibration: torch's fp32->bf16 copy of Q ({elems} elements) reads {elems * 4 // 1024} KiB and writes {elems * 2 // 1024} KiB;",
@@ -137,7 +137,7 @@ def pmc(out: str, cmd: str, paths) -> None:
                 continue
             d[n][r["Counter_Name"]].append(float(r["Counter_Value"]))
     with open(out, "w") as f:
-        f.write("rocprofv3 --pmc summary (mean per dispatch)\ncommands (run from the repository root on the GPU box, "
+        f.write("rocprofv3 --pmc summary (mean per dispatch)\ncommands (run from the repository root, "
                 "one run per counter group):\n")
         for c in cmd.split(";;"):
             f.write("  " + c.strip() + "\n")

@@ -100,7 +100,7 @@ def main():
         return "    - " if (a is None or b is None) else f"{a / b:6.2f}"
 
     emit("Attention-level sweeps, forward, bf16, one MI355X (milliseconds, median of %d calls)" % args.steps)
-    emit("command (from the repository root on the GPU box): python -m paper_2306_15799_amd.sweeps --steps %d" % args.steps)
+    emit("command (from the repository root): python -m paper_2306_15799_amd.sweeps --steps %d" % args.steps)
     emit()
     emit("1. Sequence length (Sec. 4.1 \"Model speed\"): B=1 H=16 d=64 k=512 m=256")
     emit(f"{'N':>8s} {'flurka':>8s} {'kernel':>8s} {'linformer':>9s}   kernel/flurka  linformer/flurka")
