@@ -9,6 +9,26 @@
 
 namespace flurka {
 
+// A plan depends on sizes alone, and a call asks for it three or four times (buffer sizes, layout, launch): each thread
+// keeps its last few, so that neither the call's own questions nor a few alternating shapes work it out again.
+template <class Plan>
+struct KeptPlans {
+    static constexpr int PLANS = 8, SIZES = 6;
+    long key[PLANS][SIZES] = {};       // no plan has sizes of 0
+    Plan plan[PLANS] = {};
+    int next = 0;
+    template <class Make>
+    const Plan& get(const long (&sizes)[SIZES], Make&& make) {
+        for (int i = 0; i < PLANS; ++i)
+            if (memcmp(key[i], sizes, sizeof(sizes)) == 0) return plan[i];
+        const int i = next;
+        next = (next + 1) % PLANS;
+        plan[i] = make();
+        memcpy(key[i], sizes, sizeof(sizes));
+        return plan[i];
+    }
+};
+
 // ===========================================================================
 // Products that leave fp32 split partials: the projection, and the two products of the paper-order path
 // ===========================================================================
@@ -41,8 +61,7 @@ constexpr SplitGemmKind SPLIT_GEMM_KINDS[] = {{{256, 256, 128, 128}, 1.78, 1.55}
 //   k 512, n 65536, 16 heads of 128: 229 + 21 (stays)
 //   k 768 - 1129, n 8192 - 13280, 24 to 48 heads (stay, 192 to 240 workgroups): 104 - 177 + 22 - 31, with 128 x 256
 //   tiles 110 - 197 + 20
-inline SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_steps, double bytes) {
-    const int cus = chip_cus();
+inline SplitGemmPlan make_split_gemm_plan(int k, int batches, int cols, int total_steps, double bytes, int cus) {
     SplitGemmPlan best{};
     double best_t = -1.0;
     for (int kind = 0; kind < 4; ++kind) {
@@ -72,6 +91,13 @@ inline SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_ste
         }
     }
     return best;
+}
+
+inline SplitGemmPlan split_gemm_plan(int k, int batches, int cols, int total_steps, double bytes) {
+    static thread_local KeptPlans<SplitGemmPlan> kept;
+    const int cus = chip_cus();
+    const long sizes[] = {k, batches, cols, total_steps, (long)bytes, cus};
+    return kept.get(sizes, [&]() { return make_split_gemm_plan(k, batches, cols, total_steps, bytes, cus); });
 }
 
 inline SplitGemmPlan proj_plan(const Problem& p) {
@@ -155,7 +181,7 @@ struct GradEPlan {
 // (stays): 1810, with 128 x 128 1905.
 constexpr double T_PAIR_STEP_US = 1.15, T_PAIR_EPILOGUE_E_US = 2.0, T_PAIR_EPILOGUE_X_US = 2.2;
 
-inline GradEPlan make_grad_e_plan(const Problem& p) {
+inline GradEPlan make_grad_e_plan(const Problem& p, int cus) {
     GradEPlan best{};
     double best_t = -1.0;
     const int kp = (p.k + 63) / 64 * 64, steps_b = kp / GBK, rows_b = p.BH * p.d;
@@ -169,7 +195,7 @@ inline GradEPlan make_grad_e_plan(const Problem& p) {
         q.tilesM = fine ? positions : slots;
         q.tilesN = fine ? slots : positions;
         q.total_steps = p.BH * p.d / GBK;
-        q.resident = fine ? 2 * chip_cus() / 8 * 8 : chip_cus() / 8 * 8;
+        q.resident = fine ? 2 * cus / 8 * 8 : cus / 8 * 8;
         const int items_b = 8 * ((rows_b + tile - 1) / tile) * ((positions * 2 + 7) / 8);
         const double tb = fine ? steps_b * T_PAIR_STEP_US + T_PAIR_EPILOGUE_X_US : ((steps_b + 1) & ~1) * G_STEP_US + G_EPILOGUE_T_US;
         for (int want = 1; want <= (fine ? 32 : 8) && want <= q.total_steps; want += want < 8 ? 1 : 8) {
@@ -190,17 +216,11 @@ inline GradEPlan make_grad_e_plan(const Problem& p) {
     return best;
 }
 
-// The plan depends on sizes alone and a backward call asks for it four times (buffer sizes, layout, launch): the
-// thread's last one is kept.
-inline const GradEPlan& grad_e_plan(const Problem& p) {
-    static thread_local int key[5] = {0, 0, 0, 0, 0};
-    static thread_local GradEPlan plan{};
-    const int now[5] = {p.BH, p.n, p.d, p.k, chip_cus()};
-    if (memcmp(key, now, sizeof(now)) != 0) {
-        plan = make_grad_e_plan(p);
-        memcpy(key, now, sizeof(now));
-    }
-    return plan;
+inline GradEPlan grad_e_plan(const Problem& p) {
+    static thread_local KeptPlans<GradEPlan> kept;
+    const int cus = chip_cus();
+    const long sizes[] = {p.BH, p.n, p.d, p.k, cus, 1};
+    return kept.get(sizes, [&]() { return make_grad_e_plan(p, cus); });
 }
 
 }  // namespace flurka

@@ -14,13 +14,22 @@ SplitPlan = namedtuple("SplitPlan", "tm tn splits tilesM tilesN steps")
 GradPlan = namedtuple("GradPlan", "fine splits tilesM tilesN starters")
 
 
-def _ask(lines):
-    with tempfile.TemporaryDirectory() as tmp:
-        exe = os.path.join(tmp, "plans")
+_dir = None
+
+
+def _driver():
+    """The program, built once per test session."""
+    global _dir
+    if _dir is None:
+        _dir = tempfile.TemporaryDirectory()
         subprocess.run([build.find_hipcc(), "-x", "hip", "--offload-arch=gfx950", "-std=c++17", "-O1", "-I",
                         os.path.join(build.ROOT, "include"), "-I", build.CSRC, os.path.join(HERE, "host", "plan_driver.cpp"),
-                        "-o", exe], check=True, capture_output=True, text=True)
-        res = subprocess.run([exe], input="\n".join(lines), check=True, capture_output=True, text=True, timeout=300)
+                        "-o", os.path.join(_dir.name, "plans")], check=True, capture_output=True, text=True)
+    return os.path.join(_dir.name, "plans")
+
+
+def _ask(lines):
+    res = subprocess.run([_driver()], input="\n".join(lines), check=True, capture_output=True, text=True, timeout=300)
     return [[int(x) for x in line.split()] for line in res.stdout.splitlines()]
 
 

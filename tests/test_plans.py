@@ -89,3 +89,14 @@ def test_the_gradient_products_are_tested_with_both_tiles_whole_and_split():
     seen = {(p.fine, p.splits > 1, s[3]) for s, p in zip(shapes, plans.grad(shapes))
             if s[2] % (128 if p.fine else 256) and s[4] % 64}
     assert seen == {(fine, split, d) for fine in (False, True) for split in (False, True) for d in (64, 128)}
+
+
+def test_a_plan_does_not_depend_on_the_ones_before_it():
+    """Each thread keeps its last plans by their sizes: every shape alone, among many, and again in another order."""
+    shapes = _draws(40) + [(2, 2, 512, 64, 64), (2, 2, 512, 64, 65), (2, 2, 520, 64, 64), (2, 2, 512, 128, 64), (1, 4, 512, 64, 64)]
+    for ask in (plans.proj, plans.grad):
+        once = ask(shapes)
+        assert ask([s for s in shapes for _ in range(2)]) == [p for p in once for _ in range(2)]
+        assert ask(shapes[::-1] + shapes) == once[::-1] + once
+    for s, p in list(zip(shapes, plans.proj(shapes)))[-5:]:
+        assert plans.proj([s]) == [p]
